@@ -171,10 +171,10 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          (fftcg_plan_get_grid_sync reports where).
  *          Where the device also holds the whole grid of the turn pass,
  *          the row-inverse pass of every iteration but the last of a chunk
- *          goes on, after a second grid-wide barrier (for r.r and beta),
- *          into the next iteration's forward row pass on the same rows
- *          (p <- r + beta p, the pending x update, the row transform), so
- *          that r and p are not read back from memory.
+ *          goes on into the next iteration's forward row pass on the same
+ *          rows (p <- r + beta p, the pending x update, the row transform),
+ *          so that r and p are not read back from memory.  beta's r.r comes
+ *          from the sums that the one barrier returns (r.r, r.q, q.q).
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.
@@ -183,7 +183,7 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  * work can hold part of the device) abandons the solve, which is then
  * repeated from its start with mode 0 semantics; the plan keeps the separate
  * kernel from then on, until this call sets a mode again.  The result is
- * the same either way (up to the rounding of the r.r partial sums).
+ * the same either way (up to the rounding of r.r, about 1e-13).
  * FFTCG_EINVAL for a NULL plan or another mode.  Not to be called
  * concurrently with solves on the same plan.                               */
 int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode);

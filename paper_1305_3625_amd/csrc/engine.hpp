@@ -44,7 +44,7 @@ struct EngineOps {
                        hipStream_t s);
     // one CG iteration of a single slot with the update folded into the
     // row-inverse pass behind a grid-wide barrier (row_fwd, col, row_inv);
-    // token: unique per launch on the slot's partial-sum buffer.  Returns
+    // token (and token + 1): unique per launch on the slot's partial-sum buffer.  Returns
     // false (and runs the separate kernels) where grid_capable is false.
     bool (*iter_grid)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride, unsigned long long token,
                       hipStream_t s);

@@ -103,16 +103,14 @@ void iter_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, h
 void iter_fn(int prec, const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, hipStream_t s);
 
 // The same iteration for one slot with the update inside the row-inverse
-// pass (EpiCGU): the row-forward pass then reduces that pass's RB r.r
-// partials.  RB <= g4_blocks() (grid_capable_fn), so after an FP64 check,
-// which writes g4_blocks() of them (|r|^2 first, zeros after), the first RB
-// still hold the whole sum.
+// pass (EpiCGU): the row-forward pass then takes r.r from the state.  token
+// and token + 1 are the row-inverse pass's.
 template <typename W>
 void iter_grid_t(const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long token, hipStream_t s) {
     constexpr int RT = G<W>::ROW_THREADS, CT = G<W>::COL_THREADS, RB = G<W>::ROW_BLOCKS;
     const ByPtr sp{slot};
     const Tab<W> tab = tab_of<W>(pt);
-    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, RB,
+    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT, true>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, 0,
                        stride);
     hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, tab, sp);
     hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride, token);
@@ -132,8 +130,8 @@ bool iter_grid_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int stride
     return true;
 }
 
-// The turn pass saves the reads of r and p and one launch per iteration but
-// adds a second barrier.  Measured against the folded update alone (whole
+// The turn pass saves the reads of r and p and one launch per iteration.
+// Measured when it still had a second barrier, against the folded update alone (whole
 // mixed solves, alternating in one process): padded L = 2048 +4.2%, L = 256
 // +2.2%, L = 512 +0.5%, padded L = 512 FP64 +1.9%, periodic M = 256 / 512 /
 // 2048 +1.2 / +2.4 / +5.2%; but padded L = 1024 (M = 2048) -1.2% and
@@ -151,8 +149,12 @@ void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, 
     const ByPtr sp{slot};
     const Tab<W> tab = tab_of<W>(pt);
     if (pass == 0) {
-        hipExtLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, e0, e1, 0,
-                              tab, sp, grid ? RB : g4_blocks(), stride);
+        if (grid)
+            hipExtLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT, true>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s,
+                                  e0, e1, 0, tab, sp, 0, stride);
+        else
+            hipExtLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, e0,
+                                  e1, 0, tab, sp, g4_blocks(), stride);
     } else if (pass == 1) {
         hipExtLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, e0, e1, 0,
                               tab, sp);
@@ -228,8 +230,8 @@ void iter_grid_chunk_t(const PlanTabs& pt, const SlotDesc* slot, int stride, uns
             constexpr int RT = G<W>::ROW_THREADS, CT = G<W>::COL_THREADS, RB = G<W>::ROW_BLOCKS;
             const ByPtr sp{slot};
             const Tab<W> tab = tab_of<W>(pt);
-            hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab,
-                               sp, RB, stride);
+            hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT, true>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s,
+                               tab, sp, 0, stride);
             hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, tab, sp);
             for (int k = 1; k < K; ++k) {
                 const unsigned long long t = *token + 1;
@@ -239,11 +241,12 @@ void iter_grid_chunk_t(const PlanTabs& pt, const SlotDesc* slot, int stride, uns
                                    sp);
             }
             hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride,
-                               ++*token);
+                               *token + 1);
+            *token += 2;
             return;
         }
     }
-    for (int k = 0; k < K; ++k) iter_grid_t<W>(pt, slot, stride, ++*token, s);
+    for (int k = 0; k < K; ++k, *token += 2) iter_grid_t<W>(pt, slot, stride, *token + 1, s);
 }
 
 void iter_grid_chunk_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long* token,

@@ -517,6 +517,22 @@ __device__ __forceinline__ double block_reduce_n(const double* acc, double* sh) 
     return r;
 }
 
+// N block sums for any block size, each in block_sum's order, to out[0..N)
+// in LDS (valid after the next barrier; its readers of before must be done).
+template <int NT, int N>
+__device__ __forceinline__ void block_sums(const double* acc, double* sh, double* out) {
+    if constexpr (NT % 64 == 0) {
+        const double v = block_reduce_n<NT, N, 0u>(acc, sh);
+        if (threadIdx.x < N) out[threadIdx.x] = v;
+    } else {
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+            const double v = block_sum<NT>(acc[a], sh);
+            if (threadIdx.x == 0) out[a] = v;
+        }
+    }
+}
+
 // Sum of n partials in a fixed order (thread t takes t, t+NT, ...).
 template <int NT>
 __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int n, double* sh) {

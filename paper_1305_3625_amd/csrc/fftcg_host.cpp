@@ -544,9 +544,7 @@ extern "C" int fftcg_profile_iteration(fftcg_plan_t plan, int precision, const d
         for (size_t i = 0; i < seq.size(); ++i) {
             const int pass = seq[i];
             unsigned long long token = 0;
-            if (grid && pass == 2) {
-                token = ++w->grid_token;
-            } else if (pass == 4) {
+            if (grid && (pass == 2 || pass == 4)) {
                 token = w->grid_token + 1;
                 w->grid_token += 2;
             }

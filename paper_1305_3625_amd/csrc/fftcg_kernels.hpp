@@ -308,7 +308,9 @@ struct ProApply {
 // CG iteration: x_acc += alpha p_old (pending update of the last iteration),
 // p = r + beta p_old (or p = r on restart), then transform p.
 // W: working precision of r, p; XA: accumulator (double: x itself; float: e).
-template <typename W, typename XA, int NT>
+// FOLD: r.r comes from the state, where the folded update (EpiCGU) or the
+// check left it, instead of from the update kernel's partials.
+template <typename W, typename XA, int NT, bool FOLD = false>
 struct ProCG {
     static constexpr int NACC = 0;
     struct Sh {
@@ -320,7 +322,7 @@ struct ProCG {
     static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int npart_rr, int stride) {
         if (!GateIter::ok(sd)) return false;
         SolveState* st = sd.st;
-        const double rr = sum_partials<NT>(sd.part + PS_RR * stride, npart_rr, sh.red);
+        const double rr = FOLD ? st->rho_next : sum_partials<NT>(sd.part + PS_RR * stride, npart_rr, sh.red);
         if (check_due(st, rr)) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st->pause = 1;
             return false;
@@ -734,14 +736,18 @@ struct EpiCG {
 };
 
 // The CG epilogue with the residual update folded in: q = A p never leaves
-// registers.  After every workgroup has published its p.q
-// partial (a grid-wide barrier; the host launches this only where the whole
-// grid fits the device at once), each workgroup forms alpha = rho / (p.q)
-// from all partials in the same order and updates r <- r - alpha q on its
-// own rows, with the r.r partials of the next iteration.  It replaces the
-// separate update kernel: one pass over q fewer, and one kernel fewer.
+// registers.  Every workgroup reduces four sums over its own rows, p.q, r.r,
+// r.q and q.q (FP64), meets the others at a grid-wide barrier that returns
+// the totals (grid_sums; the host launches this only where the whole grid
+// fits the device at once), forms alpha = r.r / p.q and updates r <- r -
+// alpha q on its own rows.  r.r of the updated residual, which the next beta
+// and the check decision need, follows from the same totals:
+//   |r - a q|^2 = r.r - 2 a (r.q) + a^2 (q.q),
+// so that no second barrier is needed for it.  It replaces the separate
+// update kernel: one pass over q fewer, and one kernel fewer.
 template <typename W>
 struct EpiCGU : EpiCG<W> {
+    static constexpr int NACC = 4;
     static constexpr bool UPD = true;
 };
 template <class E, class = void>
@@ -753,46 +759,98 @@ struct EpiUpd<E, decltype((void)E::UPD)> {
     static constexpr bool value = E::UPD;
 };
 
-// Grid-wide barrier without read-modify-write traffic on one address (1,024
-// atomic additions to one counter serialise where they are performed and
-// cost tens of microseconds).  Each launch carries a token that no other
-// launch on the same partial-sum buffer uses.  A workgroup arrives by
-// storing the token to its own word flags[b]; workgroup 0 waits until every
-// flag holds the token, then stores it to the release word *rel, which the
-// others wait for.  All of these are agent-scope atomics, performed where
-// every XCD sees them, and each step waits for the previous step's value, so
-// no cache-wide fence is needed (a release/acquire pair at agent scope
-// writes back and invalidates the L2 of every workgroup's XCD, which costs
-// more than the whole update).  Waits are bounded: after `limit` ticks of
-// the 100 MHz constant clock the workgroup gives up and false is returned (a
-// grid that is not resident as a whole cannot complete the barrier).
+// r.r after the update from the totals t = {p.q, r.r, r.q, q.q} (a: alpha in
+// the working precision, as the update uses it).  Where the residual falls
+// by so much that the difference cancels (below a hundredth of a^2 q.q; an
+// ordinary iteration leaves a tenth or more) the caller sums it anew behind
+// a second barrier, so the relative error stays near 1e-13.  False also for
+// NaN.
+__device__ __forceinline__ bool next_rr(const double* t, double a, double* rr) {
+    *rr = fma(a, fma(a, t[3], -2.0 * t[2]), t[1]);
+    return *rr > 0.01 * (a * a * t[3]);
+}
+
+// The sums of N per-thread values over the whole grid, in every thread
+// (tot), with a grid-wide barrier on the way, without read-modify-write
+// traffic on one address (1,024 atomic additions to one counter serialise
+// where they are performed and cost tens of microseconds).  Each call
+// carries a token that no other call on the same partial-sum buffer uses.  A
+// workgroup stores its N partials (set a at part[sets[a] stride + block]),
+// waits for them to complete and arrives by storing the token to its own
+// word flags[b]; workgroup 0 waits until every flag holds the token, sums
+// the partials (thread t takes t, t + NT, ..., then the block sum), stores
+// the totals and then the token to the release line rel, which the others
+// wait for (rel[0] the token, rel[1 + a] the totals).  One workgroup summing
+// for all keeps the traffic at the coherence point to one read of the
+// partials: with every workgroup reading all of them, 1,024 workgroups would
+// move 33 MB per barrier.  All of these are agent-scope atomics, performed
+// where every XCD sees them, and each step waits for the previous step's
+// value, so no cache-wide fence is needed (a release/acquire pair at agent
+// scope writes back and invalidates the L2 of every workgroup's XCD, which
+// costs more than the whole update).  Waits are bounded: after `limit` ticks
+// of the 100 MHz constant clock the workgroup gives up and false is returned
+// (a grid that is not resident as a whole cannot complete the barrier).
 // Called by every thread of the workgroup; returns the same value in all.
-template <int NT>
-__device__ inline bool grid_barrier(unsigned long long* flags, unsigned long long* rel, unsigned long long token,
-                                    long long limit) {
+// sh must hold N * (NT + 63) / 64 doubles.
+template <int NT, int N>
+__device__ inline bool grid_sums(const double* acc, double* part, int stride, unsigned long long token,
+                                 long long limit, double* sh, double* tot) {
+    constexpr int sets[4] = {PS_PQ, PS_RR, PS_RQ, PS_QQ};
+    static_assert(N <= 4, "four sets");
+    __shared__ double s_tot[N];
     __shared__ int s_ok;
     const int tid = threadIdx.x;
     const unsigned int nb = gridDim.x;
+    auto* flags = reinterpret_cast<unsigned long long*>(part + PS_BAR * stride);
+    auto* rel = reinterpret_cast<unsigned long long*>(part + PS_BARREL * stride);
+    auto put = [](unsigned long long* p, double v) {
+        (void)__hip_atomic_exchange(p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto get = [](const unsigned long long* p) {
+        return __builtin_bit_cast(double, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    auto setp = [&](int a) {  // partials of set a (a small: no table in memory)
+        const int ps = a == 0 ? sets[0] : (a == 1 ? sets[1] : (a == 2 ? sets[2] : sets[3]));
+        return reinterpret_cast<unsigned long long*>(part + ps * stride);
+    };
+    block_sums<NT, N>(acc, sh, s_tot);
+    __syncthreads();
+    for (int a = tid; a < N; a += NT) put(setp(a) + blockIdx.x, s_tot[a]);
+    __builtin_amdgcn_s_waitcnt(0);  // the first wave's exchanges are complete
     if (tid == 0) __hip_atomic_store(flags + blockIdx.x, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
     int ok = 1;
     if (blockIdx.x == 0) {
         for (;;) {
-            int mine = 1;
+            int here = 1;
             for (unsigned int i = tid; i < nb; i += NT)
-                mine &= __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
+                here &= __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
             const int expired = (long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit;
             // both decisions are taken by the whole workgroup
-            if (__syncthreads_and(mine)) break;
+            if (__syncthreads_and(here)) break;
             if (__syncthreads_or(expired)) {
                 ok = 0;
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        if (ok && tid == 0) __hip_atomic_store(rel, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ok) {
+            double s[N];
+#pragma unroll
+            for (int a = 0; a < N; ++a) s[a] = 0.0;
+            for (unsigned int i = tid; i < nb; i += NT)
+#pragma unroll
+                for (int a = 0; a < N; ++a) s[a] += get(setp(a) + i);
+            block_sums<NT, N>(s, sh, s_tot);
+            __syncthreads();
+            for (int a = tid; a < N; a += NT) put(rel + 1 + a, s_tot[a]);
+            __builtin_amdgcn_s_waitcnt(0);
+            if (tid == 0) __hip_atomic_store(rel, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
     } else {
-        if (tid == 0) {
+        if (tid < cmin(N, NT)) {
             while (__hip_atomic_load(rel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != token) {
                 if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit) {
                     ok = 0;
@@ -800,11 +858,15 @@ __device__ inline bool grid_barrier(unsigned long long* flags, unsigned long lon
                 }
                 __builtin_amdgcn_s_sleep(1);
             }
-            s_ok = ok;
+            if (ok)
+                for (int a = tid; a < N; a += NT) s_tot[a] = get(rel + 1 + a);
+            if (tid == 0) s_ok = ok;
         }
         __syncthreads();
         ok = s_ok;
     }
+#pragma unroll
+    for (int a = 0; a < N; ++a) tot[a] = s_tot[a];
     return ok != 0;
 }
 
@@ -919,11 +981,11 @@ struct EpiPreT<Epi, true> {
 // into the half spectrum of the real row, and the W stores of the
 // workgroup's rows (block rb).
 template <typename T, int M, int PAD, int NT>
-__device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& tab, const SlotDesc& sd, int rb) {
+__device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& tab, const SlotDesc& sd, int rb,
+                                            const int tid) {
     using G = Geo<T, M, PAD>;
     constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L, TT = G::TT;
     constexpr int WORDS = G::ROW_WORDS;
-    const int tid = threadIdx.x;
     const int rl = tid / P, j = tid % P;
     LdsLay<T, 1, 4, 1> lay{lds + rl * WORDS, 0};
     constexpr int NSTG = fft_nstages(N);
@@ -1005,7 +1067,7 @@ __global__ void __launch_bounds__(NT) k_row_fwd(Tab<T> tab, Slot slot, int npart
             for (int r = 0; r < RK; ++r)
                 v[u * R1 + r] = Pro::template load2<L>(sd, sh, row, 2 * ((j + u * P) + r * (N / R1)), &acc);
     }
-    row_fwd_out<T, M, PAD, NT>(v, lds, tab, sd, rb);
+    row_fwd_out<T, M, PAD, NT>(v, lds, tab, sd, rb, tid);
     if constexpr (LATE && Pro::PREF && (E / R1) * RK <= 8) {
 #pragma unroll
         for (int u = 0; u < E / R1; ++u)
@@ -1127,8 +1189,8 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
         }
 }
 
-// Body of the row-inverse pass; token: the grid-wide barrier's arrival
-// token of this launch (epilogues with the folded update only).
+// Body of the row-inverse pass; token, token + 1: the grid-wide barriers'
+// arrival tokens of this launch (epilogues with the folded update only).
 // FWD (with the folded update only): the pass goes on into the next
 // iteration's forward row pass on the same rows (k_row_turn).
 template <typename T, int M, int PAD, class Epi, class Slot, int NT, bool FWD = false>
@@ -1255,13 +1317,22 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             }
         }
     if constexpr (UPD) {
-        // r of the same pairs, requested before the reduction and the barrier
-        // so that its latency hides behind them
+        // r of the same pairs, and their parts of r.r, r.q and q.q
 #pragma unroll
         for (int u = 0; u < E / RL; ++u)
 #pragma unroll
             for (int r = 0; r < RK; ++r)
                 rk[u * RK + r] = ld2<T>(reinterpret_cast<const T*>(sd.r) + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL)));
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            const cx<double> rv = mkc((double)rk[i].x, (double)rk[i].y), qv = mkc((double)qk[i].x, (double)qk[i].y);
+            acc[1] += rv.x * rv.x + rv.y * rv.y;
+            acc[2] += rv.x * qv.x + rv.y * qv.y;
+            acc[3] += qv.x * qv.x + qv.y * qv.y;
+            // one pair's doubles at a time: widened all together they would
+            // spill on the largest rows
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     if constexpr (Epi::NACC > 0 && !UPD) {
         double* part = sd.part;
@@ -1286,17 +1357,6 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     }
     if constexpr (UPD) {
         SolveState* st = sd.st;
-        auto* pq_bits = reinterpret_cast<unsigned long long*>(sd.part + PS_PQ * stride);
-        auto* bar_rel = reinterpret_cast<unsigned long long*>(sd.part + PS_BARREL * stride);
-        const double s_pq = block_sum<NT>(acc[0], red);
-        if (tid == 0) {
-            // the partial is exchanged atomically and its completion awaited
-            // (s_waitcnt 0) before the arrival is stored
-            (void)__hip_atomic_exchange(pq_bits + blockIdx.x, __builtin_bit_cast(unsigned long long, s_pq),
-                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_s_waitcnt(0);
-        }
-        auto* bar_flags = reinterpret_cast<unsigned long long*>(sd.part + PS_BAR * stride);
         // the grid was not resident as a whole: the solve is abandoned and
         // the host repeats it with the separate update kernel
         auto give_up = [&]() {
@@ -1306,17 +1366,12 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
                 publish_status(sd, 1, ST_EGRID, st->gen, st->iters, st->last_check_iter);
             }
         };
-        if (!grid_barrier<NT>(bar_flags, bar_rel, token, st->bar_limit)) {
+        double tot[4];  // p.q, r.r, r.q, q.q
+        if (!grid_sums<NT, 4>(acc, sd.part, stride, token, st->bar_limit, red, tot)) {
             give_up();
             return;
         }
-        // every partial: strided per thread, then the block sum (the update
-        // kernel's order when both reduce with the same thread count)
-        double spq = 0.0;
-        for (int i = tid; i < (int)gridDim.x; i += NT)
-            spq += __builtin_bit_cast(double, __hip_atomic_load(pq_bits + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const double pq = block_sum<NT>(spq, red);
-        const double rho = st->rho_cur;
+        const double pq = tot[0], rho = tot[1];
         if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
             if (blockIdx.x == 0 && tid == 0) {
                 st->status = ST_EBREAKDOWN;
@@ -1326,14 +1381,9 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             return;
         }
         const double alpha = rho / pq;
-        if (blockIdx.x == 0 && tid == 0) {
-            st->alpha = alpha;
-            st->rho_prev = rho;
-            st->iters += 1;
-            st->restart = 0;
-        }
         const T a = (T)alpha;
-        double rr = 0.0;
+        double rrn;
+        const bool sure = next_rr(tot, (double)a, &rrn);
 #pragma unroll
         for (int u = 0; u < E / RL; ++u)
 #pragma unroll
@@ -1343,39 +1393,37 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
                 rv.x -= a * qv.x;
                 rv.y -= a * qv.y;
                 st2<T>(reinterpret_cast<T*>(sd.r) + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL)), rv);
-                rr += (double)rv.x * rv.x + (double)rv.y * rv.y;
-                if constexpr (FWD) rk[u * RK + r] = rv;
+                rk[u * RK + r] = rv;
             }
-        const double srr = block_sum<NT>(rr, red);
-        if constexpr (!FWD) {
-            if (tid == 0) sd.part[PS_RR * stride + blockIdx.x] = srr;
-        } else {
-            // The next iteration's forward row pass on the same rows, as
-            // ProCG in k_row_fwd computes it: beta = r.r / rho from every
-            // workgroup's r.r partial (a second barrier, token + 1; the same
-            // summation order), the check decision, p <- r + beta p, the
-            // transform, and the pending x update x <- x + alpha p_old.  The
-            // forward pass's first radix equals this pass's last, so the
-            // thread holds the same pairs of r and p in both.
-            auto* rr_bits = reinterpret_cast<unsigned long long*>(sd.part + PS_RR * stride);
-            if (tid == 0) {
-                (void)__hip_atomic_exchange(rr_bits + blockIdx.x, __builtin_bit_cast(unsigned long long, srr),
-                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_s_waitcnt(0);
-            }
-            if (!grid_barrier<NT>(bar_flags, bar_rel, token + 1, st->bar_limit)) {
+        // the totals are the same in every workgroup, so all take this branch
+        // or none
+        if (!sure) {
+            double rr[1] = {0.0};
+#pragma unroll
+            for (int i = 0; i < NO; ++i) rr[0] += (double)rk[i].x * rk[i].x + (double)rk[i].y * rk[i].y;
+            // set 0 of the partials again (its first use ended with the barrier)
+            if (!grid_sums<NT, 1>(rr, sd.part, stride, token + 1, st->bar_limit, red, &rrn)) {
                 give_up();
                 return;
             }
-            double s2 = 0.0;
-            for (int i = tid; i < (int)gridDim.x; i += NT)
-                s2 += __builtin_bit_cast(double, __hip_atomic_load(rr_bits + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            const double rrn = block_sum<NT>(s2, red);
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            st->alpha = alpha;
+            st->rho_prev = rho;
+            st->rho_next = rrn;
+            st->iters += 1;
+            st->restart = 0;
+        }
+        if constexpr (FWD) {
+            // The next iteration's forward row pass on the same rows, as
+            // ProCG in k_row_fwd computes it: the check decision, p <- r +
+            // beta p, the transform, and the pending x update x <- x + alpha
+            // p_old.  The forward pass's first radix equals this pass's last,
+            // so the thread holds the same pairs of r and p in both.
             if (check_due(st, rrn, s_iters + 1)) {
                 if (blockIdx.x == 0 && tid == 0) st->pause = 1;
                 return;
             }
-            if (blockIdx.x == 0 && tid == 0) st->rho_cur = rrn;
             const T beta = (T)(rrn / rho);
             constexpr int R1 = NSTG > 0 ? fft_radix(N, false, 0) : 1;
             static_assert(R1 == RL, "forward first radix and inverse last radix");
@@ -1408,7 +1456,9 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             // index is kept uniform
             Tab<T> tab2 = tab;
             asm volatile("" : "+s"(tab2.tw));
-            row_fwd_out<T, M, PAD, NT>(v2, lds, tab2, sd, __builtin_amdgcn_readfirstlane(row0 / RPW));
+            int tid2 = tid;
+            asm volatile("" : "+v"(tid2));
+            row_fwd_out<T, M, PAD, NT>(v2, lds, tab2, sd, __builtin_amdgcn_readfirstlane(row0 / RPW), tid2);
         }
     }
 }
@@ -1428,7 +1478,7 @@ __global__ void __launch_bounds__(NT) k_row_inv_upd(Tab<T> tab, Slot slot, int s
 
 // One CG iteration's turn in one pass (k_row_inv_upd followed by k_row_fwd):
 // q's row inverse, the folded update, and the next direction's forward row
-// transform, with two grid-wide barriers (tokens token and token + 1).  Four
+// transform, with one grid-wide barrier.  Four
 // waves per SIMD are asked for: the whole grid must be resident (four
 // 256-thread workgroups per CU at M = 4096), which caps it at 128 VGPRs.
 template <typename T, int M, int PAD, class Slot, int NT>
@@ -1578,6 +1628,7 @@ __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, i
     if (threadIdx.x == 0) {
         if (st->checks == 0) st->dbar = DSUM / (double)n;
         s_update = check_decide(st, R, X, B, RW, BAD, DIFF, dmin);
+        if (s_update) st->rho_next = RW;  // r.r for the folded update's iterations
         // preconditioned CG: z = P^{-1} r of the replaced residual comes next
         st->need_pre = (s_update && st->pcg) ? 1 : 0;
         publish_status(sd, st->done, st->status, st->gen, st->iters, st->last_check_iter);

@@ -34,6 +34,7 @@ struct SolveState {
     double rho_ref;      // r.r right after the last check (residual replacement)
     double delta2;       // reliable-update threshold: check when r.r <= delta2 * rho_ref
     double dbar;         // mean of d (first check), for the preconditioner
+    double rho_next;     // r.r of the coming iteration with the folded update (row-inverse kernel or check finaliser)
     int iters;           // CG iterations done
     int maxit;
     int refresh;         // FP64 check period (0 = only at candidate convergence)
@@ -93,8 +94,10 @@ enum PartSet {
     PS_RZ = 9,        // r . z per block of the preconditioner's row-inverse pass
     PS_CHK_DSUM = 10, // sum of d (for its mean)
     PS_BAR = 11,      // grid-wide barrier: arrival token per block (64-bit words)
-    PS_BARREL = 12,   // [0] the barrier's release word (64 bits)
-    NPART_SETS = 13
+    PS_BARREL = 12,   // the barrier's release word and the totals (64-bit words)
+    PS_RQ = 13,       // r . q per block of the row-inverse pass with the folded update
+    PS_QQ = 14,       // q . q, likewise
+    NPART_SETS = 15
 };
 
 }  // namespace fftcg
