@@ -175,6 +175,13 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          rows (p <- r + beta p, the pending x update, the row transform),
  *          so that r and p are not read back from memory.  beta's r.r comes
  *          from the sums that the one barrier returns (r.r, r.q, q.q).
+ *          On grids with 64 <= M <= 1024 a solve runs whole iterations in
+ *          one resident kernel instead, with bitwise the result of mode 3:
+ *          r, p, x and d stay in registers between checks, and the
+ *          workgroups of one XCD (M <= 256 and the smaller row counts) or of
+ *          the whole device meet three times per iteration.  At most one
+ *          such kernel per XCD, or one on the whole device, runs at a time
+ *          in a process; a solve that finds no room runs the passes.
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.
@@ -231,7 +238,9 @@ int fftcg_profile_apply(fftcg_plan_t plan, int precision, const double* d,
  * per launch of [0] the forward row pass (with the CG prologue), [1] the
  * column pass, [2] the row-inverse pass (with the folded update when it
  * applies, fftcg_plan_set_grid_sync), [3] the separate update kernel (0 when
- * folded), [4] the turn pass (0 when not used).  The launches follow a
+ * folded), [4] the turn pass (0 when not used).  (On grids where a solve runs
+ * the resident kernel, fftcg_plan_set_grid_sync, these are the passes of mode
+ * 3, whose arithmetic it repeats.)  The launches follow a
  * solve's chunk: with the turn pass, row_fwd, col, (turn, col) x (reps - 1),
  * row_inv (so [0] and [2] are single launches; reps >= 2), else reps times
  * each pass.  *folded (HOST, may be NULL) = 0 separate update, 1 folded,

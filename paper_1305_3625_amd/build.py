@@ -27,6 +27,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 CXXFLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
+    # multiply-adds are contracted within one source expression only: the same
+    # expression then rounds alike in every kernel it is inlined into, so the
+    # engines' variants of one iteration agree bitwise (contraction across
+    # expressions depends on the surrounding code; the instruction counts of
+    # the passes are the same either way)
+    "-ffp-contract=on",
     # code objects loadable by the HIP runtime bundled with PyTorch
     "-mcode-object-version=5",
     # packed FP32 instructions stay off (hand-written or compiler-made)
@@ -49,6 +55,13 @@ def engine_radix(m: int) -> int:
     251/468/588/797.  L = 2048, one solve, per product (eps 1e-3): radix 16
     95.5 us, radix 8 117.9 us."""
     return 4 if m <= 256 else (8 if m <= 2048 else 16)
+
+
+def engine_row_threads(m: int, pad: int) -> int:
+    """Threads of a row-pass workgroup (and with them the rows and the number
+    of workgroups of the resident kernel)."""
+    return {(64, 0): 64, (64, 1): 64, (128, 0): 64, (128, 1): 64, (256, 1): 128, (512, 1): 64, (512, 0): 128,
+            (1024, 1): 128}.get((m, pad), 256)
 
 
 ENGINE_SIZES = [(m, 0, engine_radix(m)) for m in (2, 4, 8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192)] + \
@@ -81,8 +94,8 @@ def _jobs(build_dir, extra):
         lang = ["-x", "hip"] if s.endswith(".cpp") else []
         yield [HIPCC, *CXXFLAGS, *extra, *lang, "-c", src, "-o", obj(os.path.splitext(s)[0])]
     for m, pad, maxr in ENGINE_SIZES:
-        yield [HIPCC, *CXXFLAGS, *extra, f"-DFFTCG_M={m}", f"-DFFTCG_PAD={pad}", f"-DFFTCG_MAXR={maxr}", "-c",
-               os.path.join(CSRC, "engine_inst.hip"), "-o", obj(f"engine_{m}_{pad}")]
+        yield [HIPCC, *CXXFLAGS, *extra, f"-DFFTCG_M={m}", f"-DFFTCG_PAD={pad}", f"-DFFTCG_MAXR={maxr}",
+               f"-DFFTCG_ROW_NT={engine_row_threads(m, pad)}", "-c", os.path.join(CSRC, "engine_inst.hip"), "-o", obj(f"engine_{m}_{pad}")]
     for m, pad, maxr in FUSED_SIZES:
         yield [HIPCC, *CXXFLAGS, *extra, f"-DFFTCG_M={m}", f"-DFFTCG_PAD={pad}", f"-DFFTCG_MAXR={maxr}", "-c",
                os.path.join(CSRC, "fused_inst.hip"), "-o", obj(f"fused_{m}_{pad}")]

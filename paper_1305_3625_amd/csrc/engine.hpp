@@ -42,12 +42,6 @@ struct EngineOps {
     void (*check0)(int prec, const PlanTabs& t, const SlotDesc* slots, int nslots, int stride, hipStream_t s);
     void (*check0_pcg)(int prec, const PlanTabs& t, const SlotDesc* slots, int nslots, int stride,
                        hipStream_t s);
-    // one CG iteration of a single slot with the update folded into the
-    // row-inverse pass behind a grid-wide barrier (row_fwd, col, row_inv);
-    // token (and token + 1): unique per launch on the slot's partial-sum buffer.  Returns
-    // false (and runs the separate kernels) where grid_capable is false.
-    bool (*iter_grid)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride, unsigned long long token,
-                      hipStream_t s);
     // one pass of a plain-CG iteration of one slot (measurement aid): 0 the
     // forward row pass, 1 the column pass, 2 the row-inverse pass (with the
     // folded update when grid), 3 the separate update (nothing when grid),
@@ -55,20 +49,33 @@ struct EngineOps {
     // records ev0 as the kernel starts and ev1 as it ends
     void (*iter_pass)(int prec, int pass, bool grid, const PlanTabs& t, const SlotDesc* slot, int stride,
                       unsigned long long token, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
-    // whether iter_grid applies on the current device: the whole
-    // row-inverse grid resident at once, and no more r.r partials per pass
-    // than the update kernel writes
+    // whether the folded update (below) applies on the current device: the
+    // whole row-inverse grid resident at once
     bool (*grid_capable)(int prec);
-    // K (>= 1) such iterations of a single slot, as a chunk: with turn, the
-    // row-inverse pass of every iteration but the last goes on into the next
-    // iteration's forward row pass (k_row_turn), so the chunk launches
-    // row_fwd, col, (turn, col) x (K - 1), row_inv; without it, K times
-    // iter_grid.  *token is advanced past every token the launches use.
+    // K (>= 1) CG iterations of a single slot, as a chunk, with the update
+    // folded into the row-inverse pass behind a grid-wide barrier.  With
+    // turn, the row-inverse pass of every iteration but the last goes on into
+    // the next iteration's forward row pass (k_row_turn), so the chunk
+    // launches row_fwd, col, (turn, col) x (K - 1), row_inv; without it, K
+    // times row_fwd, col, row_inv.  *token is advanced past every token the
+    // launches use (each unique on the slot's partial-sum buffer).
     void (*iter_grid_chunk)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride,
                             unsigned long long* token, int K, bool turn, hipStream_t s);
     // whether the turn pass is resident as a whole as well (implies
     // grid_capable)
     bool (*turn_capable)(int prec);
+    // up to K iterations of a single slot in one launch (k_cg_resident; slot:
+    // the descriptor itself; words: kMeetWords 64-bit words), ending early
+    // when an FP64 check is due.  xcd: the XCD it runs on, where
+    // resident_xcds is 1.  *token is advanced past every token the launch can
+    // use (they grow with every launch on the same words).
+    void (*resident)(int prec, const PlanTabs& t, const SlotDesc& slot, unsigned long long* words, int xcd,
+                     unsigned long long* token, int K, hipStream_t s);
+    // the XCDs it occupies: 1 or 8
+    int (*resident_xcds)(int prec);
+    // whether resident applies on the current device (built for this grid and
+    // resident as a whole; implies grid_capable)
+    bool (*resident_capable)(int prec);
 };
 
 const EngineOps* find_engine(int M, int pad);

@@ -6,6 +6,7 @@
 
 #include "engine.hpp"
 #include "fftcg_kernels.hpp"
+#include "resident_kernels.hpp"
 
 #ifndef FFTCG_M
 #error "FFTCG_M must be defined"
@@ -116,31 +117,25 @@ void iter_grid_t(const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned 
     hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride, token);
 }
 
-bool iter_grid_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long token,
-                  hipStream_t s) {
-    const bool fits = prec == 0 ? G<double>::ROW_BLOCKS <= g4_blocks() : G<float>::ROW_BLOCKS <= g4_blocks();
-    if (!fits) {
-        iter_fn(prec, pt, slot, 1, stride, s);
-        return false;
-    }
-    if (prec == 0)
-        iter_grid_t<double>(pt, slot, stride, token, s);
-    else
-        iter_grid_t<float>(pt, slot, stride, token, s);
-    return true;
-}
+// Resident CG is built where the iteration is latency-bound and its vectors
+// fit the registers.  Whole solves to 1e-10, folded passes (mode 3) -> resident:
+// periodic M = 64 FP64 759 -> 302 us, padded M = 256 mixed 1465 -> 711 us,
+// M = 512 mixed 1953 -> 1405 us, M = 1024 FP64 3250 -> 2160 us, M = 1024 mixed
+// 2660 -> 1900 us, periodic M = 1024 FP64 3318 -> 1933 us.
+template <typename W>
+constexpr bool kResBuilt = M >= 64 && G<W>::SUM_GROUPS > 0 && RGeo<W, M, PAD>::OK;
 
 // The turn pass saves the reads of r and p and one launch per iteration.
-// Measured when it still had a second barrier, against the folded update alone (whole
-// mixed solves, alternating in one process): padded L = 2048 +4.2%, L = 256
-// +2.2%, L = 512 +0.5%, padded L = 512 FP64 +1.9%, periodic M = 256 / 512 /
-// 2048 +1.2 / +2.4 / +5.2%; but padded L = 1024 (M = 2048) -1.2% and
-// periodic M = 1024 -0.7%, so it is not offered on those two grids.
-constexpr bool kTurnPays = PAD ? M != 2048 : M != 1024;
-// Built where its grid can be resident at once: not in FP64 on rows of 16
-// pairs a thread and more (over 200 VGPRs, two workgroups per CU).
+// Measured when it still had a second barrier, against the folded update
+// alone (whole mixed solves, alternating in one process): padded L = 2048
+// +4.2%, periodic M = 2048 +5.2%; but padded L = 1024 (M = 2048) -1.2%, so it
+// is not offered there.
+constexpr bool kTurnPays = !(PAD && M == 2048);
+// Built above the resident kernel's grids, where its own grid can be resident
+// at once: not in FP64 on rows of 16 pairs a thread and more (over 200 VGPRs,
+// two workgroups per CU).
 template <typename W>
-constexpr bool kTurnBuilt = !(sizeof(W) == 8 && G<W>::ER >= 16);
+constexpr bool kTurnBuilt = !kResBuilt<W> && !(sizeof(W) == 8 && G<W>::ER >= 16);
 
 template <typename W>
 void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long token,
@@ -180,16 +175,15 @@ void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, 
 void iter_pass_fn(int prec, int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, int stride,
                   unsigned long long token, hipEvent_t e0, hipEvent_t e1, hipStream_t s) {
     if (prec == 0)
-        iter_pass_t<double>(pass, grid && G<double>::ROW_BLOCKS <= g4_blocks(), pt, slot, stride, token, e0, e1, s);
+        iter_pass_t<double>(pass, grid, pt, slot, stride, token, e0, e1, s);
     else
-        iter_pass_t<float>(pass, grid && G<float>::ROW_BLOCKS <= g4_blocks(), pt, slot, stride, token, e0, e1, s);
+        iter_pass_t<float>(pass, grid, pt, slot, stride, token, e0, e1, s);
 }
 
 // whether every workgroup of kernel `kern` (RB of RT threads) can be
 // resident at once on the current device
 template <int RT, int RB>
 bool whole_grid_resident(const void* kern) {
-    if (RB > g4_blocks()) return false;
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -255,6 +249,47 @@ void iter_grid_chunk_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int 
         iter_grid_chunk_t<double>(pt, slot, stride, token, K, turn, s);
     else
         iter_grid_chunk_t<float>(pt, slot, stride, token, K, turn, s);
+}
+
+template <typename W>
+void resident_t(const PlanTabs& pt, const SlotDesc& slot, unsigned long long* words, int xcd,
+                unsigned long long* token, int K, hipStream_t s) {
+    if constexpr (kResBuilt<W>) {
+        using R = RGeo<W, M, PAD>;
+        const unsigned long long t = *token + 1;
+        *token += 2ull * K;
+        hipLaunchKernelGGL((k_cg_resident<W, M, PAD, R::NT>), dim3(R::NB * (R::ONEX ? 8 : 1)), dim3(R::NT), 0, s,
+                           tab_of<W>(pt), slot, words, xcd, t, K);
+    }
+}
+
+void resident_fn(int prec, const PlanTabs& pt, const SlotDesc& slot, unsigned long long* words, int xcd,
+                 unsigned long long* token, int K, hipStream_t s) {
+    if (prec == 0)
+        resident_t<double>(pt, slot, words, xcd, token, K, s);
+    else
+        resident_t<float>(pt, slot, words, xcd, token, K, s);
+}
+
+template <typename W>
+bool resident_capable_t() {
+    if constexpr (!kResBuilt<W>)
+        return false;
+    else {
+        using R = RGeo<W, M, PAD>;
+        // on one XCD: an eighth of the CUs
+        return grid_capable_t<W>() &&
+               whole_grid_resident<R::NT, R::NB * (R::ONEX ? 8 : 1)>(
+                   reinterpret_cast<const void*>(k_cg_resident<W, M, PAD, R::NT>));
+    }
+}
+
+bool resident_capable_fn(int prec) {
+    return prec == 0 ? resident_capable_t<double>() : resident_capable_t<float>();
+}
+
+int resident_xcds_fn(int prec) {
+    return (prec == 0 ? RGeo<double, M, PAD>::ONEX : RGeo<float, M, PAD>::ONEX) ? 1 : 8;
 }
 
 void iter_fn(int prec, const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, hipStream_t s) {
@@ -402,11 +437,13 @@ const EngineOps kOps = {M,
                         &check_pcg_fn,
                         &check0_fn,
                         &check0_pcg_fn,
-                        &iter_grid_fn,
                         &iter_pass_fn,
                         &grid_capable_fn,
                         &iter_grid_chunk_fn,
-                        &turn_capable_fn};
+                        &turn_capable_fn,
+                        &resident_fn,
+                        &resident_xcds_fn,
+                        &resident_capable_fn};
 
 }  // namespace
 

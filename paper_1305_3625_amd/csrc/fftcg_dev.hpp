@@ -343,12 +343,40 @@ template <int R>
 __host__ __device__ constexpr int tw_nb() {
     return R > 8 ? 4 : (R > 4 ? 3 : (R > 2 ? 2 : 1));
 }
-template <typename T, int R>
-__device__ __forceinline__ void tw_load(cx<T>* pb, const cx<T>* __restrict__ tw, int m) {
-    pb[0] = gld(tw + m);
-    if constexpr (R > 2) pb[1] = gld(tw + 2 * m);
-    if constexpr (R > 4) pb[2] = gld(tw + 4 * m);
-    if constexpr (R > 8) pb[3] = gld(tw + 8 * m);
+template <typename T>
+__device__ __forceinline__ cx<T> twl(const cx<T>* tw, int m) {
+    return gld(tw + m);
+}
+// A twiddle table in constant memory: its loads are invariant, so a kernel
+// that loops over transforms keeps its twiddles in registers.
+template <typename T>
+struct ConstTw {
+    const cx<T>* p;
+};
+template <typename T>
+__device__ __forceinline__ cx<T> twl(ConstTw<T> tw, int m) {
+    typedef __attribute__((address_space(4))) const typename VecT<T, 2>::type V;
+    const auto v = ((V*)tw.p)[m];
+    return mkc(v.x, v.y);
+}
+template <typename T, int R, class TW>
+__device__ __forceinline__ void tw_load(cx<T>* pb, TW tw, int m) {
+    pb[0] = twl(tw, m);
+    if constexpr (R > 2) pb[1] = twl(tw, 2 * m);
+    if constexpr (R > 4) pb[2] = twl(tw, 4 * m);
+    if constexpr (R > 8) pb[3] = twl(tw, 8 * m);
+}
+// The barrier of an LDS exchange: of the workgroup, or (WV) among the lanes
+// of one wave, whose LDS accesses are performed in order, so that only the
+// compiler must not move them across.
+template <bool WV>
+__device__ __forceinline__ void xsync() {
+    if constexpr (WV) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
 }
 template <typename T, int R, int DIR>
 __device__ __forceinline__ void tw_apply(cx<T>* v, const cx<T>* pb) {
@@ -388,9 +416,9 @@ __device__ __forceinline__ void tw_apply(cx<T>* v, const cx<T>* pb) {
 // their reads compute while the others still read.  The last exchange's reads
 // are therefore not fenced: a caller that writes the buffer after the
 // transform places a barrier first.
-template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, int S, class Lay, bool LEAD>
-__device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, const cx<T>* __restrict__ tw,
-                                       const cx<T>* pre) {
+// WV: the transform's threads are lanes of one wave.
+template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, int S, class Lay, bool LEAD, bool WV, class TW>
+__device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, TW tw, const cx<T>* pre) {
     constexpr int E = fft_elems(N);
     constexpr int P = N / E;
     constexpr int R = fft_radix(N, REV, S);
@@ -412,40 +440,76 @@ __device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, const cx
             for (int u = 0; u < NB2; ++u)
                 tw_load<T, R2>(nxt + u * tw_nb<R2>(), tw, ((j + u * P) & (NS2 - 1)) * STEP2);
         }
-        if constexpr (S > 0 || LEAD) __syncthreads();
+        if constexpr (S > 0 || LEAD) xsync<WV>();
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
             const int b = j + u * P;
             const int base = (b / NS) * NS * R + (b & (NS - 1));
             lay.template st_run<R, NS>(base, v + u * R);
         }
-        __syncthreads();
+        xsync<WV>();
 #pragma unroll
         for (int u = 0; u < NB2; ++u) lay.template ld_run<R2, N / R2>(j + u * P, v + u * R2);
-        stages<T, N, MTAB, DIR, REV, HALF_IN, S + 1, Lay, LEAD>(v, lay, j, tw, nxt);
+        stages<T, N, MTAB, DIR, REV, HALF_IN, S + 1, Lay, LEAD, WV, TW>(v, lay, j, tw, nxt);
     }
 }
 
 // Full transform (all stages).  Length 1 is the identity.  LEAD: the caller
 // read the LDS buffer before (its reads are fenced before the first write).
 // Returns with the last exchange's reads unfenced (see stages).
-template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, class Lay, bool LEAD = false>
-__device__ __forceinline__ void fft_run(cx<T>* v, const Lay& lay, int j,
-                                        const cx<T>* __restrict__ tw) {
+template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, class Lay, bool LEAD = false, bool WV = false,
+          class TW = const cx<T>*>
+__device__ __forceinline__ void fft_run(cx<T>* v, const Lay& lay, int j, TW tw) {
     // stage 0 has no twiddles (NS = 1)
     if constexpr (fft_nstages(N) > 0)
-        stages<T, N, MTAB, DIR, REV, HALF_IN, 0, Lay, LEAD>(v, lay, j, tw, nullptr);
+        stages<T, N, MTAB, DIR, REV, HALF_IN, 0, Lay, LEAD, WV, TW>(v, lay, j, tw, nullptr);
 }
 
 // ---- reductions -----------------------------------------------------------
+// Lane exchanges of a wave reduction on the VALU (DPP rotations within rows
+// of 16 lanes, row and half swaps) instead of LDS permutes, whose latency
+// chain took 0.45 us for four doubles.  After the 32 and 16 steps all rows
+// hold the same values, and a rotation by 8, 4, 2, 1 then pairs the lanes as
+// an exchange with lane ^ 8, 4, 2, 1 does: the sums are those of a xor tree,
+// bitwise.
+template <int STEP>
+__device__ __forceinline__ void lane_pair(double v, double* a, double* b) {
+    const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)w, hi = (unsigned)(w >> 32);
+    auto join = [](unsigned l, unsigned h) {
+        return __builtin_bit_cast(double, (unsigned long long)l | ((unsigned long long)h << 32));
+    };
+    if constexpr (STEP == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        *a = join(l[0], h[0]);
+        *b = join(l[1], h[1]);
+    } else if constexpr (STEP == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        *a = join(l[0], h[0]);
+        *b = join(l[1], h[1]);
+    } else {
+        constexpr int ROR = 0x120 + STEP;  // row_ror:STEP
+        *a = v;
+        *b = join((unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, ROR, 0xf, 0xf, false),
+                  (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi, ROR, 0xf, 0xf, false));
+    }
+}
+template <int STEP = 32>
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    double a, b;
+    lane_pair<STEP>(v, &a, &b);
+    v = a + b;
+    if constexpr (STEP > 1) v = wave_sum<STEP / 2>(v);
     return v;
 }
+template <int STEP = 32>
 __device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+    double a, b;
+    lane_pair<STEP>(v, &a, &b);
+    v = fmin(a, b);
+    if constexpr (STEP > 1) v = wave_min<STEP / 2>(v);
     return v;
 }
 

@@ -103,7 +103,7 @@ static int check_device() {
 Workspace::~Workspace() { release(); }
 
 void Workspace::release() {
-    void* dev[] = {W, r, p, q, z, e, d32, part, st, slot, ls_pv, ls_pi, ls_out};
+    void* dev[] = {W, r, p, q, z, e, d32, part, st, slot, ls_pv, ls_pi, ls_out, meet};
     for (void* v : dev)
         if (v) (void)hipFree(v);
     if (h_slot) (void)hipHostFree(h_slot);
@@ -117,6 +117,7 @@ void Workspace::release() {
     W = r = p = q = z = nullptr;
     e = d32 = nullptr;
     part = nullptr;
+    meet = nullptr;
     st = nullptr;
     slot = nullptr;
     h_slot = nullptr;
@@ -266,6 +267,8 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
         p->grid_cap[1] = p->ops->grid_capable(FFTCG_MIXED);
         p->turn_cap[0] = p->grid_cap[0] && p->ops->turn_capable(FFTCG_FP64);
         p->turn_cap[1] = p->grid_cap[1] && p->ops->turn_capable(FFTCG_MIXED);
+        p->res_cap[0] = p->ops->resident_capable(FFTCG_FP64);
+        p->res_cap[1] = p->ops->resident_capable(FFTCG_MIXED);
     }
     // quarter spectrum (host copy, FP64) for the fused engine
     p->quarter.resize((size_t)(M / 2 + 1) * (M / 2 + 1));
@@ -377,6 +380,12 @@ extern "C" int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, dou
 // update's mode, and the turn pass's grid resident as a whole)
 static bool plan_turn(fftcg_plan_t plan, int precision) {
     return (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->turn_cap[precision == FFTCG_MIXED];
+}
+
+// whether solves in `precision` on this plan run the resident kernel (the
+// same modes)
+static bool plan_resident(fftcg_plan_t plan, int precision) {
+    return (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->res_cap[precision == FFTCG_MIXED];
 }
 
 extern "C" int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode) try {
@@ -726,6 +735,10 @@ static void fill_info(fftcg_info* info, const SolveState& st, float ms) {
 // L = 2048 / 512 +0.4 / +1.2%, the same iterations and checks.
 constexpr int kChunkSpan = 4;
 
+// Iterations of one launch of the resident kernel, which ends by itself when
+// a check falls due: a bound on the launch's length (a few milliseconds).
+constexpr int kResidentIters = 128;
+
 struct ChunkPlanner {
     int kmax;
     int known_iters = 0;  // iterations at the end of the last chunk the host has seen
@@ -757,6 +770,56 @@ struct ChunkPlanner {
         }
     }
 };
+
+// The XCDs that resident solves of this process hold, per device (a bit
+// each): two resident kernels never wait for each other's workgroups to make
+// room.  A solve that finds none free runs the iteration's passes instead,
+// with bitwise the same result.
+class XcdHold {
+    static constexpr int kDevices = 64;
+    static std::mutex mu_;
+    static unsigned used_[kDevices];
+    int dev_;
+    unsigned mask_ = 0;
+
+public:
+    XcdHold(int dev, int xcds) : dev_(dev) {
+        if (dev < 0 || dev >= kDevices) return;
+        if (xcds == 0) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        if (xcds == 8) {
+            if (used_[dev] == 0) mask_ = 0xff;
+        } else {
+            for (int i = 0; i < 8 && !mask_; ++i)
+                if (!(used_[dev] & (1u << i))) mask_ = 1u << i;
+        }
+        used_[dev] |= mask_;
+    }
+    ~XcdHold() {
+        if (!mask_) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        used_[dev_] &= ~mask_;
+    }
+    XcdHold(const XcdHold&) = delete;
+    XcdHold& operator=(const XcdHold&) = delete;
+    bool held() const { return mask_ != 0; }
+    int first() const { return mask_ ? __builtin_ctz(mask_) : 0; }
+};
+// The words through which the workspace's resident launches meet, zeroed once
+// (tokens start at 1 and only grow).
+static bool resident_words(Workspace* w, hipStream_t s) {
+    if (w->meet) return true;
+    void* p = nullptr;
+    if (hipMalloc(&p, kMeetWords * 8) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    w->meet = (unsigned long long*)p;
+    return hipMemsetAsync(p, 0, kMeetWords * 8, s) == hipSuccess;
+}
+
+std::mutex XcdHold::mu_;
+unsigned XcdHold::used_[XcdHold::kDevices] = {};
 
 static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, const double* d, const double* b,
                                 const double* x0, double tol, int maxit, double* x, fftcg_info* info,
@@ -842,11 +905,16 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
         const int pkey = 2 * precision + (pcg ? 1 : 0);
         const bool carry = precision == FFTCG_MIXED && w->check_period_prec == pkey;
         ChunkPlanner planner(kmax, carry ? w->check_period : 0);
+        bool resident = grid && plan_resident(plan, precision);
+        XcdHold hold(plan->device, resident ? ops->resident_xcds(precision) : 0);
+        resident = resident && hold.held() && resident_words(w, s);
         long c = 0;
         bool finished = false;
         while (!finished) {
-            const int K = planner.next();
-            if (grid)
+            const int K = resident ? kResidentIters : planner.next();
+            if (resident)
+                ops->resident(precision, plan->tabs, *w->h_slot, w->meet, hold.first(), &w->grid_token, K, s);
+            else if (grid)
                 ops->iter_grid_chunk(precision, plan->tabs, w->slot, plan->stride, &w->grid_token, K,
                                      plan_turn(plan, precision), s);
             else

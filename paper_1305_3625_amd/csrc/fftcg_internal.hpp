@@ -56,6 +56,7 @@ struct Workspace {
     // launches of the grid-synchronised update on this workspace's partial
     // sums (each launch's barrier token is the next value)
     unsigned long long grid_token = 0;
+    unsigned long long* meet = nullptr;  // kMeetWords words of the resident kernel (made by its first solve)
     int init(int L, int M, int stride);
     void release();
     ~Workspace();
@@ -111,6 +112,7 @@ struct fftcg_plan_s {
     int grid_mode = 1;
     bool grid_cap[2] = {false, false};
     bool turn_cap[2] = {false, false};  // the turn pass (k_row_turn) resident as a whole, per precision
+    bool res_cap[2] = {false, false};   // resident CG (k_cg_resident), likewise
     std::atomic<int> grid_broken{0};
     std::mutex mu;
     std::vector<fftcg::Workspace*> free_ws;

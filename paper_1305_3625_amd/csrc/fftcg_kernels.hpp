@@ -62,6 +62,10 @@ struct Geo {
     static constexpr int RPW = RPW_fit(RPW0);
     static constexpr int ROW_THREADS = RPW * PR;
     static constexpr int ROW_BLOCKS = L / RPW;
+    // Sums over the row blocks (grid_sums) in the resident kernel's order,
+    // where the grid has one: by groups of its workgroups per XCD (one group
+    // up to 64 workgroups, eight above).  0: no such order.
+    static constexpr int SUM_GROUPS = (M > 1024 || ROW_BLOCKS > 512) ? 0 : (ROW_BLOCKS <= 64 ? 1 : 8);
     // column pass
     static constexpr int EC = fft_elems(M);
     static constexpr int PC = M / EC;
@@ -792,7 +796,13 @@ __device__ __forceinline__ bool next_rr(const double* t, double a, double* rr) {
 // (a grid that is not resident as a whole cannot complete the barrier).
 // Called by every thread of the workgroup; returns the same value in all.
 // sh must hold N * (NT + 63) / 64 doubles.
-template <int NT, int N>
+// NG: groups of the summation order (Geo::SUM_GROUPS).  0: thread t takes t,
+// t + NT, ..., then the block sum.  Else block b is member b / NG of group
+// b % NG; a group is a wave sum, and the groups are added as a tree.
+__device__ __forceinline__ double group_tree(double v) {  // over lane & 7, in rows of 16 lanes holding them twice
+    return wave_sum<4>(v);
+}
+template <int NT, int N, int NG>
 __device__ inline bool grid_sums(const double* acc, double* part, int stride, unsigned long long token,
                                  long long limit, double* sh, double* tot) {
     constexpr int sets[4] = {PS_PQ, PS_RR, PS_RQ, PS_QQ};
@@ -836,13 +846,30 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
             __builtin_amdgcn_s_sleep(1);
         }
         if (ok) {
-            double s[N];
+            if constexpr (NG > 0 && NT % 64 == 0) {
+                if (tid < 64) {
+                    const unsigned int lane = tid;
 #pragma unroll
-            for (int a = 0; a < N; ++a) s[a] = 0.0;
-            for (unsigned int i = tid; i < nb; i += NT)
+                    for (int a = 0; a < N; ++a) {
+                        double mine = 0.0;  // lane's group (lane & 7)
+                        for (unsigned int g = 0; g < NG; ++g) {
+                            const unsigned int i = g + NG * lane;
+                            const double t = wave_sum(i < nb ? get(setp(a) + i) : 0.0);
+                            if (NG == 1 || (lane & 7) == g) mine = t;
+                        }
+                        if (NG > 1) mine = group_tree(mine);
+                        if (lane == 0) s_tot[a] = mine;
+                    }
+                }
+            } else {
+                double s[N];
 #pragma unroll
-                for (int a = 0; a < N; ++a) s[a] += get(setp(a) + i);
-            block_sums<NT, N>(s, sh, s_tot);
+                for (int a = 0; a < N; ++a) s[a] = 0.0;
+                for (unsigned int i = tid; i < nb; i += NT)
+#pragma unroll
+                    for (int a = 0; a < N; ++a) s[a] += get(setp(a) + i);
+                block_sums<NT, N>(s, sh, s_tot);
+            }
             __syncthreads();
             for (int a = tid; a < N; a += NT) put(rel + 1 + a, s_tot[a]);
             __builtin_amdgcn_s_waitcnt(0);
@@ -1367,7 +1394,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             }
         };
         double tot[4];  // p.q, r.r, r.q, q.q
-        if (!grid_sums<NT, 4>(acc, sd.part, stride, token, st->bar_limit, red, tot)) {
+        if (!grid_sums<NT, 4, G::SUM_GROUPS>(acc, sd.part, stride, token, st->bar_limit, red, tot)) {
             give_up();
             return;
         }
@@ -1402,7 +1429,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
 #pragma unroll
             for (int i = 0; i < NO; ++i) rr[0] += (double)rk[i].x * rk[i].x + (double)rk[i].y * rk[i].y;
             // set 0 of the partials again (its first use ended with the barrier)
-            if (!grid_sums<NT, 1>(rr, sd.part, stride, token + 1, st->bar_limit, red, &rrn)) {
+            if (!grid_sums<NT, 1, G::SUM_GROUPS>(rr, sd.part, stride, token + 1, st->bar_limit, red, &rrn)) {
                 give_up();
                 return;
             }

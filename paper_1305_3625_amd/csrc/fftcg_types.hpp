@@ -100,4 +100,8 @@ enum PartSet {
     NPART_SETS = 15
 };
 
+// 64-bit words of a workspace through which the resident kernel's workgroups
+// meet.
+constexpr int kMeetWords = 8192;
+
 }  // namespace fftcg

@@ -1,0 +1,113 @@
+"""The resident kernel (whole CG iterations of a single solve in one launch,
+Sec. 3, Listing 2) against the passes whose arithmetic it repeats.
+
+* every grid and precision it is built for, and the grids at its edges: the
+  iterates and counts are bitwise those of the folded passes (mode 3);
+* an iteration that reduces r.r so far that the difference of the sums
+  cancels (a right-hand side close to an eigenvector): r.r is summed anew;
+* the masked operator (fracture driver), and the fallback when a meeting
+  gives up.
+
+The results are compared for equality, so there is no tolerance to choose,
+except against the dense solution: the solves' certified 1e-10.
+"""
+
+import numpy as np
+import pytest
+
+from paper_1305_3625_amd import binding
+from workloads import spectrum, padded_instance, periodic_instance, fracture_instance
+from oracle import kernel_table, solve_dense
+from gpu_util import dev, host, relerr, banner
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(plan, inst, mode, precision, tol=1e-10, maxit=10000, x0=None):
+    import torch
+    plan.set_grid_sync(mode)
+    x = torch.zeros((inst["L"], inst["L"]), dtype=torch.float64, device="cuda")
+    info = plan.solve(dev(inst["d"]), dev(inst["b"]), x, x0=x0, tol=tol, maxit=maxit, precision=precision,
+                      raise_on_error=False)
+    return host(x), info
+
+
+@pytest.mark.parametrize("precision", [binding.FP64, binding.MIXED])
+@pytest.mark.parametrize("L,padded", [(16, 1), (32, 1), (64, 1), (128, 1), (256, 1), (512, 1), (1024, 1),
+                                      (32, 0), (64, 0), (128, 0), (256, 0), (512, 0), (1024, 0)])
+def test_resident_bitwise_as_passes(L, padded, precision):
+    inst = (padded_instance if padded else periodic_instance)(L, [7, L, padded], eps=1e-3)
+    plan = binding.Plan(L, padded, inst["ghat"])
+    plan.set_engine(binding.ENGINE_MULTIPASS)
+    banner("resident", L, padded, precision)
+    w = dev(np.random.default_rng([7, 1, L]).standard_normal((L, L)))
+    for kw in (dict(), dict(maxit=3), dict(x0=w)):
+        out = {m: _run(plan, inst, m, precision, **kw) for m in (3, 1)}
+        print(kw.keys(), [o[1]["iterations"] for o in out.values()], out[1][1]["error_bound"])
+        assert out[1][1]["status"] == out[3][1]["status"]
+        assert out[1][1]["iterations"] == out[3][1]["iterations"]
+        assert out[1][1]["error_bound"] == out[3][1]["error_bound"]
+        assert np.array_equal(out[1][0], out[3][0])
+    assert plan.grid_sync(precision) != binding.GRID_FELL_BACK
+    plan.close()
+
+
+@pytest.mark.parametrize("precision", [binding.FP64, binding.MIXED])
+def test_resident_residual_falls_at_once(precision):
+    """Uniform d and b = 1 plus a thousandth of noise on a periodic grid: the
+    first iteration removes the constant, and r.r with it to 1e-6."""
+    L = 16
+    rng = np.random.default_rng([7, 2])
+    g = spectrum(64, 1e-2)
+    b = 1.0 + 1e-3 * rng.standard_normal((64, 64))
+    inst = dict(L=64, d=np.ones((64, 64)), b=b)
+    plan = binding.Plan(64, 0, g)
+    plan.set_engine(binding.ENGINE_MULTIPASS)
+    banner("resident-fall", 64, precision)
+    x, info = _run(plan, inst, 1, precision)
+    y, info3 = _run(plan, inst, 3, precision)
+    assert info["status"] == binding.OK and info["iterations"] == info3["iterations"]
+    assert np.array_equal(x, y)
+    # diagonal in Fourier space
+    ref = np.real(np.fft.ifft2(np.fft.fft2(b) / (1.0 + g)))
+    assert relerr(x, ref) <= 1e-10
+    plan.close()
+    inst = dict(periodic_instance(L, [7, 3]), padded=0)
+    ref = solve_dense(kernel_table(inst["ghat"]), inst["d"], inst["b"], 0)
+    plan = binding.Plan(L, 0, inst["ghat"])
+    x, info = _run(plan, inst, 1, precision)
+    assert relerr(x, ref) <= 1e-10
+    plan.close()
+
+
+def test_resident_masked():
+    import torch
+    L, steps = 128, 4
+    inst = fracture_instance(1, L=L)
+    plan = binding.Plan(L, 1, spectrum(2 * L, 1e-3))
+    banner("resident-masked", L)
+    out = {}
+    for mode in (3, 1):
+        plan.set_grid_sync(mode)
+        f = torch.zeros((L, L), dtype=torch.float64, device="cuda")
+        st, broken, dbreak, iters = plan.fracture(inst["k"], dev(inst["t"]), f, steps, tol=1e-9)
+        assert st == binding.OK
+        out[mode] = (host(f), broken, dbreak, iters)
+    assert all(np.array_equal(a, b) for a, b in zip(out[1], out[3]))
+    plan.close()
+
+
+@pytest.mark.parametrize("L,padded", [(64, 0), (512, 1)])
+def test_resident_gives_up(L, padded):
+    """A wait limit of zero: the meetings give up and the solve is repeated
+    with the separate update kernel, bitwise that kernel's result."""
+    inst = (padded_instance if padded else periodic_instance)(L, [7, 5, L], eps=1e-3)
+    plan = binding.Plan(L, padded, inst["ghat"])
+    plan.set_engine(binding.ENGINE_MULTIPASS)
+    banner("resident-gives-up", L)
+    x0, info0 = _run(plan, inst, 0, binding.FP64)
+    x2, info2 = _run(plan, inst, 2, binding.FP64)
+    assert info2["status"] == binding.OK
+    assert plan.grid_sync(binding.FP64) == binding.GRID_FELL_BACK
+    assert np.array_equal(x0, x2) and info0["iterations"] == info2["iterations"]
+    plan.close()
