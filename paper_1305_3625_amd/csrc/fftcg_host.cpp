@@ -161,7 +161,11 @@ int Workspace::init(int L_, int M_, int stride_) {
     HIPCHK(hipHostMalloc((void**)&h_status, 16, hipHostMallocMapped | hipHostMallocCoherent));
     HIPCHK(hipHostGetDevicePointer((void**)&d_status, h_status, 0));
     HIPCHK(hipHostMalloc((void**)&h_ls, 16, hipHostMallocDefault));
+    // the clearing runs on the null stream, which does not order itself with
+    // the (non-blocking) stream of the first solve: wait for it here, or it
+    // can wipe partial sums and barrier words of a solve that has begun
     HIPCHK(hipMemset(part, 0, (size_t)NPART_SETS * stride * 8));
+    HIPCHK(hipStreamSynchronize(nullptr));
     for (int i = 0; i < 2; ++i) HIPCHK(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
     HIPCHK(hipEventCreate(&ev0));
     HIPCHK(hipEventCreate(&ev1));

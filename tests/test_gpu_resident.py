@@ -5,12 +5,14 @@ Sec. 3, Listing 2) against the passes whose arithmetic it repeats.
   iterates and counts are bitwise those of the folded passes (mode 3);
 * an iteration that reduces r.r so far that the difference of the sums
   cancels (a right-hand side close to an eigenvector): r.r is summed anew;
-* the masked operator (fracture driver), and the fallback when a meeting
-  gives up.
+* the masked operator (fracture driver), more solves at once than XCDs, and
+  the fallback when a meeting gives up.
 
 The results are compared for equality, so there is no tolerance to choose,
 except against the dense solution: the solves' certified 1e-10.
 """
+
+import threading
 
 import numpy as np
 import pytest
@@ -94,6 +96,48 @@ def test_resident_masked():
         assert st == binding.OK
         out[mode] = (host(f), broken, dbreak, iters)
     assert all(np.array_equal(a, b) for a, b in zip(out[1], out[3]))
+    plan.close()
+
+
+@pytest.mark.parametrize("L,count", [(128, 10), (512, 3)])
+def test_resident_solves_at_once(L, count):
+    """More solves at once than XCDs (or than one, where a solve takes the
+    device): those without room run the passes; every result is the same as
+    alone.  A fresh plan each time: its workspaces are made while other
+    solves run, and nothing of that may reach into a solve (the clearing of
+    the partial sums once did)."""
+    import torch
+    insts = [padded_instance(L, [7, 4, k], eps=1e-3) for k in range(count)]
+    plan = binding.Plan(L, 1, insts[0]["ghat"])
+    banner("resident-at-once", L, count)
+    ref = [_run(plan, i, 3, binding.MIXED)[0] for i in insts]
+    D, B = [dev(i["d"]) for i in insts], [dev(i["b"]) for i in insts]
+    for _ in range(6):
+        plan.close()
+        plan = binding.Plan(L, 1, insts[0]["ghat"])
+        X = [torch.zeros((L, L), dtype=torch.float64, device="cuda") for _ in insts]
+        streams = [torch.cuda.Stream() for _ in insts]
+        infos = [None] * count
+        torch.cuda.synchronize()
+
+        def work(k):
+            infos[k] = plan.solve(D[k], B[k], X[k], tol=1e-10, precision=binding.MIXED, stream=streams[k],
+                                  raise_on_error=False)
+
+        th = [threading.Thread(target=work, args=(k,)) for k in range(count)]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        torch.cuda.synchronize()
+        fell = plan.grid_sync(binding.MIXED) == binding.GRID_FELL_BACK
+        print("fell back:", fell)
+        for k in range(count):
+            assert infos[k]["status"] == binding.OK
+            if fell:
+                assert relerr(host(X[k]), ref[k]) <= 2e-10
+            else:
+                assert np.array_equal(host(X[k]), ref[k])
     plan.close()
 
 
