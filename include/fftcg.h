@@ -64,8 +64,10 @@ extern "C" {
 #define FFTCG_MIXED 1
 
 /* ---- engines (fftcg_plan_set_engine) -----------------------------------
- * AUTO     : the fused engine for M <= 64 in single solves and for
- *            M <= 128 in server classes, the multi-pass engine above.
+ * AUTO     : the fused engine for M <= 64 in products and in single solves
+ *            (there only where the multi-pass engine's resident kernel,
+ *            fftcg_plan_set_grid_sync, does not apply) and for M <= 128 in
+ *            server classes, the multi-pass engine above.
  * MULTIPASS: three HBM passes per product (row R2C, column FFT*ghat*IFFT,
  *            row C2R + epilogue); every grid.
  * FUSED    : one workgroup per solve, whole CG loop in one kernel, the
@@ -175,13 +177,13 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          rows (p <- r + beta p, the pending x update, the row transform),
  *          so that r and p are not read back from memory.  beta's r.r comes
  *          from the sums that the one barrier returns (r.r, r.q, q.q).
- *          On grids with 64 <= M <= 1024 a solve runs whole iterations in
- *          one resident kernel instead, with bitwise the result of mode 3:
- *          r, p, x and d stay in registers between checks, and the
- *          workgroups of one XCD (M <= 256 and the smaller row counts) or of
- *          the whole device meet three times per iteration.  At most one
- *          such kernel per XCD, or one on the whole device, runs at a time
- *          in a process; a solve that finds no room runs the passes.
+ *          On grids with 32 <= M <= 1024 a solve, preconditioned or not, runs
+ *          in one resident kernel instead, checks included, with bitwise the
+ *          result of mode 3: r, p, x and d stay in registers, and the
+ *          workgroups of one XCD (M <= 256) or of the whole device meet three
+ *          times per product.  At most one such kernel per XCD, or one on the
+ *          whole device, runs at a time in a process; a solve that finds no
+ *          room runs the passes.
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.

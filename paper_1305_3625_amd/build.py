@@ -60,7 +60,7 @@ def engine_radix(m: int) -> int:
 def engine_row_threads(m: int, pad: int) -> int:
     """Threads of a row-pass workgroup (and with them the rows and the number
     of workgroups of the resident kernel)."""
-    return {(64, 0): 64, (64, 1): 64, (128, 0): 64, (128, 1): 64, (256, 1): 128, (512, 1): 64, (512, 0): 128,
+    return {(32, 1): 64, (64, 0): 64, (64, 1): 64, (128, 0): 64, (128, 1): 64, (256, 1): 128, (512, 1): 64, (512, 0): 128,
             (1024, 1): 128}.get((m, pad), 256)
 
 

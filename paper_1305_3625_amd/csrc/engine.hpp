@@ -16,6 +16,22 @@ struct PlanTabs {
     const void* ghN64;  // double[M/2 + 1]
 };
 
+// One launch of the resident kernel.
+struct ResidentRun {
+    SlotDesc slot;              // the descriptor itself
+    unsigned long long* words;  // kMeetWords 64-bit words the workgroups meet through
+    unsigned long long token;   // first of kResidentTokens tokens that no launch on the words has used (they grow)
+    int xcd;                    // the XCD to run on, where resident_xcds is 1
+    int K;                      // iterations at most, <= kResidentIters
+    int first;                  // 1: the solve begins; 0: it goes on
+    int zero;                   // with first: from x = 0 (slot.x is not read)
+};
+// Iterations of one launch: a bound on its length (some milliseconds); most
+// solves end within one.  Every iteration meets at most four times, and at
+// most one check (four meetings) precedes it.
+constexpr int kResidentIters = 256;
+constexpr unsigned long long kResidentTokens = 8ull * (kResidentIters + 2);
+
 struct EngineOps {
     int M, pad, L;
     int tt32, tt64;          // columns per tile of the column pass
@@ -64,18 +80,16 @@ struct EngineOps {
     // whether the turn pass is resident as a whole as well (implies
     // grid_capable)
     bool (*turn_capable)(int prec);
-    // up to K iterations of a single slot in one launch (k_cg_resident; slot:
-    // the descriptor itself; words: kMeetWords 64-bit words), ending early
-    // when an FP64 check is due.  xcd: the XCD it runs on, where
-    // resident_xcds is 1.  *token is advanced past every token the launch can
-    // use (they grow with every launch on the same words).
-    void (*resident)(int prec, const PlanTabs& t, const SlotDesc& slot, unsigned long long* words, int xcd,
-                     unsigned long long* token, int K, hipStream_t s);
+    // a single solve, or K of its iterations, in one launch
+    // (k_solve_resident); pcg: with the circulant preconditioner.  st: the
+    // state it begins with (run.first), else taken from the slot's.
+    void (*resident)(int prec, bool pcg, const PlanTabs& t, const ResidentRun& run, const SolveState& st,
+                     hipStream_t s);
     // the XCDs it occupies: 1 or 8
     int (*resident_xcds)(int prec);
-    // whether resident applies on the current device (built for this grid and
-    // resident as a whole; implies grid_capable)
-    bool (*resident_capable)(int prec);
+    // whether it applies on the current device (built for this grid and
+    // resident as a whole)
+    bool (*resident_capable)(int prec, bool pcg);
 };
 
 const EngineOps* find_engine(int M, int pad);

@@ -117,13 +117,13 @@ void iter_grid_t(const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned 
     hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride, token);
 }
 
-// Resident CG is built where the iteration is latency-bound and its vectors
-// fit the registers.  Whole solves to 1e-10, folded passes (mode 3) -> resident:
-// periodic M = 64 FP64 759 -> 302 us, padded M = 256 mixed 1465 -> 711 us,
-// M = 512 mixed 1953 -> 1405 us, M = 1024 FP64 3250 -> 2160 us, M = 1024 mixed
-// 2660 -> 1900 us, periodic M = 1024 FP64 3318 -> 1933 us.
+// The resident kernel is built where the iteration is latency-bound and its
+// vectors fit the registers.  Whole solves to 1e-10, folded passes (mode 3) ->
+// resident: periodic M = 64 FP64 759 -> 241 us, padded M = 256 mixed 1465 ->
+// 596 us, M = 1024 FP64 3250 -> 1968 us, M = 1024 mixed 2660 -> 1680 us;
+// preconditioned padded M = 1024 FP64 1697 -> 1047 us.
 template <typename W>
-constexpr bool kResBuilt = M >= 64 && G<W>::SUM_GROUPS > 0 && RGeo<W, M, PAD>::OK;
+constexpr bool kResBuilt = M >= 32 && G<W>::SUM_GROUPS > 0 && RGeo<W, M, PAD>::OK;
 
 // The turn pass saves the reads of r and p and one launch per iteration.
 // Measured when it still had a second barrier, against the folded update
@@ -252,40 +252,42 @@ void iter_grid_chunk_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int 
 }
 
 template <typename W>
-void resident_t(const PlanTabs& pt, const SlotDesc& slot, unsigned long long* words, int xcd,
-                unsigned long long* token, int K, hipStream_t s) {
+void resident_t(bool pcg, const PlanTabs& pt, const ResidentRun& rr, const SolveState& st, hipStream_t s) {
     if constexpr (kResBuilt<W>) {
         using R = RGeo<W, M, PAD>;
-        const unsigned long long t = *token + 1;
-        *token += 2ull * K;
-        hipLaunchKernelGGL((k_cg_resident<W, M, PAD, R::NT>), dim3(R::NB * (R::ONEX ? 8 : 1)), dim3(R::NT), 0, s,
-                           tab_of<W>(pt), slot, words, xcd, t, K);
+        const ResArgs a{rr.slot, rr.words, rr.token, rr.xcd, rr.K, rr.first, rr.zero};
+        const dim3 grid(R::NB * (R::ONEX ? 8 : 1)), block(R::NT);
+        if (pcg)
+            hipLaunchKernelGGL((k_solve_resident<W, M, PAD, R::NT, true>), grid, block, 0, s, tab_of<W>(pt),
+                               tab_of<double>(pt), a, st);
+        else
+            hipLaunchKernelGGL((k_solve_resident<W, M, PAD, R::NT, false>), grid, block, 0, s, tab_of<W>(pt),
+                               tab_of<double>(pt), a, st);
     }
 }
 
-void resident_fn(int prec, const PlanTabs& pt, const SlotDesc& slot, unsigned long long* words, int xcd,
-                 unsigned long long* token, int K, hipStream_t s) {
+void resident_fn(int prec, bool pcg, const PlanTabs& pt, const ResidentRun& rr, const SolveState& st, hipStream_t s) {
     if (prec == 0)
-        resident_t<double>(pt, slot, words, xcd, token, K, s);
+        resident_t<double>(pcg, pt, rr, st, s);
     else
-        resident_t<float>(pt, slot, words, xcd, token, K, s);
+        resident_t<float>(pcg, pt, rr, st, s);
 }
 
 template <typename W>
-bool resident_capable_t() {
+bool resident_capable_t(bool pcg) {
     if constexpr (!kResBuilt<W>)
         return false;
     else {
         using R = RGeo<W, M, PAD>;
+        const void* k = pcg ? reinterpret_cast<const void*>(k_solve_resident<W, M, PAD, R::NT, true>)
+                            : reinterpret_cast<const void*>(k_solve_resident<W, M, PAD, R::NT, false>);
         // on one XCD: an eighth of the CUs
-        return grid_capable_t<W>() &&
-               whole_grid_resident<R::NT, R::NB * (R::ONEX ? 8 : 1)>(
-                   reinterpret_cast<const void*>(k_cg_resident<W, M, PAD, R::NT>));
+        return whole_grid_resident<R::NT, R::NB * (R::ONEX ? 8 : 1)>(k);
     }
 }
 
-bool resident_capable_fn(int prec) {
-    return prec == 0 ? resident_capable_t<double>() : resident_capable_t<float>();
+bool resident_capable_fn(int prec, bool pcg) {
+    return prec == 0 ? resident_capable_t<double>(pcg) : resident_capable_t<float>(pcg);
 }
 
 int resident_xcds_fn(int prec) {
@@ -310,7 +312,7 @@ void check_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, 
                        s, tab, sp);
     hipLaunchKernelGGL((k_row_inv<double, M, PAD, EpiCheck<W>, ByPtr, RT>), dim3(G<double>::ROW_BLOCKS, nslots),
                        dim3(RT), 0, s, tab, sp, stride);
-    hipLaunchKernelGGL((k_check_final<256>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS,
+    hipLaunchKernelGGL((k_check_final<256, G<double>::SUM_GROUPS>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS,
                        g4_blocks(), stride, LL * LL);
 }
 
@@ -331,13 +333,13 @@ void iter_pcg_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int strid
     constexpr int RT = G<W>::ROW_THREADS, CT = G<W>::COL_THREADS, RB = G<W>::ROW_BLOCKS;
     const ByPtr sp{slots};
     const Tab<W> tab = tab_of<W>(pt);
-    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPCG<W, XA, RT, RB>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
+    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPCG<W, XA, RT, RB, G<W>::SUM_GROUPS>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
                        tab, sp, RB, stride);
     hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE, nslots), dim3(CT), 0, s, tab,
                        sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiCG<W>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s, tab, sp,
                        stride);
-    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProUpdPre<W, RT, RB>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
+    hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProUpdPre<W, RT, RB, G<W>::SUM_GROUPS>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
                        tab, sp, 0, stride);
     hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT, true>), dim3(G<W>::NTILE, nslots), dim3(CT), 0, s,
                        tab, sp);
@@ -368,7 +370,7 @@ void check_pcg_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stri
                        s, tab, sp);
     hipLaunchKernelGGL((k_row_inv<double, M, PAD, EpiCheck<W>, ByPtr, RT>), dim3(G<double>::ROW_BLOCKS, nslots),
                        dim3(RT), 0, s, tab, sp, stride);
-    hipLaunchKernelGGL((k_check_final<256>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS, RBW,
+    hipLaunchKernelGGL((k_check_final<256, G<double>::SUM_GROUPS>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS, RBW,
                        stride, LL * LL);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPre<W>, ByPtr, RTW>), dim3(RBW, nslots), dim3(RTW), 0, s, tabw, sp,
                        0, stride);
@@ -392,9 +394,10 @@ template <typename W>
 void check0_t(bool pcg, const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, hipStream_t s) {
     constexpr int RTW = G<W>::ROW_THREADS, CTW = G<W>::COL_THREADS, RBW = G<W>::ROW_BLOCKS;
     const ByPtr sp{slots};
-    hipLaunchKernelGGL((k_check_zero<W, 256>), dim3(G<double>::ROW_BLOCKS, nslots), dim3(256), 0, s, sp, LL * LL,
+    constexpr int RT = G<double>::ROW_THREADS;
+    hipLaunchKernelGGL((k_check_zero<W, M, PAD, RT>), dim3(G<double>::ROW_BLOCKS, nslots), dim3(RT), 0, s, sp,
                        stride);
-    hipLaunchKernelGGL((k_check_final<256>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS,
+    hipLaunchKernelGGL((k_check_final<256, G<double>::SUM_GROUPS>), dim3(1, nslots), dim3(256), 0, s, sp, G<double>::ROW_BLOCKS,
                        pcg ? RBW : g4_blocks(), stride, LL * LL);
     if (pcg) {
         const Tab<W> tabw = tab_of<W>(pt);

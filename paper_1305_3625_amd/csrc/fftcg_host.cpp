@@ -271,8 +271,6 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
         p->grid_cap[1] = p->ops->grid_capable(FFTCG_MIXED);
         p->turn_cap[0] = p->grid_cap[0] && p->ops->turn_capable(FFTCG_FP64);
         p->turn_cap[1] = p->grid_cap[1] && p->ops->turn_capable(FFTCG_MIXED);
-        p->res_cap[0] = p->ops->resident_capable(FFTCG_FP64);
-        p->res_cap[1] = p->ops->resident_capable(FFTCG_MIXED);
     }
     // quarter spectrum (host copy, FP64) for the fused engine
     p->quarter.resize((size_t)(M / 2 + 1) * (M / 2 + 1));
@@ -322,8 +320,9 @@ extern "C" int fftcg_plan_destroy(fftcg_plan_t plan) try {
 } FFTCG_ABI_CATCH
 
 // AUTO: one workgroup per solve beats four kernel launches per iteration on
-// the smallest grids.  A single solve takes the fused engine up to M = 64; a
-// server class, whose slots share each launch of the multi-pass engine, up
+// the smallest grids.  A product, and a single solve that the resident kernel
+// does not take (fftcg_solve), uses the fused engine up to M = 64; a server
+// class, whose slots share each launch of the multi-pass engine, up
 // to M = 128 (measured crossovers: at M = 128 one fused solve is 15-25%
 // slower than a multi-pass one, while 64 batched solves run as fast or
 // faster fused; from M = 256 on the fused engine's serial rounds cost more).
@@ -389,7 +388,15 @@ static bool plan_turn(fftcg_plan_t plan, int precision) {
 // whether solves in `precision` on this plan run the resident kernel (the
 // same modes)
 static bool plan_resident(fftcg_plan_t plan, int precision) {
-    return (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->res_cap[precision == FFTCG_MIXED];
+    if (!plan->ops || (plan->grid_mode != 1 && plan->grid_mode != 2) || plan->grid_broken.load()) return false;
+    const bool pcg = plan->precond != FFTCG_PRECOND_NONE;
+    std::atomic<int>& cap = plan->res_cap[precision == FFTCG_MIXED][pcg];
+    int c = cap.load();
+    if (c < 0) {
+        c = plan->ops->resident_capable(precision, pcg) ? 1 : 0;
+        cap.store(c);
+    }
+    return c != 0;
 }
 
 extern "C" int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode) try {
@@ -739,10 +746,6 @@ static void fill_info(fftcg_info* info, const SolveState& st, float ms) {
 // L = 2048 / 512 +0.4 / +1.2%, the same iterations and checks.
 constexpr int kChunkSpan = 4;
 
-// Iterations of one launch of the resident kernel, which ends by itself when
-// a check falls due: a bound on the launch's length (a few milliseconds).
-constexpr int kResidentIters = 128;
-
 struct ChunkPlanner {
     int kmax;
     int known_iters = 0;  // iterations at the end of the last chunk the host has seen
@@ -789,7 +792,6 @@ class XcdHold {
 public:
     XcdHold(int dev, int xcds) : dev_(dev) {
         if (dev < 0 || dev >= kDevices) return;
-        if (xcds == 0) return;
         std::lock_guard<std::mutex> lk(mu_);
         if (xcds == 8) {
             if (used_[dev] == 0) mask_ = 0xff;
@@ -825,6 +827,46 @@ static bool resident_words(Workspace* w, hipStream_t s) {
 std::mutex XcdHold::mu_;
 unsigned XcdHold::used_[XcdHold::kDevices] = {};
 
+// A solve by the resident kernel: one launch, or one per kResidentIters
+// iterations.  The state travels as a kernel argument and comes back at the
+// end.  ST_EGRID: a meeting gave up; a warm start given in place is then in
+// w->q.
+static int solve_resident(fftcg_plan_t plan, Workspace* w, int precision, const double* d, const double* b,
+                          const double* x0, double tol, int maxit, double* x, fftcg_info* info, hipStream_t s,
+                          const uint8_t* mask, int xcd) {
+    const size_t n = (size_t)plan->L * plan->L;
+    fill_slot(w->h_slot, w, x, b, d);
+    w->h_slot->mask = mask;
+    w->h_slot->host_status = nullptr;
+    init_state(w->h_state, plan, precision, tol, maxit, 50);
+    w->h_state->bar_limit = plan->grid_mode == 2 ? 0 : kGridWaitTicks;
+    const SolveState init = *w->h_state;
+    if (hipEventRecord(w->ev0, s) != hipSuccess) return FFTCG_EDEVICE;
+    if (x0 && x0 != x && hipMemcpyAsync(x, x0, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess) return FFTCG_EDEVICE;
+    if (x0 && x0 == x && hipMemcpyAsync(w->q, x, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
+        return FFTCG_EDEVICE;
+    ResidentRun run{*w->h_slot, w->meet, 0, xcd, kResidentIters, 1, x0 ? 0 : 1};
+    SolveState st;
+    do {
+        run.token = w->grid_token + 1;
+        w->grid_token += kResidentTokens;
+        plan->ops->resident(precision, plan->precond != FFTCG_PRECOND_NONE, plan->tabs, run, init, s);
+        if (hipGetLastError() != hipSuccess || hipEventRecord(w->ev1, s) != hipSuccess ||
+            hipMemcpyAsync(w->h_state, w->st, sizeof(SolveState), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess)
+            return FFTCG_EDEVICE;
+        st = *w->h_state;
+        run.first = run.zero = 0;
+    } while (!st.done);
+    if (st.bzero && (hipMemsetAsync(x, 0, n * 8, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess))
+        return FFTCG_EDEVICE;
+    if (st.status == ST_EGRID) return ST_EGRID;
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, w->ev0, w->ev1);
+    fill_info(info, st, ms);
+    return st.status;
+}
+
 static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, const double* d, const double* b,
                                 const double* x0, double tol, int maxit, double* x, fftcg_info* info,
                                 hipStream_t s, const uint8_t* mask, bool grid);
@@ -835,6 +877,23 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
     Workspace* w = plan_acquire(plan);
     if (!w) return FFTCG_ENOMEM;
     const size_t n = (size_t)plan->L * plan->L;
+    if (plan_resident(plan, precision)) {
+        XcdHold hold(plan->device, plan->ops->resident_xcds(precision));
+        if (hold.held() && resident_words(w, s)) {
+            const int rc = solve_resident(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, hold.first());
+            if (rc != ST_EGRID) {
+                plan_release(plan, w);
+                return rc;
+            }
+            // a meeting gave up (other work on the device): the passes from
+            // here on; x may hold the caller's start vector
+            plan->grid_broken.store(1);
+            if (x0 && x0 == x && hipMemcpyAsync(x, w->q, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess) {
+                plan_release(plan, w);
+                return FFTCG_EDEVICE;
+            }
+        }
+    }
     bool grid = plan->grid_mode != 0 && !plan->grid_broken.load() && plan->grid_cap[precision == FFTCG_MIXED] &&
                 plan->precond == FFTCG_PRECOND_NONE;
     int rc = FFTCG_OK;
@@ -909,16 +968,11 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
         const int pkey = 2 * precision + (pcg ? 1 : 0);
         const bool carry = precision == FFTCG_MIXED && w->check_period_prec == pkey;
         ChunkPlanner planner(kmax, carry ? w->check_period : 0);
-        bool resident = grid && plan_resident(plan, precision);
-        XcdHold hold(plan->device, resident ? ops->resident_xcds(precision) : 0);
-        resident = resident && hold.held() && resident_words(w, s);
         long c = 0;
         bool finished = false;
         while (!finished) {
-            const int K = resident ? kResidentIters : planner.next();
-            if (resident)
-                ops->resident(precision, plan->tabs, *w->h_slot, w->meet, hold.first(), &w->grid_token, K, s);
-            else if (grid)
+            const int K = planner.next();
+            if (grid)
                 ops->iter_grid_chunk(precision, plan->tabs, w->slot, plan->stride, &w->grid_token, K,
                                      plan_turn(plan, precision), s);
             else
@@ -972,7 +1026,13 @@ extern "C" int fftcg_solve(fftcg_plan_t plan, int precision, const double* d, co
     int rc = solve_validate(plan, precision, d, b, tol, maxit, x);
     if (rc != FFTCG_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if (plan_engine(plan) == FFTCG_ENGINE_FUSED) return fused_solve(plan, precision, d, b, x0, tol, maxit, x, info, s);
+    // AUTO on small grids: the resident kernel where it applies (solves to
+    // 1e-10, fused -> resident: periodic M = 64 FP64 476 -> 241 us, padded
+    // M = 64 467 -> 298 us, periodic M = 32 241 -> 204 us), else the fused
+    // engine
+    if (plan_engine(plan) == FFTCG_ENGINE_FUSED &&
+        !(plan->engine == FFTCG_ENGINE_AUTO && plan_resident(plan, precision)))
+        return fused_solve(plan, precision, d, b, x0, tol, maxit, x, info, s);
     if (!plan->ops) return FFTCG_EINVAL;
     return solve_multipass(plan, precision, d, b, x0, tol, maxit, x, info, s);
 } FFTCG_ABI_CATCH

@@ -112,7 +112,9 @@ struct fftcg_plan_s {
     int grid_mode = 1;
     bool grid_cap[2] = {false, false};
     bool turn_cap[2] = {false, false};  // the turn pass (k_row_turn) resident as a whole, per precision
-    bool res_cap[2] = {false, false};   // resident CG (k_cg_resident), likewise
+    // the resident kernel, per precision, plain and preconditioned: -1 not
+    // asked yet (the first solve does), 0 no, 1 yes
+    std::atomic<int> res_cap[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};
     std::atomic<int> grid_broken{0};
     std::mutex mu;
     std::vector<fftcg::Workspace*> free_ws;

@@ -292,6 +292,37 @@ __device__ __forceinline__ Mask2 mask2(const SlotDesc& sd, size_t idx) {
     return Mask2{(double)m[0], (double)m[1]};
 }
 
+// The resident kernel's order of a sum over row blocks (Geo::SUM_GROUPS, NG
+// here): block b is member b / NG of group b % NG, a group is a wave sum and
+// the groups are added as a tree.  By one wave; the result in every lane.
+__device__ __forceinline__ double group_tree(double v) {  // over lane & 7, in rows of 16 lanes holding them twice
+    return wave_sum<4>(v);
+}
+template <int NG, bool MIN = false, class GET>
+__device__ __forceinline__ double group_sum(unsigned int n, double none, GET get) {
+    const unsigned int lane = threadIdx.x & 63;
+    double mine = none;  // the lane's group (lane & 7)
+    for (unsigned int g = 0; g < NG; ++g) {
+        const unsigned int i = g + NG * lane;
+        const double v = i < n ? get(i) : none;
+        const double t = MIN ? wave_min(v) : wave_sum(v);
+        if (NG == 1 || (lane & 7) == g) mine = t;
+    }
+    if (NG == 1) return mine;
+    return MIN ? wave_min<4>(mine) : group_tree(mine);
+}
+// Sum of n partials, in that order or (NG = 0, or a block without whole
+// waves) in sum_partials'; result in every thread.  sh: NT / 64 doubles.
+template <int NT, int NG>
+__device__ __forceinline__ double sum_blocks(const double* p, int n, double* sh) {
+    if constexpr (NG > 0 && NT % 64 == 0) {
+        // every wave adds them up by itself
+        return group_sum<NG>(n, 0.0, [&](unsigned int i) { return gbl(p)[i]; });
+    } else {
+        return sum_partials<NT>(p, n, sh);
+    }
+}
+
 // ==== prologues of the row-forward pass ====================================
 
 // fftcg_apply: transform x (FP64 in memory), rounded to T.
@@ -470,7 +501,7 @@ struct ProCheck {
 // preconditioner pass, p = z + beta p (p = z on restart), pending x update,
 // then transform p.  The stop triggers still use r.r.  NPZ: partial count of
 // the r.z sums.
-template <typename W, typename XA, int NT, int NPZ>
+template <typename W, typename XA, int NT, int NPZ, int NG>
 struct ProPCG {
     static constexpr int NACC = 0;
     // FP32: z, p and the x correction are requested before the reductions
@@ -486,7 +517,10 @@ struct ProPCG {
         if (!GateIter::ok(sd)) return false;
         SolveState* st = sd.st;
         double rr, rz;
-        if constexpr (NT % 64 == 0) {
+        if constexpr (NG > 0) {
+            rr = sum_blocks<NT, NG>(sd.part + PS_RR * stride, npart_rr, sh.red);
+            rz = sum_blocks<NT, NG>(sd.part + PS_RZ * stride, NPZ, sh.red);
+        } else if constexpr (NT % 64 == 0) {
             // r.r and r.z reduced together (each in sum_partials' order)
             double a2[2] = {0.0, 0.0};
             const auto* prr = gbl(sd.part + PS_RR * stride);
@@ -582,7 +616,7 @@ struct ProPCG {
 // the operator's row-inverse pass (breakdown if p.q <= 0), r <- r - alpha q
 // with partial r.r, then transform r for z = P^{-1} r.  NPQ: partial count of
 // the p.q sums.
-template <typename W, int NT, int NPQ>
+template <typename W, int NT, int NPQ, int NG>
 struct ProUpdPre {
     static constexpr int NACC = 1;
     static constexpr bool PREF = sizeof(W) == 4;  // r and q requested before the p.q reduction
@@ -595,7 +629,7 @@ struct ProUpdPre {
     static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int, int stride) {
         if (!GateIter::ok(sd)) return false;
         SolveState* st = sd.st;
-        const double pq = sum_partials<NT>(sd.part + PS_PQ * stride, NPQ, sh.red);
+        const double pq = sum_blocks<NT, NG>(sd.part + PS_PQ * stride, NPQ, sh.red);
         const double rho = st->rho_cur;
         if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
             if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -796,12 +830,8 @@ __device__ __forceinline__ bool next_rr(const double* t, double a, double* rr) {
 // (a grid that is not resident as a whole cannot complete the barrier).
 // Called by every thread of the workgroup; returns the same value in all.
 // sh must hold N * (NT + 63) / 64 doubles.
-// NG: groups of the summation order (Geo::SUM_GROUPS).  0: thread t takes t,
-// t + NT, ..., then the block sum.  Else block b is member b / NG of group
-// b % NG; a group is a wave sum, and the groups are added as a tree.
-__device__ __forceinline__ double group_tree(double v) {  // over lane & 7, in rows of 16 lanes holding them twice
-    return wave_sum<4>(v);
-}
+// NG: the summation order (group_sum), 0: thread t takes t, t + NT, ..., then
+// the block sum.
 template <int NT, int N, int NG>
 __device__ inline bool grid_sums(const double* acc, double* part, int stride, unsigned long long token,
                                  long long limit, double* sh, double* tot) {
@@ -848,17 +878,10 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
         if (ok) {
             if constexpr (NG > 0 && NT % 64 == 0) {
                 if (tid < 64) {
-                    const unsigned int lane = tid;
 #pragma unroll
                     for (int a = 0; a < N; ++a) {
-                        double mine = 0.0;  // lane's group (lane & 7)
-                        for (unsigned int g = 0; g < NG; ++g) {
-                            const unsigned int i = g + NG * lane;
-                            const double t = wave_sum(i < nb ? get(setp(a) + i) : 0.0);
-                            if (NG == 1 || (lane & 7) == g) mine = t;
-                        }
-                        if (NG > 1) mine = group_tree(mine);
-                        if (lane == 0) s_tot[a] = mine;
+                        const double t = group_sum<NG>(nb, 0.0, [&](unsigned int i) { return get(setp(a) + i); });
+                        if (tid == 0) s_tot[a] = t;
                     }
                 }
             } else {
@@ -906,24 +929,14 @@ struct EpiCheck {
     static constexpr bool PREF = false;
     using Gate = GateCheck;
     static __device__ __forceinline__ bool begin(const SlotDesc& sd) { return GateCheck::ok(sd); }
-    template <int L>
-    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, double c0, double c1,
-                                                double* acc) {
-        const size_t idx = (size_t)row * L + col;
-        cx<double> xv = ld2<double>(sd.x + idx);
-        cx<double> bv = ld2<double>(sd.b + idx);
-        cx<double> dv = ld2<double>(sd.d + idx);
-        const Mask2 mk = mask2(sd, idx);
+    // one pair: returns its new r (checked: a recursive residual ro exists)
+    static __device__ __forceinline__ cx<W> pair(cx<double> xv, cx<double> bv, cx<double> dv, Mask2 mk, double c0,
+                                                 double c1, bool checked, cx<W> ro, double* acc) {
         const double r0 = mk.m0 * (bv.x - (dv.x * xv.x + c0));
         const double r1 = mk.m1 * (bv.y - (dv.y * xv.y + c1));
         bv = mkc(mk.m0 * bv.x, mk.m1 * bv.y);
         const W w0 = (W)r0, w1 = (W)r1;
-        W* rp = reinterpret_cast<W*>(sd.r) + idx;
-        if (sd.st->checks > 0) {  // the first check has no recursive residual yet
-            const cx<W> ro = ld2<W>(rp);
-            acc[6] += (r0 - (double)ro.x) * (r0 - (double)ro.x) + (r1 - (double)ro.y) * (r1 - (double)ro.y);
-        }
-        st2<W>(rp, mkc(w0, w1));
+        if (checked) acc[6] += (r0 - (double)ro.x) * (r0 - (double)ro.x) + (r1 - (double)ro.y) * (r1 - (double)ro.y);
         acc[0] += r0 * r0 + r1 * r1;
         acc[1] += xv.x * xv.x + xv.y * xv.y;
         acc[2] += bv.x * bv.x + bv.y * bv.y;
@@ -933,6 +946,17 @@ struct EpiCheck {
                         dv.x >= 0.0 && dv.y >= 0.0;
         acc[5] += ok ? 0.0 : 1.0;
         acc[7] += dv.x + dv.y;
+        return mkc(w0, w1);
+    }
+    template <int L>
+    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, double c0, double c1,
+                                                double* acc) {
+        const size_t idx = (size_t)row * L + col;
+        const cx<double> xv = ld2<double>(sd.x + idx), bv = ld2<double>(sd.b + idx), dv = ld2<double>(sd.d + idx);
+        W* rp = reinterpret_cast<W*>(sd.r) + idx;
+        const bool checked = sd.st->checks > 0;  // the first check has no recursive residual yet
+        const cx<W> ro = checked ? ld2<W>(rp) : mkc(W(0), W(0));
+        st2<W>(rp, pair(xv, bv, dv, mask2(sd, idx), c0, c1, checked, ro, acc));
     }
 };
 
@@ -1588,41 +1612,48 @@ __global__ void __launch_bounds__(NT) k_update(ByPtr slot, int n, int npart_pq, 
 // The first FP64 check of a solve started from x = 0: r = b - A 0 = b, so
 // no product is needed.  One pass over b and d writes r and the check's
 // partials (the same values the full check would produce, bitwise: C 0 and
-// d 0 are exactly zero); the finaliser then decides as usual.  npart blocks.
-template <typename W, int NT>
-__global__ void __launch_bounds__(NT) k_check_zero(ByPtr slot, int n, int stride) {
+// d 0 are exactly zero, and blocks and threads take the FP64 row-inverse
+// pass's pairs in its order); the finaliser then decides as usual.
+template <typename W, int M, int PAD, int NT>
+__global__ void __launch_bounds__(NT) k_check_zero(ByPtr slot, int stride) {
+    using G = Geo<double, M, PAD>;
+    constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L;
+    constexpr int NSTG = fft_nstages(N);
+    constexpr int RL = NSTG > 0 ? fft_radix(N, true, NSTG - 1) : 1;
+    constexpr int RK = (PAD && RL > 1) ? RL / 2 : RL;
+    static_assert(NT == G::ROW_THREADS, "row block size");
     __shared__ double red[8 * ((NT + 63) / 64)];
     const SlotDesc& sd = slot.get();
     if (!GateCheck::ok(sd)) return;
-    const int npairs = n / 2;
-    const int per = (npairs + gridDim.x - 1) / gridDim.x;
-    const int lo = blockIdx.x * per;
-    const int hi = lo + per < npairs ? lo + per : npairs;
+    const int tid = threadIdx.x, rl = tid / P, j = tid % P;
+    const int row = xcd_remap(blockIdx.x, gridDim.x) * RPW + rl;
     double acc[8] = {0, 0, 0, 0, 1.0e300, 0, 0, 0};
-    for (int q = lo + threadIdx.x; q < hi; q += NT) {
-        const size_t idx = 2 * (size_t)q;
-        const cx<double> b2 = ld2<double>(sd.b + idx), d2 = ld2<double>(sd.d + idx);
-        const Mask2 mk = mask2(sd, idx);
-        const double r0 = mk.m0 * b2.x, r1 = mk.m1 * b2.y;
-        const W w0 = (W)r0, w1 = (W)r1;
-        st2<W>(reinterpret_cast<W*>(sd.r) + idx, mkc(w0, w1));
-        acc[0] += r0 * r0 + r1 * r1;
-        acc[2] += r0 * r0 + r1 * r1;
-        acc[3] += (double)w0 * (double)w0 + (double)w1 * (double)w1;
-        acc[4] = fmin(acc[4], fmin(mk.m0 > 0.0 ? d2.x : 1.0e300, mk.m1 > 0.0 ? d2.y : 1.0e300));
-        const bool ok = isfinite(r0) && isfinite(r1) && isfinite(d2.x) && isfinite(d2.y) && d2.x >= 0.0 &&
-                        d2.y >= 0.0;
-        acc[5] += ok ? 0.0 : 1.0;
-        acc[7] += d2.x + d2.y;
-    }
+#pragma unroll
+    for (int u = 0; u < E / RL; ++u)
+#pragma unroll
+        for (int r = 0; r < RK; ++r) {
+            const size_t idx = (size_t)row * L + 2 * ((j + u * P) + r * (N / RL));
+            const cx<double> b2 = ld2<double>(sd.b + idx), d2 = ld2<double>(sd.d + idx);
+            st2<W>(reinterpret_cast<W*>(sd.r) + idx,
+                   EpiCheck<W>::pair(mkc(0.0, 0.0), b2, d2, mask2(sd, idx), 0.0, 0.0, false, mkc(W(0), W(0)), acc));
+        }
     const int sets[8] = {PS_CHK_R, PS_CHK_X, PS_CHK_B, PS_CHK_RW, PS_CHK_DMIN, PS_CHK_BAD, PS_CHK_DIFF, PS_CHK_DSUM};
-    const double v = block_reduce_n<NT, 8, 1u << 4>(acc, red);  // set 4 (min d) a minimum
-    if (threadIdx.x < 8) sd.part[sets[threadIdx.x] * stride + blockIdx.x] = v;
+    if constexpr (NT % 64 == 0) {
+        const double v = block_reduce_n<NT, 8, 1u << 4>(acc, red);  // set 4 (min d) a minimum
+        if (tid < 8) sd.part[sets[tid] * stride + blockIdx.x] = v;
+    } else {
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const double v = (a == 4) ? block_min<NT>(acc[a], red) : block_sum<NT>(acc[a], red);
+            if (tid == 0) sd.part[sets[a] * stride + blockIdx.x] = v;
+        }
+    }
 }
 
 // Single-block finaliser of an FP64 check: stop decision, residual
 // replacement, restart guard, and status for the host.
-template <int NT>
+// NG: the order of its sums (group_sum; 0: sum_partials').
+template <int NT, int NG>
 __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, int npart_rr, int stride, int n) {
     __shared__ double red[8 * ((NT + 63) / 64)];
     __shared__ double s_tot[8];
@@ -1640,15 +1671,27 @@ __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, i
     const int sets[8] = {PS_CHK_R, PS_CHK_X, PS_CHK_B, PS_CHK_RW, PS_CHK_DMIN, PS_CHK_BAD, PS_CHK_DIFF, PS_CHK_DSUM};
     double acc[8] = {0.0, 0.0, 0.0, 0.0, 1.0e300, 0.0, 0.0, 0.0};
     const auto* part = gbl(sd.part);
-    for (int i = threadIdx.x; i < npart_chk; i += NT) {
+    if constexpr (NG > 0) {
+        if (threadIdx.x < 64) {
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const double v = part[sets[a] * stride + i];
-            acc[a] = (a == 4) ? fmin(acc[a], v) : acc[a] + v;
+            for (int a = 0; a < 8; ++a) {
+                const auto* pa = part + sets[a] * stride;
+                const auto get = [&](unsigned int i) { return pa[i]; };
+                const double t = a == 4 ? group_sum<NG, true>(npart_chk, 1.0e300, get) : group_sum<NG>(npart_chk, 0.0, get);
+                if (threadIdx.x == 0) s_tot[a] = t;
+            }
         }
+    } else {
+        for (int i = threadIdx.x; i < npart_chk; i += NT) {
+#pragma unroll
+            for (int a = 0; a < 8; ++a) {
+                const double v = part[sets[a] * stride + i];
+                acc[a] = (a == 4) ? fmin(acc[a], v) : acc[a] + v;
+            }
+        }
+        const double tot = block_reduce_n<NT, 8, 1u << 4>(acc, red);
+        if (threadIdx.x < 8) s_tot[threadIdx.x] = tot;
     }
-    const double tot = block_reduce_n<NT, 8, 1u << 4>(acc, red);
-    if (threadIdx.x < 8) s_tot[threadIdx.x] = tot;
     __syncthreads();
     const double R = s_tot[0], X = s_tot[1], B = s_tot[2], RW = s_tot[3];
     const double dmin = s_tot[4], BAD = s_tot[5], DIFF = s_tot[6], DSUM = s_tot[7];

@@ -1,24 +1,27 @@
-// Resident CG: the iterations of a single solve in one kernel.
+// The resident kernel: a single solve, checks and all, in one launch.
 //
 // On mid-sized grids an iteration's passes take a few microseconds each, most
 // of it latency: the launch, the chain of loads (slot descriptor, state, then
 // data), reading the vectors that the previous pass has just written.  Here
-// one launch runs until a check falls due.  Every workgroup owns RPW rows and
-// CW columns for the whole launch and keeps its parts of r, p, the x
-// accumulator and d, its columns' spectrum and (where they fit) all twiddles
-// in registers; only the half spectrum W crosses workgroups, and workgroups
-// meet three times per iteration:
+// every workgroup owns RPW rows and CW columns for the whole launch and keeps
+// its parts of r, p, z, the x accumulator and d and its columns' spectrum (on
+// the smaller grids all twiddles too) in registers; only the half spectrum W
+// crosses workgroups, and workgroups meet three times per iteration:
 //   rows forward -> W | columns of W in place | rows inverse of W, the sums
 //   p.q, r.r, r.q and q.q over the grid -> alpha, r, beta, p.
-// A row or column of up to 64 threads is transformed inside one wave, without
-// barriers.  The arithmetic and its order are those of the folded update's
-// passes (EpiCGU, ProCG), so the iterates are bitwise the same.
+// With the preconditioner, z = P^-1 r is three more such phases; an FP64 check
+// is the same phases in FP64.  A row or column of up to 64 threads is
+// transformed inside one wave, without barriers.  The arithmetic and its
+// order are those of the passes (EpiCGU, ProCG; iter_pcg; the check), so the
+// iterates are bitwise the same; every workgroup takes the decisions of
+// check_decide and check_due by itself from the same sums, on its own copy of
+// the state.
 //
-// What bounds it: the meetings.  On one XCD a meeting takes 0.6 us and the
-// sums 1.2 us; an iteration takes 5.8 us at padded M = 256 in FP32 (16 us as
-// passes) and 5.2 us at periodic M = 64 in FP64.  Over all XCDs, at padded
-// M = 1024, a meeting takes 2.3 to 3.5 us and the sums 3.5 us of 15 us (FP32)
-// or 19.5 us (FP64; 27 us as passes).
+// What bounds it: the meetings.  On one XCD a meeting takes 0.7 us and the
+// sums 1.4 us; an iteration takes 6.6 us at padded M = 256 in FP32 (16 us as
+// passes) and 5.9 us at periodic M = 64 in FP64.  Over all XCDs, at padded
+// M = 1024, a meeting takes 2.1 to 3 us and the sums 2.8 us of 14.4 us (FP32)
+// or 18.7 us (FP64; 27 us as passes).
 //
 // W moves between workgroups inside the launch.  Its accesses go past the
 // CUs' L1 caches, and past the L2 caches where they must reach other XCDs
@@ -55,7 +58,7 @@ struct RGeo {
     static constexpr int NG = cmax(1, G::SUM_GROUPS), GM = NB / NG;  // groups, members of a group
     static constexpr bool ONEX = NG == 1;
     // twiddles in registers for the whole launch, where they fit beside the rest
-    static constexpr bool HOIST = (int)sizeof(T) * M <= 4096;
+    static constexpr bool HOIST = (int)sizeof(T) * M <= 2048;
     static constexpr bool OK = G::SUM_GROUPS > 0 && NB % NG == 0 && GM <= 64 && RT % 64 == 0 && N % NB == 0 && CW * G::PC == U * NT && CU * U == CW && RPW >= 2 &&
                                (size_t)LDS_WORDS * sizeof(cx<T>) <= 140 * 1024;
 };
@@ -105,9 +108,10 @@ __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: 
 // ---- meetings of all workgroups -------------------------------------------------
 // The workgroups of one XCD form a group (workgroups go to the XCDs round
 // robin; hello() checks it).  Members tell their group's leader through the
-// XCD's L2; with more than one group the leaders tell everybody through words
-// that every XCD sees, eight in one line.  Polling by every workgroup of
-// every other's word instead took 4 us per meeting with 256 workgroups.
+// XCD's L2; with more than one group the eight leaders tell each other through
+// words that every XCD sees, and then their members.  With 256 workgroups,
+// polling by every workgroup of every other's word took 4 us per meeting, and
+// polling of the leaders' line by everybody 2.1 us.
 // One wave per workgroup polls.  Waits are bounded (`limit` ticks of the
 // 100 MHz clock, a thousand times an ordinary wait): a grid that is not
 // resident as a whole cannot meet, and the launch then ends.
@@ -124,15 +128,21 @@ struct Meet {
     long long limit;
     int g, i;  // this workgroup: group, member (0 leads)
 
-    // layout in words
+    // layout in words; sets 0-4 of partial sums belong to the iterations,
+    // 5-12 (and 3 with the preconditioner) to the checks
+    static constexpr int SETS = 13;
     static constexpr int FLAG = 0, REL = FLAG + NG * GS, HELLO = REL + 16, HREL = HELLO + NG * GS, PART = HREL + 16;
-    static constexpr int PART_SET = NG * GS, OUT = PART + 2 * 5 * PART_SET, OUT_RING = 5 * 16, WORDS = OUT + 2 * OUT_RING;
+    static constexpr int PART_SET = NG * GS, OUT = PART + 2 * SETS * PART_SET, GO = OUT + 2 * SETS * 16;
+    static constexpr int FIN = GO + NG * 16, WORDS = FIN + NG * 32;
     static_assert(WORDS <= kMeetWords, "the words fit");
     __device__ __forceinline__ unsigned long long* part(int ring, int set) const {
-        return base + PART + (ring * 5 + set) * PART_SET + g * GS;
+        return base + PART + (ring * SETS + set) * PART_SET + g * GS;
     }
     __device__ __forceinline__ unsigned long long* out(int ring, int set) const {
-        return base + OUT + ring * OUT_RING + set * 16;
+        return base + OUT + (ring * SETS + set) * 16;
+    }
+    __device__ __forceinline__ unsigned long long* fin(int ring, int set) const {
+        return base + FIN + g * 32 + ring * 16 + set;
     }
     template <class F>
     __device__ __forceinline__ bool wave_wait(F done) const {
@@ -151,13 +161,14 @@ struct Meet {
         auto members = [&] { return lane >= GM || word_get(base + FLAG + g * GS + lane) >= token; };
         if constexpr (NG == 1) {
             return wave_wait(members);
+        } else if (i == 0) {
+            if (!wave_wait(members)) return false;
+            if (lane == 0) word_put<true>(base + REL + g, token);
+            if (!wave_wait([&] { return lane >= NG || word_get(base + REL + lane) >= token; })) return false;
+            if (lane == 0) word_put<false>(base + GO + g * 16, token);
+            return true;
         } else {
-            bool ok = true;
-            if (i == 0) {
-                ok = wave_wait(members);
-                if (ok && lane == 0) word_put<true>(base + REL + g, token);
-            }
-            return ok && wave_wait([&] { return lane >= NG || word_get(base + REL + lane) >= token; });
+            return wave_wait([&] { return word_get(base + GO + g * 16) >= token; });
         }
     }
     // All workgroups' stores to W are complete and seen by gld_all after.
@@ -199,14 +210,14 @@ struct Meet {
         __syncthreads();
         return *s_ok != 0;
     }
-    // Empties this workgroup's words of a ring half.
-    __device__ __forceinline__ void empty(int ring) const {
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int a = 0; a < 5; ++a) word_put<false>(part(ring, a) + i, kEmpty);
+    // Empties this workgroup's words of the sets in `mask`, in a ring half.
+    __device__ __forceinline__ void empty(int ring, unsigned mask) const {
+        const int set = threadIdx.x;
+        if (set < SETS && ((mask >> set) & 1u)) {
+            word_put<false>(part(ring, set) + i, kEmpty);
             if (ALL && i == 0) {
-#pragma unroll
-                for (int a = 0; a < 5; ++a) word_put<true>(out(ring, a) + g, kEmpty);
+                word_put<true>(out(ring, set) + g, kEmpty);
+                word_put<false>(fin(ring, set), kEmpty);
             }
         }
     }
@@ -214,40 +225,38 @@ struct Meet {
         const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
         return w == kEmpty ? w ^ 1 : w;
     }
-    // The sums of N per-thread values (of the RT row threads) over the grid,
-    // in every thread.  The words hold the values themselves, kEmpty until
-    // they arrive, so no separate arrival is needed; halves of the ring are
-    // used in turn and emptied between two meetings that every reader of
-    // their last use has passed.  Order (group_total): the workgroup's
-    // partial, the members of a group as a wave sum, the groups as a tree.
-    template <int RT, int N>
+    // The sums (minimum where bit a of MINMASK is set) of N per-thread values
+    // (of the RT row threads) over the grid, in every thread.  The words hold
+    // the values themselves, kEmpty until they arrive, so no separate arrival
+    // is needed; halves of the ring are used in turn and emptied between two
+    // meetings that every reader of their last use has passed.  Order (as
+    // grid_sums): the workgroup's partial, the members of a group as a wave
+    // sum, the groups as a tree.  sh: N * RT / 64 doubles, s_tot: N.
+    template <int RT, int N, unsigned MINMASK = 0u>
     __device__ __forceinline__ bool sums(const double* acc, int set0, int ring, double* sh, double* s_tot, int* s_ok,
                                          double* tot) const {
         constexpr int NW = RT / 64;
         const int tid = threadIdx.x, lane = tid & 63;
+        auto is_min = [](int a) { return ((MINMASK >> a) & 1u) != 0; };
         if (tid < RT) {
             double w[N];
 #pragma unroll
-            for (int a = 0; a < N; ++a) w[a] = wave_sum(acc[a]);
+            for (int a = 0; a < N; ++a) w[a] = is_min(a) ? wave_min(acc[a]) : wave_sum(acc[a]);
             if (lane == 0) {
 #pragma unroll
-                for (int a = 0; a < N; ++a) {
-                    if constexpr (NW == 1)
-                        word_put<false>(part(ring, set0 + a) + i, bits(0.0 + w[a]));
-                    else
-                        sh[a * NW + (tid >> 6)] = w[a];
-                }
+                for (int a = 0; a < N; ++a) sh[a * NW + (tid >> 6)] = w[a];
             }
         }
-        if constexpr (NW > 1) __syncthreads();
+        if constexpr (NW > 1)
+            __syncthreads();
+        else
+            xsync<true>();
         if (tid < 64) {
-            if constexpr (NW > 1) {
-                if (lane < N) {
-                    double r = 0.0;
+            if (lane < N) {
+                double r = is_min(lane) ? sh[lane * NW] : 0.0;
 #pragma unroll
-                    for (int w = 0; w < NW; ++w) r += sh[lane * NW + w];
-                    word_put<false>(part(ring, set0 + lane) + i, bits(r));
-                }
+                for (int w = 0; w < NW; ++w) r = is_min(lane) ? fmin(r, sh[lane * NW + w]) : r + sh[lane * NW + w];
+                word_put<false>(part(ring, set0 + lane) + i, bits(r));
             }
             bool ok = true;
             double t[N];
@@ -257,28 +266,48 @@ struct Meet {
                     bool all = true;
 #pragma unroll
                     for (int a = 0; a < N; ++a) {
-                        w[a] = lane < GM ? word_get(part(ring, set0 + a) + lane) : 0ull;
+                        w[a] = lane < GM ? word_get(part(ring, set0 + a) + lane) : bits(is_min(a) ? 1.0e300 : 0.0);
                         all &= w[a] != kEmpty;
                     }
                     return all;
                 });
 #pragma unroll
-                for (int a = 0; a < N; ++a) t[a] = wave_sum(__builtin_bit_cast(double, w[a]));
+                for (int a = 0; a < N; ++a) {
+                    const double v = __builtin_bit_cast(double, w[a]);
+                    t[a] = is_min(a) ? wave_min(v) : wave_sum(v);
+                }
                 if (ALL && ok && lane == 0) {
 #pragma unroll
                     for (int a = 0; a < N; ++a) word_put<true>(out(ring, set0 + a) + g, bits(t[a]));
                 }
             }
             if constexpr (NG > 1) {
-                // row a of the wave takes set a: its eight groups twice
-                const int a = (lane >> 4) < N ? lane >> 4 : 0;
-                unsigned long long w = 0;
-                ok = ok && wave_wait([&] {
-                         w = word_get(out(ring, set0 + a) + (lane & 7));
-                         return w != kEmpty;
-                     });
-                const double v = group_tree(__builtin_bit_cast(double, w));
-                if ((lane & 15) == 0 && (lane >> 4) < N) s_tot[lane >> 4] = v;
+                if (i == 0) {
+                    // the leaders exchange their groups' sums: row q of the
+                    // wave takes set a0 + q, its eight groups twice
+#pragma unroll
+                    for (int a0 = 0; a0 < N; a0 += 4) {
+                        const int a = a0 + (lane >> 4) < N ? a0 + (lane >> 4) : a0;
+                        unsigned long long w = 0;
+                        ok = ok && wave_wait([&] {
+                                 w = word_get(out(ring, set0 + a) + (lane & 7));
+                                 return w != kEmpty;
+                             });
+                        const double u = __builtin_bit_cast(double, w);
+                        const double v = is_min(a) ? wave_min<4>(u) : group_tree(u);
+                        if ((lane & 15) == 0 && a0 + (lane >> 4) < N) {
+                            if (ok) word_put<false>(fin(ring, set0 + a), bits(v));
+                            s_tot[a] = v;
+                        }
+                    }
+                } else {
+                    unsigned long long w = 0;
+                    ok = wave_wait([&] {
+                        w = lane < N ? word_get(fin(ring, set0 + lane)) : 0ull;
+                        return w != kEmpty;
+                    });
+                    if (lane < N) s_tot[lane] = __builtin_bit_cast(double, w);
+                }
             } else if (lane == 0) {
 #pragma unroll
                 for (int a = 0; a < N; ++a) s_tot[a] = t[a];
@@ -288,9 +317,8 @@ struct Meet {
         __syncthreads();
 #pragma unroll
         for (int a = 0; a < N; ++a) tot[a] = s_tot[a];
-        const bool ok = *s_ok != 0;
         // (s_tot, s_ok and sh are written again only behind a later barrier)
-        return ok;
+        return *s_ok != 0;
     }
 };
 
@@ -392,14 +420,22 @@ struct ResSpec {
 // The workgroup's columns of W in place (k_col's arithmetic): forward
 // transform, times ghat / M^2, inverse transform.  All values are requested
 // before the first transform.
-template <typename T, int M, int PAD, class TW>
-__device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, PAD>& sp, cx<T>* Wb, int blk) {
+// PRE: times the preconditioner's multiplier (c2, c4: pre_mul's) instead.
+template <typename T, int M, int PAD, bool PRE, class TW>
+__device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, PAD>& sp, T c2, T c4, cx<T>* Wb,
+                                         int blk) {
     using R = RGeo<T, M, PAD>;
     using G = Geo<T, M, PAD>;
     using Lay = typename R::ColLay;
     constexpr int E = G::EC, P = G::PC;
     constexpr int NSTG = fft_nstages(M);
     constexpr int R1 = fft_radix(M, false, 0), RL = fft_radix(M, false, NSTG - 1), RZ = fft_radix(M, true, NSTG - 1);
+    auto mul = [&](T g) {
+        if constexpr (PRE)
+            return pre_mul(g, c2, c4);
+        else
+            return g;
+    };
     cx<T> v[R::U][E];
 #pragma unroll
     for (int u = 0; u < R::U; ++u) {
@@ -428,12 +464,13 @@ __device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, 
                 const int m = (c.j + (i / RL) * P) + (i % RL) * (M / RL);
                 const cx<T> a = v[u][i];
                 const cx<T> bm = conjc(lay.ld((M - m) & (M - 1)));
-                const T s = T(0.5) * (sp.g[u][i] + sp.gN[i]), t = T(0.5) * (sp.g[u][i] - sp.gN[i]);
-                v[u][i] = c.kk == 0 ? mkc(s * a.x + t * bm.x, s * a.y + t * bm.y) : scalec(a, sp.g[u][i]);
+                const T g0 = mul(sp.g[u][i]), gN = mul(sp.gN[i]);
+                const T s = T(0.5) * (g0 + gN), t = T(0.5) * (g0 - gN);
+                v[u][i] = c.kk == 0 ? mkc(s * a.x + t * bm.x, s * a.y + t * bm.y) : scalec(a, g0);
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < E; ++i) v[u][i] = scalec(v[u][i], sp.g[u][i]);
+            for (int i = 0; i < E; ++i) v[u][i] = scalec(v[u][i], mul(sp.g[u][i]));
         }
         fft_run<T, M, M, +1, true, false, Lay, true, R::WVC>(v[u], lay, c.j, tw);
 #pragma unroll
@@ -496,45 +533,72 @@ __device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const 
     }
 }
 
+// One product: the transform of the rows' pairs v (as the forward transform
+// takes them) to the rows of C v (as res_rows_inv leaves them).
+template <typename T, int M, int PAD, bool PRE, class TW, class MT>
+__device__ __forceinline__ bool res_product(cx<T>* v, cx<T>* lds, TW tw, const ResSpec<T, M, PAD>& sp, T c2, T c4,
+                                            cx<T>* Wb, int rb, int blk, const MT& all, unsigned long long token,
+                                            int* s_ok) {
+    res_rows_fwd<T, M, PAD>(v, lds, tw, Wb, rb);
+    if (!all.meet(token, s_ok)) return false;
+    res_cols<T, M, PAD, PRE>(lds, tw, sp, c2, c4, Wb, blk);
+    if (!all.meet(token + 1, s_ok)) return false;
+    res_rows_inv<T, M, PAD>(v, lds, tw, Wb, rb);
+    return true;
+}
+
 // ---- the kernel ---------------------------------------------------------------
-// Barrier tokens token .. token + 2 K - 1.  Ends after K iterations, before
-// an iteration that must wait for an FP64 check (st->pause), on breakdown, or
-// when a wait gives up.
-template <typename T, int M, int PAD, int NT>
-__global__ void __launch_bounds__(NT)
-    k_cg_resident(Tab<T> tab, SlotDesc sd, unsigned long long* words, int xcd, unsigned long long token, int K) {
+struct ResArgs {
+    SlotDesc sd;
+    unsigned long long* words;  // kMeetWords
+    unsigned long long token;   // the first of the launch's meetings' tokens
+    int xcd;                    // the XCD to run on (one-XCD grids)
+    int K;                      // iterations of this launch at most
+    int first;                  // the solve begins: state from the argument, no vectors yet
+    int zero;                   // ... from x = 0
+};
+
+// A solve, or up to K of its iterations: FP64 checks (check_decide) and CG
+// iterations until the solve is done.  Plain CG repeats the folded passes'
+// arithmetic, PCG (circulant preconditioner) that of iter_pcg.
+template <typename T, int M, int PAD, int NT, bool PCG>
+__global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> tab64, ResArgs ra, SolveState init) {
     using R = RGeo<T, M, PAD>;
     using G = Geo<T, M, PAD>;
-    constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L;
+    using R64 = RGeo<double, M, PAD>;
+    static_assert(R64::NT == NT && R64::NB == R::NB && R64::RT == R::RT && Geo<double, M, PAD>::RPW == G::RPW,
+                  "checks run on the same workgroups");
+    constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L, RT = R::RT;
     static_assert(NT == R::NT, "resident block size");
     constexpr int NSTG = fft_nstages(N);
     constexpr int RL = fft_radix(N, true, NSTG - 1), RK = PAD ? RL / 2 : RL, NO = (E / RL) * RK;
     static_assert(RL == fft_radix(N, false, 0), "forward first radix and inverse last radix");
-    __shared__ cx<T> lds[R::LDS_WORDS];
-    __shared__ double red[4 * (R::RT / 64)];
-    __shared__ double s_tot[4];
-    __shared__ int s_ok;
-    // ONEX: eight times the workgroups are launched, and those of the XCD
-    // asked for stay
-    if (R::ONEX && (int)(blockIdx.x & 7) != xcd) return;
+    constexpr bool MIXED = sizeof(T) == 4;
+    constexpr unsigned ITER_SETS = PCG ? 0x7u : 0x1fu, CHECK_SETS = (0xffu << 5) | (PCG ? 0x8u : 0u);
+    __shared__ cx<double> lds64[MIXED ? (R64::LDS_WORDS > (R::LDS_WORDS + 1) / 2 ? R64::LDS_WORDS : (R::LDS_WORDS + 1) / 2)
+                                      : R64::LDS_WORDS];
+    cx<T>* lds = reinterpret_cast<cx<T>*>(lds64);
+    __shared__ double red[8 * (RT / 64)];
+    __shared__ double s_tot[8];
+    __shared__ int s_ok, s_go;
+    __shared__ SolveState st;
+    // one-XCD grids: eight times the workgroups are launched, and those of
+    // the XCD asked for stay
+    if (R::ONEX && (int)(blockIdx.x & 7) != ra.xcd) return;
     const int blk = R::ONEX ? blockIdx.x >> 3 : blockIdx.x;
-    if (!GateIter::ok(sd)) return;
-    SolveState* st = sd.st;
-    double rho = st->rho_next;
-    int iters = st->iters;
+    const SlotDesc& sd = ra.sd;
     const int tid = threadIdx.x;
     const bool lead = blk == 0 && tid == 0;
-    if (check_due(st, rho, iters)) {
-        if (lead) st->pause = 1;
-        return;
-    }
-    const bool rows = tid < R::RT;  // this thread holds a part of a row
+    if (tid == 0) st = ra.first ? init : *sd.st;
+    __syncthreads();
+    if (st.done) return;
+    const bool rows = tid < RT;  // this thread holds a part of a row
     const int rl = tid / P, j = tid % P;
     const int rb = xcd_remap(blk, R::NB);  // as the passes: an XCD's workgroups share lines of W
     const int row = rows ? rb * RPW + rl : 0;
-    const Meet<R::NG, R::GM> all{words, st->bar_limit, blk % R::NG, blk / R::NG};
+    const Meet<R::NG, R::GM> all{ra.words, st.bar_limit, blk % R::NG, blk / R::NG};
     cx<T>* Wb = reinterpret_cast<cx<T>*>(sd.W);
-    T* xa = reinterpret_cast<T*>(sizeof(T) == 8 ? (void*)sd.x : (void*)sd.e);
+    unsigned long long token = ra.token;
     auto twiddles = [&]() {
         if constexpr (R::HOIST) {
             return ConstTw<T>{tab.tw};
@@ -547,61 +611,200 @@ __global__ void __launch_bounds__(NT)
     };
     auto give_up = [&]() {
         if (tid == 0) {
-            __hip_atomic_store(&st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            publish_status(sd, 1, ST_EGRID, st->gen, st->iters, st->last_check_iter);
+            __hip_atomic_store(&sd.st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&sd.st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
-    // both halves of the ring are empty before the first meeting
-    all.empty(0);
-    all.empty(1);
+    // all sums' words are empty before the first meeting
+    all.empty(0, ITER_SETS | CHECK_SETS);
+    all.empty(1, ITER_SETS | CHECK_SETS);
     auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
-    auto at = [&](int i) { return (size_t)row * L + col(i); };
-    cx<T> r[NO], p[NO], x[NO], d[NO];
+    // (recomputed where they are used, not kept in registers across the loop)
+    auto row0 = [&]() {
+        unsigned o = (unsigned)row * L + 2 * j;
+        asm volatile("" : "+v"(o));
+        return o;
+    };
+    auto rel = [&](int i) { return 2 * ((i / RK) * P + (i % RK) * (N / RL)); };
+    // r, p, d, the x accumulator (x itself, or the FP32 correction e), z
+    cx<T> r[NO], p[NO], x[NO], d[NO], z[PCG ? NO : 1];
+    T* xa = reinterpret_cast<T*>(MIXED ? (void*)sd.e : (void*)sd.x);
     if (rows) {
+        const unsigned o = row0();
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
-            r[i] = ld2<T>(reinterpret_cast<const T*>(sd.r) + at(i));
-            p[i] = ld2<T>(reinterpret_cast<const T*>(sd.p) + at(i));
-            x[i] = ld2<T>(xa + at(i));
-            if constexpr (sizeof(T) == 4)
-                d[i] = ld2<float>(sd.d32 + at(i));
-            else
-                d[i] = ld2<double>(sd.d + at(i));
+            const cx<double> d2 = ld2<double>(sd.d + o + rel(i));
+            d[i] = mkc((T)d2.x, (T)d2.y);
+            r[i] = p[i] = x[i] = mkc(T(0), T(0));
+            if constexpr (PCG) z[i] = mkc(T(0), T(0));
+            if (!ra.first) {
+                r[i] = ld2<T>(reinterpret_cast<const T*>(sd.r) + o + rel(i));
+                p[i] = ld2<T>(reinterpret_cast<const T*>(sd.p) + o + rel(i));
+                if constexpr (PCG) z[i] = ld2<T>(reinterpret_cast<const T*>(sd.z) + o + rel(i));
+            }
+            if (MIXED ? !ra.first : !ra.zero) x[i] = ld2<T>(xa + o + rel(i));
         }
     }
     ResSpec<T, M, PAD> sp;
     sp.load(tab, blk);
-    // p <- r + beta p with the pending x <- x + a p
-    auto direction = [&](T a, T beta) {
+    if (!all.hello(token, &s_ok)) return give_up();
+
+    // the scalars that change with an iteration are kept in registers (the
+    // same in every thread) and put into the state before a check and at the
+    // end
+    int iters = st.iters, restart = st.restart, k = 0, nchk = 0;
+    double alpha = st.alpha, rho_prev = st.rho_prev, rr = st.rho_next, rz = st.rho_cur;
+    auto save = [&]() {  // by thread 0
+        st.iters = iters;
+        st.restart = restart;
+        st.alpha = alpha;
+        st.rho_prev = rho_prev;
+        st.rho_next = rr;
+        st.rho_cur = rz;
+    };
+    // z = P^-1 r and this thread's part of r.z
+    auto precondition = [&](double* acc) {
+        cx<T> v[E];
 #pragma unroll
-        for (int i = 0; i < NO; ++i) {
-            const cx<T> po = p[i];
-            p[i] = mkc(r[i].x + beta * po.x, r[i].y + beta * po.y);
-            if (a != T(0)) {
-                x[i].x += a * po.x;
-                x[i].y += a * po.y;
+        for (int i = 0; i < NO; ++i) v[(i / RK) * RL + i % RK] = r[i];
+        const T c2 = (T)((double)M * (double)M * st.dbar);
+        const T c4 = (T)((double)M * (double)M * (double)M * (double)M);
+        if (!res_product<T, M, PAD, true>(v, lds, twiddles(), sp, c2, c4, Wb, rb, blk, all, token, &s_ok)) return false;
+        token += 2;
+        if (rows) {
+            const unsigned o = row0();
+#pragma unroll
+            for (int i = 0; i < NO; ++i) {
+                cx<T> c = v[(i / RK) * RL + i % RK];
+                if (sd.mask) {
+                    const Mask2 mk = mask2(sd, o + rel(i));
+                    c.x *= (T)mk.m0;
+                    c.y *= (T)mk.m1;
+                }
+                if constexpr (PCG) z[i] = c;
+                *acc += (double)r[i].x * (double)c.x + (double)r[i].y * (double)c.y;
             }
         }
+        return true;
     };
-    if (st->restart) {
+    for (;;) {
+        if (__builtin_expect(st.pause, 0)) {
+            // ---- FP64 check: x <- x + e + alpha p, e <- 0, r64 = b - A x ----
+            double acc[8] = {0, 0, 0, 0, 1.0e300, 0, 0, 0}, tot[8];
+            const bool zero = ra.first && ra.zero && st.checks == 0;  // x = 0: r = b, no product
+            constexpr int E64 = Geo<double, M, PAD>::ER;
+            static_assert(E64 == E, "the same pairs");
+            cx<double> v[E], xv[NO];
+            if (rows) {
+                const unsigned o = row0();
 #pragma unroll
-        for (int i = 0; i < NO; ++i) p[i] = r[i];
-    } else {
-        direction((T)st->alpha, (T)(rho / st->rho_prev));
-    }
-    double alpha = 0.0, rrn = 0.0;
-    bool stop = false;
-    if (!all.hello(token, &s_ok)) return give_up();
-    for (int k = 0;;) {
+                for (int i = 0; i < NO; ++i) {
+                    if constexpr (MIXED) {
+                        xv[i] = zero ? mkc(0.0, 0.0) : ld2<double>(sd.x + o + rel(i));
+                        xv[i].x += (double)x[i].x;
+                        xv[i].y += (double)x[i].y;
+                    } else {
+                        xv[i] = mkc((double)x[i].x, (double)x[i].y);
+                    }
+                    if (alpha != 0.0) {
+                        xv[i].x += alpha * (double)p[i].x;
+                        xv[i].y += alpha * (double)p[i].y;
+                    }
+                    const Mask2 mk = mask2(sd, o + rel(i));
+                    xv[i].x *= mk.m0;
+                    xv[i].y *= mk.m1;
+                    if constexpr (MIXED) {
+                        st2<double>(sd.x + o + rel(i), xv[i]);
+                        x[i] = mkc(T(0), T(0));
+                    } else {
+                        x[i] = mkc((T)xv[i].x, (T)xv[i].y);
+                    }
+                    v[(i / RK) * RL + i % RK] = xv[i];
+                }
+            }
+            if (!zero) {
+                Tab<double> t64 = tab64;
+                asm volatile("" : "+s"(t64.tw), "+s"(t64.ghq), "+s"(t64.ghN));
+                ResSpec<double, M, PAD> sp64;
+                sp64.load(t64, blk);
+                if (!res_product<double, M, PAD, false>(v, lds64, t64.tw, sp64, 0.0, 0.0,
+                                                        reinterpret_cast<cx<double>*>(sd.W), rb, blk, all, token, &s_ok))
+                    return give_up();
+                token += 2;
+            }
+            if (rows) {
+                const unsigned o = row0();
+#pragma unroll
+                for (int i = 0; i < NO; ++i) {
+                    const cx<double> c = zero ? mkc(0.0, 0.0) : v[(i / RK) * RL + i % RK];
+                    r[i] = EpiCheck<T>::pair(xv[i], ld2<double>(sd.b + o + rel(i)), ld2<double>(sd.d + o + rel(i)),
+                                             mask2(sd, o + rel(i)), c.x, c.y, st.checks > 0, r[i], acc);
+                }
+            }
+            if (!all.template sums<RT, 8, 1u << 4>(acc, 5, nchk & 1, red, s_tot, &s_ok, tot)) return give_up();
+            if (tid == 0) {
+                save();
+                if (st.checks == 0) st.dbar = tot[7] / (double)(L * L);
+                s_go = check_decide(&st, tot[0], tot[1], tot[2], tot[3], tot[5], tot[6], tot[4]);
+            }
+            __syncthreads();
+            if (!s_go) break;
+            rr = tot[3];  // |r|^2 of the replaced residual
+            alpha = 0.0;
+            restart = st.restart;
+            if constexpr (PCG) {
+                double a1[1] = {0.0};
+                if (!precondition(a1)) return give_up();
+                if (!all.template sums<RT, 1>(a1, 3, nchk & 1, red, s_tot, &s_ok, &rz)) return give_up();
+            }
+            ++nchk;
+            all.empty(nchk & 1, CHECK_SETS);
+        }
+        if (k >= ra.K) {
+            if (tid == 0) save();
+            break;
+        }
+        // ---- one CG iteration ----
+        if (__builtin_expect(check_due(&st, rr, iters), 0)) {
+            __syncthreads();
+            if (tid == 0) {
+                save();
+                st.pause = 1;
+            }
+            __syncthreads();
+            continue;
+        }
+        const double rho1 = PCG ? rz : rr;
+        {
+            // p <- r + beta p (z with the preconditioner), the pending x <- x + a p
+            const T a = (T)alpha, beta = (T)(restart ? 0.0 : rho1 / rho_prev);
+#pragma unroll
+            for (int i = 0; i < NO; ++i) {
+                const cx<T> po = p[i];
+                const cx<T> g = [&] {
+                    if constexpr (PCG)
+                        return z[i];
+                    else
+                        return r[i];
+                }();
+                if (restart) {
+                    p[i] = g;
+                } else {
+                    p[i] = mkc(g.x + beta * po.x, g.y + beta * po.y);
+                    if (a != T(0)) {
+                        x[i].x += a * po.x;
+                        x[i].y += a * po.y;
+                    }
+                }
+            }
+        }
         cx<T> v[E];
 #pragma unroll
         for (int i = 0; i < NO; ++i) v[(i / RK) * RL + i % RK] = p[i];
-        res_rows_fwd<T, M, PAD>(v, lds, twiddles(), Wb, rb);
-        if (!all.meet(token, &s_ok)) return give_up();
-        res_cols<T, M, PAD>(lds, twiddles(), sp, Wb, blk);
-        if (!all.meet(token + 1, &s_ok)) return give_up();
-        res_rows_inv<T, M, PAD>(v, lds, twiddles(), Wb, rb);
+        if (!res_product<T, M, PAD, false>(v, lds, twiddles(), sp, T(0), T(0), Wb, rb, blk, all, token, &s_ok))
+            return give_up();
+        token += 2;
+        constexpr int NS = PCG ? 1 : 4;
         double acc[4] = {0.0, 0.0, 0.0, 0.0}, tot[4];
         cx<T> q[NO];
         if (rows) {
@@ -613,68 +816,74 @@ __global__ void __launch_bounds__(NT)
                 pr.d = d[i];
                 q[i] = EpiCGU<T>::template outq<L>(sd, row, col(i), c.x, c.y, pr, acc);
             }
+            if constexpr (!PCG) {
 #pragma unroll
-            for (int i = 0; i < NO; ++i) {
-                const cx<double> rv = mkc((double)r[i].x, (double)r[i].y), qv = mkc((double)q[i].x, (double)q[i].y);
-                acc[1] += rv.x * rv.x + rv.y * rv.y;
-                acc[2] += rv.x * qv.x + rv.y * qv.y;
-                acc[3] += qv.x * qv.x + qv.y * qv.y;
+                for (int i = 0; i < NO; ++i) {
+                    const cx<double> rv = mkc((double)r[i].x, (double)r[i].y), qv = mkc((double)q[i].x, (double)q[i].y);
+                    acc[1] += rv.x * rv.x + rv.y * rv.y;
+                    acc[2] += rv.x * qv.x + rv.y * qv.y;
+                    acc[3] += qv.x * qv.x + qv.y * qv.y;
+                }
             }
         }
-        if (!all.template sums<R::RT, 4>(acc, 0, k & 1, red, s_tot, &s_ok, tot)) return give_up();
-        rho = tot[1];
+        if (!all.template sums<RT, NS>(acc, 0, k & 1, red, s_tot, &s_ok, tot)) return give_up();
+        const double rho = PCG ? rz : tot[1];
         if (!(tot[0] > 0.0) || !isfinite(tot[0]) || !isfinite(rho)) {
-            if (lead) {
-                st->status = ST_EBREAKDOWN;
-                st->done = 1;
-                publish_status(sd, 1, ST_EBREAKDOWN, st->gen, iters, st->last_check_iter);
+            __syncthreads();
+            if (tid == 0) {
+                save();
+                st.status = ST_EBREAKDOWN;
+                st.done = 1;
             }
-            return;
+            break;
         }
         alpha = rho / tot[0];
         const T a = (T)alpha;
-        const bool sure = next_rr(tot, (double)a, &rrn);
+        double accr[2] = {0.0, 0.0};
         if (rows) {
 #pragma unroll
             for (int i = 0; i < NO; ++i) {
                 r[i].x -= a * q[i].x;
                 r[i].y -= a * q[i].y;
+                accr[0] += (double)r[i].x * (double)r[i].x + (double)r[i].y * (double)r[i].y;
             }
         }
-        if (!sure) {
-            double rr[1] = {0.0};
-            if (rows) {
-#pragma unroll
-                for (int i = 0; i < NO; ++i) rr[0] += (double)r[i].x * r[i].x + (double)r[i].y * r[i].y;
-            }
+        if constexpr (PCG) {
+            if (!precondition(accr + 1)) return give_up();
+            double t2[2];
+            if (!all.template sums<RT, 2>(accr, 1, k & 1, red, s_tot, &s_ok, t2)) return give_up();
+            rr = t2[0];
+            rz = t2[1];
+        } else if (__builtin_expect(!next_rr(tot, (double)a, &rr), 0)) {
             __syncthreads();  // readers of the first sums
-            if (!all.template sums<R::RT, 1>(rr, 4, k & 1, red, s_tot, &s_ok, &rrn)) return give_up();
+            if (!all.template sums<RT, 1>(accr, 4, k & 1, red, s_tot, &s_ok, &rr)) return give_up();
         }
+        rho_prev = rho;
+        restart = 0;
         ++iters;
         ++k;
-        token += 2;
-        stop = check_due(st, rrn, iters);
-        if (stop || k >= K) break;
-        // the half that the next sums use: everybody has passed this
-        // iteration's meetings, hence the sums that used it last
-        all.empty(k & 1);
-        if (rows) direction(a, (T)(rrn / rho));
+        // the half that the next iteration uses: everybody has passed this
+        // one's meetings, hence the sums that used it last
+        all.empty(k & 1, ITER_SETS);
     }
+    // the results, and a last meeting: the state says done only when every
+    // workgroup has stored its rows
     if (rows) {
+        const unsigned o = row0();
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
-            st2<T>(reinterpret_cast<T*>(sd.r) + at(i), r[i]);
-            st2<T>(reinterpret_cast<T*>(sd.p) + at(i), p[i]);
-            st2<T>(xa + at(i), x[i]);
+            if (!st.done) {
+                st2<T>(reinterpret_cast<T*>(sd.r) + o + rel(i), r[i]);
+                st2<T>(reinterpret_cast<T*>(sd.p) + o + rel(i), p[i]);
+                if constexpr (PCG) st2<T>(reinterpret_cast<T*>(sd.z) + o + rel(i), z[i]);
+            }
+            if (!MIXED || !st.done) st2<T>(xa + o + rel(i), x[i]);
         }
     }
+    if (!all.meet(token, &s_ok)) return give_up();
     if (lead) {
-        st->alpha = alpha;
-        st->rho_prev = rho;
-        st->rho_next = rrn;
-        st->iters = iters;
-        st->restart = 0;
-        if (stop) st->pause = 1;
+        *sd.st = st;
+        publish_status(sd, st.done, st.status, st.gen, st.iters, st.last_check_iter);
     }
 }
 

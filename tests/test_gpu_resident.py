@@ -1,8 +1,10 @@
 """The resident kernel (whole CG iterations of a single solve in one launch,
 Sec. 3, Listing 2) against the passes whose arithmetic it repeats.
 
-* every grid and precision it is built for, and the grids at its edges: the
-  iterates and counts are bitwise those of the folded passes (mode 3);
+* every grid and precision it is built for, and the grids at its edges, plain
+  and preconditioned: the iterates and counts are bitwise those of the passes
+  (mode 3);
+* solves longer than a launch, iteration limits, b = 0 and refused data;
 * an iteration that reduces r.r so far that the difference of the sums
   cancels (a right-hand side close to an eigenvector): r.r is summed anew;
 * the masked operator (fracture driver), more solves at once than XCDs, and
@@ -51,6 +53,55 @@ def test_resident_bitwise_as_passes(L, padded, precision):
         assert out[1][1]["error_bound"] == out[3][1]["error_bound"]
         assert np.array_equal(out[1][0], out[3][0])
     assert plan.grid_sync(precision) != binding.GRID_FELL_BACK
+    plan.close()
+
+
+@pytest.mark.parametrize("precision", [binding.FP64, binding.MIXED])
+@pytest.mark.parametrize("L,padded", [(16, 1), (64, 1), (128, 1), (256, 1), (512, 1), (64, 0), (256, 0), (1024, 0)])
+def test_resident_precond_bitwise_as_passes(L, padded, precision):
+    """The preconditioned iteration: modes without the resident kernel (0 and
+    3) run its passes."""
+    inst = (padded_instance if padded else periodic_instance)(L, [7, 6, L, padded], eps=1e-3)
+    plan = binding.Plan(L, padded, inst["ghat"])
+    plan.set_precond(binding.PRECOND_CIRCULANT)
+    banner("resident-precond", L, padded, precision)
+    w = dev(np.random.default_rng([7, 7, L]).standard_normal((L, L)))
+    for kw in (dict(), dict(maxit=3), dict(x0=w)):
+        out = {m: _run(plan, inst, m, precision, **kw) for m in (3, 1)}
+        print(kw.keys(), [o[1]["iterations"] for o in out.values()], out[1][1]["error_bound"])
+        assert out[1][1]["status"] == out[3][1]["status"]
+        assert out[1][1]["iterations"] == out[3][1]["iterations"]
+        assert out[1][1]["error_bound"] == out[3][1]["error_bound"]
+        assert np.array_equal(out[1][0], out[3][0])
+    assert plan.grid_sync(precision) != binding.GRID_FELL_BACK
+    plan.close()
+
+
+def test_resident_many_iterations_and_limits():
+    """More iterations than one launch runs (256), maxit inside a launch, b =
+    0, invalid data, and a start vector with a NaN."""
+    L = 32
+    inst = padded_instance(L, [7, 8], eps=1e-3)
+    plan = binding.Plan(L, 1, inst["ghat"] ** 3 + 1e-4)  # ill-conditioned: hundreds of iterations
+    plan.set_engine(binding.ENGINE_MULTIPASS)
+    banner("resident-many", L)
+    for precision in (binding.FP64, binding.MIXED):
+        out = {m: _run(plan, inst, m, precision, maxit=700) for m in (3, 1)}
+        print([o[1] for o in out.values()])
+        assert out[1][1]["iterations"] == out[3][1]["iterations"] > 256
+        assert out[1][1]["status"] == out[3][1]["status"]
+        assert np.array_equal(out[1][0], out[3][0])
+    zero = dict(inst, b=np.zeros((L, L)))
+    x, info = _run(plan, zero, 1, binding.MIXED)
+    assert info["status"] == binding.OK and info["iterations"] == 0 and not x.any()
+    bad = dict(inst, d=inst["d"].copy())
+    bad["d"][3, 5] = -1.0
+    import torch
+    for x0, i, want in ((None, bad, binding.EINVAL), (np.full((L, L), np.nan), inst, binding.EBREAKDOWN)):
+        x = torch.zeros((L, L), dtype=torch.float64, device="cuda")
+        with pytest.raises(binding.FftcgError) as e:
+            plan.solve(dev(i["d"]), dev(i["b"]), x, x0=None if x0 is None else dev(x0), precision=binding.MIXED)
+        assert e.value.status == want
     plan.close()
 
 
