@@ -80,6 +80,13 @@ struct EngineOps {
     // whether the turn pass is resident as a whole as well (implies
     // grid_capable)
     bool (*turn_capable)(int prec);
+    // K preconditioned iterations of a single slot as a chunk, with the two
+    // turns behind grid-wide barriers: row_fwd, (col, turn, col) with a turn
+    // between them, row_inv.  *token as above.
+    void (*iter_pcg_chunk)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride, unsigned long long* token,
+                           int K, hipStream_t s);
+    // whether that is built and resident as a whole
+    bool (*turn_pcg_capable)(int prec);
     // a single solve, or K of its iterations, in one launch
     // (k_solve_resident); pcg: with the circulant preconditioner.  st: the
     // state it begins with (run.first), else taken from the slot's.

@@ -59,7 +59,7 @@ void apply_pass_t(int pass, const PlanTabs& pt, const double* d, const double* x
         hipLaunchKernelGGL((k_row_fwd<T, M, PAD, ProApply<T>, ByVal, RT>), dim3(G<T>::ROW_BLOCKS), dim3(RT), 0,
                            s, tab, sv, 0, 0);
     else if (pass == 1)
-        hipLaunchKernelGGL((k_col<T, M, PAD, GateAlways, ByVal, CT>), dim3(G<T>::NTILE), dim3(CT), 0, s, tab, sv);
+        hipLaunchKernelGGL((k_col<T, M, PAD, GateAlways, ByVal, CT>), dim3(G<T>::COL_BLOCKS), dim3(CT), 0, s, tab, sv);
     else
         hipLaunchKernelGGL((k_row_inv<T, M, PAD, EpiApply<T>, ByVal, RT>), dim3(G<T>::ROW_BLOCKS), dim3(RT), 0,
                            s, tab, sv, 0);
@@ -93,7 +93,7 @@ void iter_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, h
     const Tab<W> tab = tab_of<W>(pt);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, XA, RT>, ByPtr, RT>), dim3(G<W>::ROW_BLOCKS, nslots),
                        dim3(RT), 0, s, tab, sp, g4_blocks(), stride);
-    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE, nslots), dim3(CT), 0, s, tab,
+    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS, nslots), dim3(CT), 0, s, tab,
                        sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiCG<W>, ByPtr, RT>), dim3(G<W>::ROW_BLOCKS, nslots), dim3(RT), 0,
                        s, tab, sp, stride);
@@ -113,7 +113,7 @@ void iter_grid_t(const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned 
     const Tab<W> tab = tab_of<W>(pt);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT, true>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, 0,
                        stride);
-    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, tab, sp);
+    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s, tab, sp);
     hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride, token);
 }
 
@@ -151,7 +151,7 @@ void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, 
             hipExtLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, e0,
                                   e1, 0, tab, sp, g4_blocks(), stride);
     } else if (pass == 1) {
-        hipExtLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, e0, e1, 0,
+        hipExtLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s, e0, e1, 0,
                               tab, sp);
     } else if (pass == 2) {
         if (grid) {
@@ -226,12 +226,12 @@ void iter_grid_chunk_t(const PlanTabs& pt, const SlotDesc* slot, int stride, uns
             const Tab<W> tab = tab_of<W>(pt);
             hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProCG<W, W, RT, true>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s,
                                tab, sp, 0, stride);
-            hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, tab, sp);
+            hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s, tab, sp);
             for (int k = 1; k < K; ++k) {
                 const unsigned long long t = *token + 1;
                 *token += 2;
                 hipLaunchKernelGGL((k_row_turn<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride, t);
-                hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE), dim3(CT), 0, s, tab,
+                hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s, tab,
                                    sp);
             }
             hipLaunchKernelGGL((k_row_inv_upd<W, M, PAD, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp, stride,
@@ -308,7 +308,7 @@ void check_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, 
     const Tab<double> tab = tab_of<double>(pt);
     hipLaunchKernelGGL((k_row_fwd<double, M, PAD, ProCheck<W, RT>, ByPtr, RT>),
                        dim3(G<double>::ROW_BLOCKS, nslots), dim3(RT), 0, s, tab, sp, 0, stride);
-    hipLaunchKernelGGL((k_col<double, M, PAD, GateCheck, ByPtr, CT>), dim3(G<double>::NTILE, nslots), dim3(CT), 0,
+    hipLaunchKernelGGL((k_col<double, M, PAD, GateCheck, ByPtr, CT>), dim3(G<double>::COL_BLOCKS, nslots), dim3(CT), 0,
                        s, tab, sp);
     hipLaunchKernelGGL((k_row_inv<double, M, PAD, EpiCheck<W>, ByPtr, RT>), dim3(G<double>::ROW_BLOCKS, nslots),
                        dim3(RT), 0, s, tab, sp, stride);
@@ -335,13 +335,13 @@ void iter_pcg_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int strid
     const Tab<W> tab = tab_of<W>(pt);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPCG<W, XA, RT, RB, G<W>::SUM_GROUPS>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
                        tab, sp, RB, stride);
-    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::NTILE, nslots), dim3(CT), 0, s, tab,
+    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS, nslots), dim3(CT), 0, s, tab,
                        sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiCG<W>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s, tab, sp,
                        stride);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProUpdPre<W, RT, RB, G<W>::SUM_GROUPS>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
                        tab, sp, 0, stride);
-    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT, true>), dim3(G<W>::NTILE, nslots), dim3(CT), 0, s,
+    hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT, true>), dim3(G<W>::COL_BLOCKS, nslots), dim3(CT), 0, s,
                        tab, sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiPre<W, GateIter>, ByPtr, RT>), dim3(RB, nslots), dim3(RT), 0, s,
                        tab, sp, stride);
@@ -352,6 +352,62 @@ void iter_pcg_fn(int prec, const PlanTabs& pt, const SlotDesc* slots, int nslots
         iter_pcg_t<double, double>(pt, slots, nslots, stride, s);
     else
         iter_pcg_t<float, float>(pt, slots, nslots, stride, s);
+}
+
+// The two turns in place of four row passes per iteration, where their grid is
+// resident at once (FP32: 120 VGPRs, four workgroups per CU at M = 4096).
+// Measured with the plan's other choices alike.
+template <typename W>
+constexpr bool kTurnPcgBuilt = !kResBuilt<W> && sizeof(W) == 4 && M >= 2048 && M <= 4096;
+
+template <typename W>
+bool turn_pcg_capable_t() {
+    if constexpr (!kTurnPcgBuilt<W>) {
+        return false;
+    } else {
+        constexpr int RT = G<W>::ROW_THREADS, RB = G<W>::ROW_BLOCKS;
+        return whole_grid_resident<RT, RB>(
+                   reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnR<W>, ByPtr, RT>)) &&
+               whole_grid_resident<RT, RB>(
+                   reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnZ<W>, ByPtr, RT>));
+    }
+}
+
+bool turn_pcg_capable_fn(int prec) {
+    return prec == 0 ? turn_pcg_capable_t<double>() : turn_pcg_capable_t<float>();
+}
+
+template <typename W>
+void iter_pcg_chunk_t(const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long* token, int K,
+                      hipStream_t s) {
+    if constexpr (kTurnPcgBuilt<W>) {
+        constexpr int RT = G<W>::ROW_THREADS, CT = G<W>::COL_THREADS, RB = G<W>::ROW_BLOCKS;
+        const ByPtr sp{slot};
+        const Tab<W> tab = tab_of<W>(pt);
+        hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPCG<W, W, RT, RB, G<W>::SUM_GROUPS>, ByPtr, RT>), dim3(RB),
+                           dim3(RT), 0, s, tab, sp, RB, stride);
+        for (int k = 0; k < K; ++k) {
+            if (k > 0)
+                hipLaunchKernelGGL((k_row_turn_pcg<W, M, PAD, EpiTurnZ<W>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab,
+                                   sp, stride, ++*token);
+            hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s, tab,
+                               sp);
+            hipLaunchKernelGGL((k_row_turn_pcg<W, M, PAD, EpiTurnR<W>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp,
+                               stride, ++*token);
+            hipLaunchKernelGGL((k_col<W, M, PAD, GateIter, ByPtr, CT, true>), dim3(G<W>::COL_BLOCKS), dim3(CT), 0, s,
+                               tab, sp);
+        }
+        hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiPre<W, GateIter>, ByPtr, RT>), dim3(RB), dim3(RT), 0, s, tab, sp,
+                           stride);
+    }
+}
+
+void iter_pcg_chunk_fn(int prec, const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long* token,
+                       int K, hipStream_t s) {
+    if (prec == 0)
+        iter_pcg_chunk_t<double>(pt, slot, stride, token, K, s);
+    else
+        iter_pcg_chunk_t<float>(pt, slot, stride, token, K, s);
 }
 
 // FP64 check of the preconditioned solve (r.r partial count = the working
@@ -366,7 +422,7 @@ void check_pcg_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stri
     const Tab<W> tabw = tab_of<W>(pt);
     hipLaunchKernelGGL((k_row_fwd<double, M, PAD, ProCheck<W, RT>, ByPtr, RT>),
                        dim3(G<double>::ROW_BLOCKS, nslots), dim3(RT), 0, s, tab, sp, 0, stride);
-    hipLaunchKernelGGL((k_col<double, M, PAD, GateCheck, ByPtr, CT>), dim3(G<double>::NTILE, nslots), dim3(CT), 0,
+    hipLaunchKernelGGL((k_col<double, M, PAD, GateCheck, ByPtr, CT>), dim3(G<double>::COL_BLOCKS, nslots), dim3(CT), 0,
                        s, tab, sp);
     hipLaunchKernelGGL((k_row_inv<double, M, PAD, EpiCheck<W>, ByPtr, RT>), dim3(G<double>::ROW_BLOCKS, nslots),
                        dim3(RT), 0, s, tab, sp, stride);
@@ -374,7 +430,7 @@ void check_pcg_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stri
                        stride, LL * LL);
     hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPre<W>, ByPtr, RTW>), dim3(RBW, nslots), dim3(RTW), 0, s, tabw, sp,
                        0, stride);
-    hipLaunchKernelGGL((k_col<W, M, PAD, GatePre, ByPtr, CTW, true>), dim3(G<W>::NTILE, nslots), dim3(CTW), 0, s,
+    hipLaunchKernelGGL((k_col<W, M, PAD, GatePre, ByPtr, CTW, true>), dim3(G<W>::COL_BLOCKS, nslots), dim3(CTW), 0, s,
                        tabw, sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiPre<W, GatePre>, ByPtr, RTW>), dim3(RBW, nslots), dim3(RTW), 0, s,
                        tabw, sp, stride);
@@ -403,7 +459,7 @@ void check0_t(bool pcg, const PlanTabs& pt, const SlotDesc* slots, int nslots, i
         const Tab<W> tabw = tab_of<W>(pt);
         hipLaunchKernelGGL((k_row_fwd<W, M, PAD, ProPre<W>, ByPtr, RTW>), dim3(RBW, nslots), dim3(RTW), 0, s, tabw,
                            sp, 0, stride);
-        hipLaunchKernelGGL((k_col<W, M, PAD, GatePre, ByPtr, CTW, true>), dim3(G<W>::NTILE, nslots), dim3(CTW), 0,
+        hipLaunchKernelGGL((k_col<W, M, PAD, GatePre, ByPtr, CTW, true>), dim3(G<W>::COL_BLOCKS, nslots), dim3(CTW), 0,
                            s, tabw, sp);
         hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiPre<W, GatePre>, ByPtr, RTW>), dim3(RBW, nslots), dim3(RTW), 0,
                            s, tabw, sp, stride);
@@ -444,6 +500,8 @@ const EngineOps kOps = {M,
                         &grid_capable_fn,
                         &iter_grid_chunk_fn,
                         &turn_capable_fn,
+                        &iter_pcg_chunk_fn,
+                        &turn_pcg_capable_fn,
                         &resident_fn,
                         &resident_xcds_fn,
                         &resident_capable_fn};

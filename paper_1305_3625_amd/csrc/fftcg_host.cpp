@@ -271,6 +271,8 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
         p->grid_cap[1] = p->ops->grid_capable(FFTCG_MIXED);
         p->turn_cap[0] = p->grid_cap[0] && p->ops->turn_capable(FFTCG_FP64);
         p->turn_cap[1] = p->grid_cap[1] && p->ops->turn_capable(FFTCG_MIXED);
+        p->turn_pcg_cap[0] = p->ops->turn_pcg_capable(FFTCG_FP64);
+        p->turn_pcg_cap[1] = p->ops->turn_pcg_capable(FFTCG_MIXED);
     }
     // quarter spectrum (host copy, FP64) for the fused engine
     p->quarter.resize((size_t)(M / 2 + 1) * (M / 2 + 1));
@@ -894,8 +896,11 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
             }
         }
     }
-    bool grid = plan->grid_mode != 0 && !plan->grid_broken.load() && plan->grid_cap[precision == FFTCG_MIXED] &&
-                plan->precond == FFTCG_PRECOND_NONE;
+    // the folded update (any mode but 0), or the preconditioned turns (1, 2)
+    bool grid = !plan->grid_broken.load() &&
+                (plan->precond == FFTCG_PRECOND_NONE
+                     ? plan->grid_mode != 0 && plan->grid_cap[precision == FFTCG_MIXED]
+                     : (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->turn_pcg_cap[precision == FFTCG_MIXED]);
     int rc = FFTCG_OK;
     // a warm start in place is kept in q, which the grid-synchronised path
     // never writes, so that a solve abandoned at a barrier can be repeated
@@ -972,7 +977,9 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
         bool finished = false;
         while (!finished) {
             const int K = planner.next();
-            if (grid)
+            if (grid && pcg)
+                ops->iter_pcg_chunk(precision, plan->tabs, w->slot, plan->stride, &w->grid_token, K, s);
+            else if (grid)
                 ops->iter_grid_chunk(precision, plan->tabs, w->slot, plan->stride, &w->grid_token, K,
                                      plan_turn(plan, precision), s);
             else

@@ -112,6 +112,7 @@ struct fftcg_plan_s {
     int grid_mode = 1;
     bool grid_cap[2] = {false, false};
     bool turn_cap[2] = {false, false};  // the turn pass (k_row_turn) resident as a whole, per precision
+    bool turn_pcg_cap[2] = {false, false};  // the preconditioned turns, likewise
     // the resident kernel, per precision, plain and preconditioned: -1 not
     // asked yet (the first solve does), 0 no, 1 yes
     std::atomic<int> res_cap[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};

@@ -76,10 +76,21 @@ struct Geo {
 #ifndef FFTCG_COL_TTMAX
 #define FFTCG_COL_TTMAX 4
 #endif
-    static constexpr int TT = TT_fit(cmin(N, FFTCG_COL_TTMAX));
-    static constexpr int COL_SH = ilog2c(16 * TT);
-    static constexpr int COL_THREADS = TT * PC;
+#ifndef FFTCG_W_TT
+#define FFTCG_W_TT 2
+#endif
+    static constexpr int TT = (M >= 8192 && sizeof(T) == 4) ? FFTCG_W_TT : TT_fit(cmin(N, FFTCG_COL_TTMAX));
+    // columns per workgroup: a whole tile, but one column of the pair on the
+    // largest grid, where a tile takes 140 KB of LDS and leaves one workgroup
+    // per CU, whose loads, transform and stores then run one after another.
+    // Two workgroups of a column each overlap them (M = 8192 FP32: column
+    // pass 137 -> 105 us); W keeps its pairs, for the row passes' 32-byte
+    // runs (with tiles of one column the row passes lost 33 us).
+    static constexpr int CT = (M >= 8192 && TT > 1) ? 1 : TT;
+    static constexpr int COL_SH = ilog2c(16 * CT);
+    static constexpr int COL_THREADS = CT * PC;
     static constexpr int NTILE = N / TT;
+    static constexpr int COL_BLOCKS = N / CT;
     static constexpr int MH = M / 2 + 1;
 };
 
@@ -788,6 +799,18 @@ struct EpiCGU : EpiCG<W> {
     static constexpr int NACC = 4;
     static constexpr bool UPD = true;
 };
+// The preconditioned iteration's two turns, each a row-inverse pass that goes
+// on into a forward row pass on the same rows behind one barrier:
+// EpiTurnR: q = A p, the sum p.q; then alpha, r <- r - alpha q, and r's
+//   transform (EpiCG's pass followed by ProUpdPre's).
+// EpiTurnZ: z = P^-1 r, the sums r.z and r.r; then beta, the check decision,
+//   p <- z + beta p, the pending x update, and p's transform (EpiPre's pass
+//   followed by ProPCG's).
+// q and z never reach memory.
+template <typename W>
+struct EpiTurnR : EpiCG<W> {
+    static constexpr int TURN = 1;
+};
 template <class E, class = void>
 struct EpiUpd {
     static constexpr bool value = false;
@@ -795,6 +818,14 @@ struct EpiUpd {
 template <class E>
 struct EpiUpd<E, decltype((void)E::UPD)> {
     static constexpr bool value = E::UPD;
+};
+template <class E, class = void>
+struct EpiTurn {
+    static constexpr int value = 0;
+};
+template <class E>
+struct EpiTurn<E, decltype((void)E::TURN)> {
+    static constexpr int value = E::TURN;
 };
 
 // r.r after the update from the totals t = {p.q, r.r, r.q, q.q} (a: alpha in
@@ -835,7 +866,8 @@ __device__ __forceinline__ bool next_rr(const double* t, double a, double* rr) {
 template <int NT, int N, int NG>
 __device__ inline bool grid_sums(const double* acc, double* part, int stride, unsigned long long token,
                                  long long limit, double* sh, double* tot) {
-    constexpr int sets[4] = {PS_PQ, PS_RR, PS_RQ, PS_QQ};
+    // (N = 2, the preconditioned turn: r.z and r.r)
+    constexpr int sets[4] = {PS_PQ, N == 2 ? PS_RZ : PS_RR, PS_RQ, PS_QQ};
     static_assert(N <= 4, "four sets");
     __shared__ double s_tot[N];
     __shared__ int s_ok;
@@ -995,6 +1027,12 @@ struct EpiPre {
     }
 };
 
+template <typename W>
+struct EpiTurnZ : EpiPre<W, GateIter> {
+    static constexpr int NACC = 2;
+    static constexpr int TURN = 2;
+};
+
 // Whether a prologue defers part of its work until after the transform.
 template <class P, class = void>
 struct ProLate {
@@ -1146,13 +1184,22 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
     using G = Geo<T, M, PAD>;
     constexpr int E = G::EC, P = G::PC, TT = G::TT, L = G::L, MH = G::MH;
     static_assert(NT == G::COL_THREADS, "column block size");
-    using Lay = LdsLay<T, TT, G::COL_SH, TT>;
+    constexpr int CT = G::CT;
+    using Lay = LdsLay<T, CT, G::COL_SH, CT>;
     __shared__ cx<T> lds[Lay::words(M)];
     const SlotDesc& sd = slot.get();
     if (!Gate::ok(sd)) return;
-    const int kt = blockIdx.x;
-    const int tid = threadIdx.x, kk = tid % TT, j = tid / TT;
-    Lay lay{lds, kk};
+    const int tid = threadIdx.x, kl = tid % CT, j = tid / CT;
+    int kt = blockIdx.x, kk = kl;  // tile, column in it
+    if constexpr (CT < TT) {
+        // the columns of a tile go to workgroups next to each other on one
+        // XCD (workgroups go round robin over the eight), which share its lines
+        static_assert(CT == 1 && G::COL_BLOCKS % (8 * TT) == 0, "tiles split by columns over the XCDs");
+        const int i = blockIdx.x >> 3;
+        kt = (i / TT) * 8 + (blockIdx.x & 7);
+        kk = i % TT;
+    }
+    Lay lay{lds, kl};
     cx<T>* Wt = reinterpret_cast<cx<T>*>(sd.W) + (size_t)kt * L * TT;
     cx<T> v[E];
     constexpr int NSTG = fft_nstages(M);
@@ -1238,6 +1285,132 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
             const int n = (j + u * P) + r * (M / RZ);
             gst(Wt + (size_t)n * TT + kk, v[u * RZ + r]);
         }
+}
+
+// What follows the row-inverse transform in the preconditioned turns (v: its
+// outputs; pre: prefetched operands, or not where they are read here).
+template <typename T, int M, int PAD, class Epi, int NT, int TURN, class PreA>
+__device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, double* red, const Tab<T>& tab,
+                                         const SlotDesc& sd, int stride, unsigned long long token, int row0) {
+    using G = Geo<T, M, PAD>;
+    constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L;
+    constexpr int NSTG = fft_nstages(N);
+    constexpr int RL = NSTG > 0 ? fft_radix(N, true, NSTG - 1) : 1, R1 = NSTG > 0 ? fft_radix(N, false, 0) : 1;
+    static_assert(R1 == RL, "forward first radix and inverse last radix");
+    constexpr int RK = (PAD && RL > 1) ? RL / 2 : RL, NO = (E / RL) * RK;
+    const int tid = threadIdx.x, rl = tid / P, j = tid % P, row = row0 + rl;
+    SolveState* st = sd.st;
+    auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
+    auto at = [&](const void* p, int i) { return (T*)p + (size_t)row * L + col(i); };
+    auto give_up = [&]() {
+        if (tid == 0) {
+            __hip_atomic_store(&st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            publish_status(sd, 1, ST_EGRID, st->gen, st->iters, st->last_check_iter);
+        }
+    };
+    constexpr bool HAVE = std::extent<std::remove_reference_t<PreA>>::value == NO;
+    cx<T> w[NO];  // q, then the new r (TURN 1); z, then the new p (TURN 2)
+    double acc[2] = {0.0, 0.0}, tot[2];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        const cx<T> c = v[(i / RK) * RL + i % RK];
+        typename Epi::Pre pr;
+        if constexpr (HAVE)
+            pr = pre[i];
+        else
+            pr = Epi::template pre<L>(sd, row, col(i));
+        if constexpr (TURN == 1) {
+            w[i] = Epi::template outq<L>(sd, row, col(i), c.x, c.y, pr, acc);
+        } else {
+            w[i] = c;
+            if (sd.mask) {
+                const Mask2 mk = mask2(sd, (size_t)row * L + col(i));
+                w[i] = mkc(c.x * (T)mk.m0, c.y * (T)mk.m1);
+            }
+            acc[0] += (double)pr.r.x * (double)w[i].x + (double)pr.r.y * (double)w[i].y;
+            acc[1] += (double)pr.r.x * (double)pr.r.x + (double)pr.r.y * (double)pr.r.y;
+        }
+    }
+    // the operands that the second half changes, requested before the barrier
+    cx<T> o[NO];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) o[i] = ld2<T>(at(TURN == 1 ? sd.r : sd.p, i));
+    if (!grid_sums<NT, TURN, G::SUM_GROUPS>(acc, sd.part, stride, token, st->bar_limit, red, tot)) {
+        give_up();
+        return;
+    }
+    cx<T> v2[E];
+    if constexpr (TURN == 1) {
+        const double pq = tot[0], rho = st->rho_cur;
+        if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
+            if (blockIdx.x == 0 && tid == 0) {
+                st->status = ST_EBREAKDOWN;
+                st->done = 1;
+                publish_status(sd, 1, ST_EBREAKDOWN, st->gen, st->iters, st->last_check_iter);
+            }
+            return;
+        }
+        const double alpha = rho / pq;
+        const T a = (T)alpha;
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            o[i].x -= a * w[i].x;
+            o[i].y -= a * w[i].y;
+            st2<T>(at(sd.r, i), o[i]);
+            v2[(i / RK) * RL + i % RK] = o[i];
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            st->alpha = alpha;
+            st->rho_prev = rho;
+            st->iters += 1;
+            st->restart = 0;
+        }
+        // r.r of the updated residual for the next launch's prologue, should
+        // the next one be a separate pass
+        double rr = 0.0;
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            rr += (double)o[i].x * (double)o[i].x + (double)o[i].y * (double)o[i].y;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const double s = block_sum<NT>(rr, red);
+        if (tid == 0) sd.part[PS_RR * stride + blockIdx.x] = s;
+    } else {
+        const double rz = tot[0], rr = tot[1];
+        if (check_due(st, rr)) {
+            if (blockIdx.x == 0 && tid == 0) st->pause = 1;
+            return;
+        }
+        // (an iteration always precedes, so this is no restart)
+        const T a = (T)st->alpha, beta = (T)(rz / st->rho_prev);
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            const cx<T> p2 = mkc(w[i].x + beta * o[i].x, w[i].y + beta * o[i].y);
+            st2<T>(at(sd.p, i), p2);
+            v2[(i / RK) * RL + i % RK] = p2;
+        }
+        if (a != T(0)) {
+            const void* xa = sizeof(T) == 8 ? (const void*)sd.x : (const void*)sd.e;
+#pragma unroll
+            for (int i = 0; i < NO; ++i) {
+                cx<T> xv = ld2<T>(at(xa, i));
+                xv.x += a * o[i].x;
+                xv.y += a * o[i].y;
+                st2<T>(at(xa, i), xv);
+            }
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            st->rho_cur = rz;
+            st->need_pre = 0;
+        }
+    }
+    // the forward transform reads its tables afresh, as in the turn pass below
+    Tab<T> tab2 = tab;
+    asm volatile("" : "+s"(tab2.tw));
+    int tid2 = tid;
+    asm volatile("" : "+v"(tid2));
+    row_fwd_out<T, M, PAD, NT>(v2, lds, tab2, sd, __builtin_amdgcn_readfirstlane(row0 / RPW), tid2);
 }
 
 // Body of the row-inverse pass; token, token + 1: the grid-wide barriers'
@@ -1343,7 +1516,12 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     for (int a = 0; a < (Epi::NACC > 0 ? Epi::NACC : 1); ++a) acc[a] = 0.0;
     if constexpr (Epi::NACC > 4) acc[4] = 1.0e300;
     constexpr bool UPD = EpiUpd<Epi>::value;
+    constexpr int TURN = EpiTurn<Epi>::value;
     constexpr int NO = (E / RL) * RK;  // outputs (pairs) of this thread
+    if constexpr (TURN > 0) {
+        turn_pcg<T, M, PAD, Epi, NT, TURN>(v, pre, lds, red, tab, sd, stride, token, row0);
+        return;
+    }
     cx<T> qk[UPD ? NO : 1], rk[UPD ? NO : 1];
     static_assert(!FWD || UPD, "the fused forward pass follows the folded update");
     cx<T> pk[FWD ? NO : 1];  // FWD: p of the pairs, for the next direction and the x update
@@ -1536,6 +1714,13 @@ template <typename T, int M, int PAD, class Slot, int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
 k_row_turn(Tab<T> tab, Slot slot, int stride, unsigned long long token) {
     row_inv_body<T, M, PAD, EpiCGU<T>, Slot, NT, true>(tab, slot, stride, token);
+}
+
+// The preconditioned turns (EpiTurnR, EpiTurnZ), one barrier each.
+template <typename T, int M, int PAD, class Epi, class Slot, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+k_row_turn_pcg(Tab<T> tab, Slot slot, int stride, unsigned long long token) {
+    row_inv_body<T, M, PAD, Epi, Slot, NT>(tab, slot, stride, token);
 }
 
 // r <- r - alpha q, partial r . r.  alpha = rho / (p . q) from the partials

@@ -57,7 +57,8 @@ def test_resident_bitwise_as_passes(L, padded, precision):
 
 
 @pytest.mark.parametrize("precision", [binding.FP64, binding.MIXED])
-@pytest.mark.parametrize("L,padded", [(16, 1), (64, 1), (128, 1), (256, 1), (512, 1), (64, 0), (256, 0), (1024, 0)])
+@pytest.mark.parametrize("L,padded", [(16, 1), (64, 1), (128, 1), (256, 1), (512, 1), (1024, 1), (2048, 1),
+                                      (64, 0), (256, 0), (1024, 0), (2048, 0)])
 def test_resident_precond_bitwise_as_passes(L, padded, precision):
     """The preconditioned iteration: modes without the resident kernel (0 and
     3) run its passes."""
