@@ -112,10 +112,11 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
 __device__ __forceinline__ void publish_status(const SlotDesc& sd, int done, int status, int gen, int iters,
                                                int last_check) {
     if (!sd.host_status) return;
-    __hip_atomic_store(sd.host_status + 1, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(sd.host_status + 2, last_check, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(sd.host_status + 3, iters, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(sd.host_status, 2 * gen + (done ? 1 : 0), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    auto* hs = gbl(sd.host_status);
+    __hip_atomic_store(hs + 1, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(hs + 2, last_check, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(hs + 3, iters, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(hs, 2 * gen + (done ? 1 : 0), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- CG control shared by both engines --------------------------------------
@@ -129,16 +130,30 @@ __device__ __forceinline__ void publish_status(const SlotDesc& sd, int done, int
 // progress.
 // iters: the iteration count the decision is for (st->iters, unless the
 // caller has counted an iteration whose store to st it cannot read back)
-__device__ __forceinline__ bool check_due(const SolveState* st, double rr, int iters) {
-    const bool progressed = iters > st->last_check_iter;
-    const bool periodic = st->refresh > 0 && iters - st->last_check_iter >= st->refresh;
-    const bool candidate = progressed && !(rr > st->trigger_rr);
+// What the decision depends on besides r.r, read all at once (each read of
+// the state costs an L2 round trip when a branch separates it from the next)
+struct CheckIn {
+    double trigger_rr, delta2, rho_ref;
+    int iters, last_check_iter, refresh, maxit;
+};
+template <class St>
+__device__ __forceinline__ CheckIn check_in(const St* st) {
+    return CheckIn{st->trigger_rr, st->delta2, st->rho_ref, st->iters, st->last_check_iter, st->refresh, st->maxit};
+}
+__device__ __forceinline__ bool check_due(const CheckIn& c, double rr, int iters) {
+    const int since = iters - c.last_check_iter;
+    const bool progressed = since > 0;
+    const bool periodic = (c.refresh > 0) & (since >= c.refresh);
+    const bool candidate = progressed & !(rr > c.trigger_rr);
     // a reliable update is skipped when the convergence trigger lies within
     // a factor 100 (10 in the residual norm) below its threshold: the check at
     // candidate convergence comes soon and replaces the residual as well
-    const double rel = st->delta2 * st->rho_ref;
-    const bool reliable = progressed && rr <= rel && st->trigger_rr < 1e-2 * rel;
-    return iters >= st->maxit || candidate || periodic || reliable;
+    const double rel = c.delta2 * c.rho_ref;
+    const bool reliable = progressed & (rr <= rel) & (c.trigger_rr < 1e-2 * rel);
+    return (iters >= c.maxit) | candidate | periodic | reliable;
+}
+__device__ __forceinline__ bool check_due(const SolveState* st, double rr, int iters) {
+    return check_due(check_in(st), rr, iters);
 }
 __device__ __forceinline__ bool check_due(const SolveState* st, double rr) { return check_due(st, rr, st->iters); }
 
@@ -288,6 +303,39 @@ template <typename T>
 __device__ __forceinline__ void st2(T* p, cx<T> c) {
     gst(reinterpret_cast<cx<T>*>(p), c);
 }
+// The same at element idx of a base that is the same in every thread: a 32-bit
+// byte offset beside a base in scalar registers (every array is under 4 GB),
+// instead of a 64-bit address per element (an eighth of the turn pass's
+// vector instructions were address arithmetic and sign extensions).
+template <typename V, typename T>
+__device__ __forceinline__ typename GlobalT<V>::type* at_byte(T* base, unsigned bytes) {
+    typedef typename GlobalT<char>::type C;
+    return (typename GlobalT<V>::type*)((C*)base + bytes);
+}
+template <typename T>
+__device__ __forceinline__ cx<T> ld2(const T* base, unsigned idx) {
+    const auto v = *at_byte<const typename VecT<T, 2>::type>(const_cast<T*>(base), idx * (unsigned)sizeof(T));
+    return mkc(v.x, v.y);
+}
+template <typename T>
+__device__ __forceinline__ void st2(T* base, unsigned idx, cx<T> c) {
+    typename VecT<T, 2>::type v;
+    v.x = c.x;
+    v.y = c.y;
+    *at_byte<typename VecT<T, 2>::type>(base, idx * (unsigned)sizeof(T)) = v;
+}
+template <typename T>
+__device__ __forceinline__ cx<T> gld(const cx<T>* base, unsigned idx) {
+    return ld2<T>(reinterpret_cast<const T*>(base), 2 * idx);
+}
+template <typename T>
+__device__ __forceinline__ void gst(cx<T>* base, unsigned idx, cx<T> c) {
+    st2<T>(reinterpret_cast<T*>(base), 2 * idx, c);
+}
+__device__ __forceinline__ cx<double> ld2f(const float* base, unsigned idx) {
+    const cx<float> v = ld2<float>(base, idx);
+    return mkc((double)v.x, (double)v.y);
+}
 __device__ __forceinline__ cx<double> ld2f(const float* p) {
     const cx<float> v = gld(reinterpret_cast<const cx<float>*>(p));
     return mkc((double)v.x, (double)v.y);
@@ -297,7 +345,7 @@ __device__ __forceinline__ cx<double> ld2f(const float* p) {
 struct Mask2 {
     double m0, m1;
 };
-__device__ __forceinline__ Mask2 mask2(const SlotDesc& sd, size_t idx) {
+__device__ __forceinline__ Mask2 mask2(const SlotDesc& sd, unsigned idx) {
     if (!sd.mask) return Mask2{1.0, 1.0};
     const auto* m = gbl(sd.mask + idx);
     return Mask2{(double)m[0], (double)m[1]};
@@ -335,6 +383,15 @@ __device__ __forceinline__ double sum_blocks(const double* p, int n, double* sh)
 }
 
 // ==== prologues of the row-forward pass ====================================
+//
+// begin() decides whether the pass runs and fills the scalars (Sc, the same
+// in every thread; Sh: LDS for its reductions).  A pair's input then comes in
+// two steps, fetch (reads only) and combine (arithmetic and stores): a pass
+// fetches all pairs of a thread, up to eight at a time, before it combines
+// them.  In one step each pair's store held up the next pair's reads, which
+// may alias it as far as the compiler knows, and a read behind a store also
+// waits for that store to complete.  PREF: the fetch comes before begin's
+// reductions (FP32).
 
 // fftcg_apply: transform x (FP64 in memory), rounded to T.
 template <typename T>
@@ -342,11 +399,16 @@ struct ProApply {
     static constexpr int NACC = 0;
     static constexpr bool PREF = false;
     struct Sh {};
+    struct Sc {};
     using Gate = GateAlways;
-    static __device__ __forceinline__ bool begin(const SlotDesc&, Sh&, int, int) { return true; }
+    using Raw = cx<double>;
+    static __device__ __forceinline__ bool begin(const SlotDesc&, Sh&, Sc&, int, int) { return true; }
     template <int L>
-    static __device__ __forceinline__ cx<T> load2(const SlotDesc& sd, const Sh&, int row, int col, double*) {
-        cx<double> v = ld2<double>(sd.x + (size_t)row * L + col);
+    static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
+        return ld2<double>(sd.x, (unsigned)row * L + col);
+    }
+    template <int L>
+    static __device__ __forceinline__ cx<T> combine(const SlotDesc&, const Sc&, const Raw& v, int, int, double*) {
         return mkc((T)v.x, (T)v.y);
     }
 };
@@ -361,33 +423,33 @@ struct ProCG {
     static constexpr int NACC = 0;
     struct Sh {
         double red[(NT + 63) / 64];
+    };
+    struct Sc {
         W alpha, beta;
         int restart;
     };
     using Gate = GateIter;
-    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int npart_rr, int stride) {
+    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, Sc& sc, int npart_rr, int stride) {
         if (!GateIter::ok(sd)) return false;
-        SolveState* st = sd.st;
-        const double rr = FOLD ? st->rho_next : sum_partials<NT>(sd.part + PS_RR * stride, npart_rr, sh.red);
-        if (check_due(st, rr)) {
+        auto* st = gbl(sd.st);
+        const CheckIn ci = check_in(st);
+        const double alpha = st->alpha, rho_prev = st->rho_prev, rho_next = st->rho_next;
+        sc.restart = st->restart;
+        const double rr = FOLD ? rho_next : sum_partials<NT>(sd.part + PS_RR * stride, npart_rr, sh.red);
+        if (check_due(ci, rr, ci.iters)) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st->pause = 1;
             return false;
         }
-        const int restart = st->restart;
-        const double beta = restart ? 0.0 : rr / st->rho_prev;
-        sh.alpha = (W)st->alpha;
-        sh.beta = (W)beta;
-        sh.restart = restart;
+        sc.alpha = (W)alpha;
+        sc.beta = (W)(sc.restart ? 0.0 : rr / rho_prev);
         if (blockIdx.x == 0 && threadIdx.x == 0) st->rho_cur = rr;
         return true;
     }
-    // FP32: the pair's r and p are requested before the r.r reduction
-    // (fetch), so that the reduction's latency overlaps them; the arithmetic
-    // (combine) is the same either way.  The pending x update (late) runs
-    // after the transform: its reads then overlap the W writes instead of
-    // lengthening the pass's first, read-only phase (p stays in registers
-    // until then, within the pass's register budget)
     static constexpr bool PREF = sizeof(W) == 4;
+    // The pending x update (late) runs after the transform (FP32): its reads
+    // then overlap the W writes instead of lengthening the pass's first,
+    // read-only phase (p stays in registers until then, within the pass's
+    // register budget)
 #ifndef FFTCG_LATE_X
 #define FFTCG_LATE_X 1
 #endif
@@ -401,67 +463,43 @@ struct ProCG {
     }
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
-        const size_t idx = (size_t)row * L + col;
+        const unsigned idx = (unsigned)row * L + col;
         Raw w;
-        w.r = ld2<W>(reinterpret_cast<const W*>(sd.r) + idx);
-        w.p = ld2<W>(reinterpret_cast<const W*>(sd.p) + idx);
-        if constexpr (!LATE_X) w.x = ld2<XA>(xacc(sd) + idx);
+        w.r = ld2<W>(reinterpret_cast<const W*>(sd.r), idx);
+        w.p = ld2<W>(reinterpret_cast<const W*>(sd.p), idx);
+        if constexpr (!LATE_X) w.x = ld2<XA>(xacc(sd), idx);
         return w;
     }
     template <int L>
-    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sh& sh, const Raw& w, int row,
+    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
                                                     int col, double*) {
-        const size_t idx = (size_t)row * L + col;
-        cx<W> p2;
-        if (sh.restart) {
-            p2 = w.r;
-        } else {
-            const cx<W> po = w.p;
-            p2 = mkc(w.r.x + sh.beta * po.x, w.r.y + sh.beta * po.y);
-            if constexpr (!LATE_X) {
-                if (sh.alpha != W(0)) {
-                    cx<XA> xv = w.x;
-                    xv.x += (XA)sh.alpha * (XA)po.x;
-                    xv.y += (XA)sh.alpha * (XA)po.y;
-                    st2<XA>(xacc(sd) + idx, xv);
-                }
+        const unsigned idx = (unsigned)row * L + col;
+        const cx<W> po = w.p;
+        cx<W> p2 = mkc(w.r.x + sc.beta * po.x, w.r.y + sc.beta * po.y);
+        if (sc.restart) p2 = w.r;
+        if constexpr (!LATE_X) {
+            if (!sc.restart && sc.alpha != W(0)) {
+                cx<XA> xv = w.x;
+                xv.x += (XA)sc.alpha * (XA)po.x;
+                xv.y += (XA)sc.alpha * (XA)po.y;
+                st2<XA>(xacc(sd), idx, xv);
             }
         }
-        st2<W>(reinterpret_cast<W*>(sd.p) + idx, p2);
+        st2<W>(reinterpret_cast<W*>(sd.p), idx, p2);
         return p2;
     }
-    // the pending x update of the pair, after the transform (LATE_X)
+    // the pending x update of a pair, after the transform (LATE_X), in two steps
+    static __device__ __forceinline__ bool late_due(const Sc& sc) { return !sc.restart && sc.alpha != W(0); }
     template <int L>
-    static __device__ __forceinline__ void late(const SlotDesc& sd, const Sh& sh, const Raw& w, int row, int col) {
-        if (sh.restart || sh.alpha == W(0)) return;
-        const size_t idx = (size_t)row * L + col;
-        cx<XA> xv = ld2<XA>(xacc(sd) + idx);
-        xv.x += (XA)sh.alpha * (XA)w.p.x;
-        xv.y += (XA)sh.alpha * (XA)w.p.y;
-        st2<XA>(xacc(sd) + idx, xv);
+    static __device__ __forceinline__ cx<XA> late_fetch(const SlotDesc& sd, int row, int col) {
+        return ld2<XA>(xacc(sd), (unsigned)row * L + col);
     }
     template <int L>
-    static __device__ __forceinline__ cx<W> load2(const SlotDesc& sd, const Sh& sh, int row, int col, double*) {
-        const size_t idx = (size_t)row * L + col;
-        W* p = reinterpret_cast<W*>(sd.p);
-        const W* r = reinterpret_cast<const W*>(sd.r);
-        cx<W> r2 = ld2<W>(r + idx);
-        cx<W> p2;
-        if (sh.restart) {
-            p2 = r2;
-        } else {
-            cx<W> po = ld2<W>(p + idx);
-            p2 = mkc(r2.x + sh.beta * po.x, r2.y + sh.beta * po.y);
-            if (sh.alpha != W(0)) {
-                XA* xa = xacc(sd);
-                cx<XA> xv = ld2<XA>(xa + idx);
-                xv.x += (XA)sh.alpha * (XA)po.x;
-                xv.y += (XA)sh.alpha * (XA)po.y;
-                st2<XA>(xa + idx, xv);
-            }
-        }
-        st2<W>(p + idx, p2);
-        return p2;
+    static __device__ __forceinline__ void late(const SlotDesc& sd, const Sc& sc, const Raw& w, cx<XA> xv, int row,
+                                                int col) {
+        xv.x += (XA)sc.alpha * (XA)w.p.x;
+        xv.y += (XA)sc.alpha * (XA)w.p.y;
+        st2<XA>(xacc(sd), (unsigned)row * L + col, xv);
     }
 };
 
@@ -471,38 +509,47 @@ template <typename W, int NT>
 struct ProCheck {
     static constexpr int NACC = 0;
     static constexpr bool PREF = false;
-    struct Sh {
+    struct Sh {};
+    struct Sc {
         double alpha;
         int mixed;
     };
     using Gate = GateCheck;
-    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int, int) {
+    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh&, Sc& sc, int, int) {
         if (!GateCheck::ok(sd)) return false;
-        sh.alpha = sd.st->alpha;
-        sh.mixed = sd.st->mixed;
+        sc.alpha = gbl(sd.st)->alpha;
+        sc.mixed = gbl(sd.st)->mixed;
         return true;
     }
+    struct Raw {
+        cx<double> x;
+        cx<float> e;
+        cx<W> p;
+    };
+    // (e is an array of every slot, e and p are read whether used or not)
     template <int L>
-    static __device__ __forceinline__ cx<double> load2(const SlotDesc& sd, const Sh& sh, int row, int col,
-                                                       double*) {
-        const size_t idx = (size_t)row * L + col;
-        cx<double> xv = ld2<double>(sd.x + idx);
-        if (sh.mixed) {
-            cx<double> ev = ld2f(sd.e + idx);
-            xv.x += ev.x;
-            xv.y += ev.y;
-            st2<float>(sd.e + idx, mkc(0.0f, 0.0f));
+    static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
+        const unsigned idx = (unsigned)row * L + col;
+        return Raw{ld2<double>(sd.x, idx), ld2<float>(sd.e, idx), ld2<W>(reinterpret_cast<const W*>(sd.p), idx)};
+    }
+    template <int L>
+    static __device__ __forceinline__ cx<double> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
+                                                         int col, double*) {
+        const unsigned idx = (unsigned)row * L + col;
+        cx<double> xv = w.x;
+        if (sc.mixed) {
+            xv.x += (double)w.e.x;
+            xv.y += (double)w.e.y;
+            st2<float>(sd.e, idx, mkc(0.0f, 0.0f));
         }
-        if (sh.alpha != 0.0) {
-            const W* p = reinterpret_cast<const W*>(sd.p);
-            cx<W> pv = ld2<W>(p + idx);
-            xv.x += sh.alpha * (double)pv.x;
-            xv.y += sh.alpha * (double)pv.y;
+        if (sc.alpha != 0.0) {
+            xv.x += sc.alpha * (double)w.p.x;
+            xv.y += sc.alpha * (double)w.p.y;
         }
         const Mask2 mk = mask2(sd, idx);  // broken entries carry no force
         xv.x *= mk.m0;
         xv.y *= mk.m1;
-        st2<double>(sd.x + idx, xv);
+        st2<double>(sd.x, idx, xv);
         return xv;
     }
 };
@@ -515,18 +562,22 @@ struct ProCheck {
 template <typename W, typename XA, int NT, int NPZ, int NG>
 struct ProPCG {
     static constexpr int NACC = 0;
-    // FP32: z, p and the x correction are requested before the reductions
     static constexpr bool PREF = sizeof(W) == 4;
     struct Sh {
         double red[2 * ((NT + 63) / 64)];
         double tot[2];
+    };
+    struct Sc {
         W alpha, beta;
         int restart;
     };
     using Gate = GateIter;
-    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int npart_rr, int stride) {
+    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, Sc& sc, int npart_rr, int stride) {
         if (!GateIter::ok(sd)) return false;
-        SolveState* st = sd.st;
+        auto* st = gbl(sd.st);
+        const CheckIn ci = check_in(st);
+        const double alpha = st->alpha, rho_prev = st->rho_prev;
+        sc.restart = st->restart;
         double rr, rz;
         if constexpr (NG > 0) {
             rr = sum_blocks<NT, NG>(sd.part + PS_RR * stride, npart_rr, sh.red);
@@ -547,15 +598,12 @@ struct ProPCG {
             rr = sum_partials<NT>(sd.part + PS_RR * stride, npart_rr, sh.red);
             rz = sum_partials<NT>(sd.part + PS_RZ * stride, NPZ, sh.red);
         }
-        if (check_due(st, rr)) {
+        if (check_due(ci, rr, ci.iters)) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st->pause = 1;
             return false;
         }
-        const int restart = st->restart;
-        const double beta = restart ? 0.0 : rz / st->rho_prev;
-        sh.alpha = (W)st->alpha;
-        sh.beta = (W)beta;
-        sh.restart = restart;
+        sc.alpha = (W)alpha;
+        sc.beta = (W)(sc.restart ? 0.0 : rz / rho_prev);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st->rho_cur = rz;
             st->need_pre = 0;
@@ -571,54 +619,24 @@ struct ProPCG {
     }
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
-        const size_t idx = (size_t)row * L + col;
-        Raw w;
-        w.z = ld2<W>(reinterpret_cast<const W*>(sd.z) + idx);
-        w.p = ld2<W>(reinterpret_cast<const W*>(sd.p) + idx);
-        w.x = ld2<XA>(xacc(sd) + idx);
-        return w;
+        const unsigned idx = (unsigned)row * L + col;
+        return Raw{ld2<W>(reinterpret_cast<const W*>(sd.z), idx), ld2<W>(reinterpret_cast<const W*>(sd.p), idx),
+                   ld2<XA>(xacc(sd), idx)};
     }
     template <int L>
-    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sh& sh, const Raw& w, int row,
+    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
                                                     int col, double*) {
-        const size_t idx = (size_t)row * L + col;
-        cx<W> p2;
-        if (sh.restart) {
-            p2 = w.z;
-        } else {
-            const cx<W> po = w.p;
-            p2 = mkc(w.z.x + sh.beta * po.x, w.z.y + sh.beta * po.y);
-            if (sh.alpha != W(0)) {
-                cx<XA> xv = w.x;
-                xv.x += (XA)sh.alpha * (XA)po.x;
-                xv.y += (XA)sh.alpha * (XA)po.y;
-                st2<XA>(xacc(sd) + idx, xv);
-            }
+        const unsigned idx = (unsigned)row * L + col;
+        const cx<W> po = w.p;
+        cx<W> p2 = mkc(w.z.x + sc.beta * po.x, w.z.y + sc.beta * po.y);
+        if (sc.restart) p2 = w.z;
+        if (!sc.restart && sc.alpha != W(0)) {
+            cx<XA> xv = w.x;
+            xv.x += (XA)sc.alpha * (XA)po.x;
+            xv.y += (XA)sc.alpha * (XA)po.y;
+            st2<XA>(xacc(sd), idx, xv);
         }
-        st2<W>(reinterpret_cast<W*>(sd.p) + idx, p2);
-        return p2;
-    }
-    template <int L>
-    static __device__ __forceinline__ cx<W> load2(const SlotDesc& sd, const Sh& sh, int row, int col, double*) {
-        const size_t idx = (size_t)row * L + col;
-        W* p = reinterpret_cast<W*>(sd.p);
-        const W* z = reinterpret_cast<const W*>(sd.z);
-        cx<W> z2 = ld2<W>(z + idx);
-        cx<W> p2;
-        if (sh.restart) {
-            p2 = z2;
-        } else {
-            cx<W> po = ld2<W>(p + idx);
-            p2 = mkc(z2.x + sh.beta * po.x, z2.y + sh.beta * po.y);
-            if (sh.alpha != W(0)) {
-                XA* xa = reinterpret_cast<XA*>(sizeof(XA) == 8 ? (void*)sd.x : (void*)sd.e);
-                cx<XA> xv = ld2<XA>(xa + idx);
-                xv.x += (XA)sh.alpha * (XA)po.x;
-                xv.y += (XA)sh.alpha * (XA)po.y;
-                st2<XA>(xa + idx, xv);
-            }
-        }
-        st2<W>(p + idx, p2);
+        st2<W>(reinterpret_cast<W*>(sd.p), idx, p2);
         return p2;
     }
 };
@@ -630,18 +648,20 @@ struct ProPCG {
 template <typename W, int NT, int NPQ, int NG>
 struct ProUpdPre {
     static constexpr int NACC = 1;
-    static constexpr bool PREF = sizeof(W) == 4;  // r and q requested before the p.q reduction
+    static constexpr bool PREF = sizeof(W) == 4;
     static constexpr int SET = PS_RR;
     struct Sh {
         double red[(NT + 63) / 64];
+    };
+    struct Sc {
         W alpha;
     };
     using Gate = GateIter;
-    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, int, int stride) {
+    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh& sh, Sc& sc, int, int stride) {
         if (!GateIter::ok(sd)) return false;
-        SolveState* st = sd.st;
-        const double pq = sum_blocks<NT, NG>(sd.part + PS_PQ * stride, NPQ, sh.red);
+        auto* st = gbl(sd.st);
         const double rho = st->rho_cur;
+        const double pq = sum_blocks<NT, NG>(sd.part + PS_PQ * stride, NPQ, sh.red);
         if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 st->status = ST_EBREAKDOWN;
@@ -657,35 +677,23 @@ struct ProUpdPre {
             st->iters += 1;
             st->restart = 0;
         }
-        sh.alpha = (W)alpha;
+        sc.alpha = (W)alpha;
         return true;
-    }
-    template <int L>
-    static __device__ __forceinline__ cx<W> load2(const SlotDesc& sd, const Sh& sh, int row, int col,
-                                                  double* acc) {
-        const size_t idx = (size_t)row * L + col;
-        W* r = reinterpret_cast<W*>(sd.r);
-        const W* q = reinterpret_cast<const W*>(sd.q);
-        const cx<W> r2 = ld2<W>(r + idx), q2 = ld2<W>(q + idx);
-        const cx<W> rn = mkc(r2.x - sh.alpha * q2.x, r2.y - sh.alpha * q2.y);
-        st2<W>(r + idx, rn);
-        acc[0] += (double)rn.x * (double)rn.x + (double)rn.y * (double)rn.y;
-        return rn;
     }
     struct Raw {
         cx<W> r, q;
     };
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
-        const size_t idx = (size_t)row * L + col;
-        return Raw{ld2<W>(reinterpret_cast<const W*>(sd.r) + idx), ld2<W>(reinterpret_cast<const W*>(sd.q) + idx)};
+        const unsigned idx = (unsigned)row * L + col;
+        return Raw{ld2<W>(reinterpret_cast<const W*>(sd.r), idx), ld2<W>(reinterpret_cast<const W*>(sd.q), idx)};
     }
     template <int L>
-    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sh& sh, const Raw& w, int row,
+    static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
                                                     int col, double* acc) {
-        const size_t idx = (size_t)row * L + col;
-        const cx<W> rn = mkc(w.r.x - sh.alpha * w.q.x, w.r.y - sh.alpha * w.q.y);
-        st2<W>(reinterpret_cast<W*>(sd.r) + idx, rn);
+        const unsigned idx = (unsigned)row * L + col;
+        const cx<W> rn = mkc(w.r.x - sc.alpha * w.q.x, w.r.y - sc.alpha * w.q.y);
+        st2<W>(reinterpret_cast<W*>(sd.r), idx, rn);
         acc[0] += (double)rn.x * (double)rn.x + (double)rn.y * (double)rn.y;
         return rn;
     }
@@ -698,15 +706,25 @@ struct ProPre {
     static constexpr int NACC = 0;
     static constexpr bool PREF = false;
     struct Sh {};
+    struct Sc {};
     using Gate = GatePre;
-    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh&, int, int) { return GatePre::ok(sd); }
+    using Raw = cx<W>;
+    static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh&, Sc&, int, int) { return GatePre::ok(sd); }
     template <int L>
-    static __device__ __forceinline__ cx<W> load2(const SlotDesc& sd, const Sh&, int row, int col, double*) {
-        return ld2<W>(reinterpret_cast<const W*>(sd.r) + (size_t)row * L + col);
+    static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
+        return ld2<W>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col);
+    }
+    template <int L>
+    static __device__ __forceinline__ cx<W> combine(const SlotDesc&, const Sc&, const Raw& w, int, int, double*) {
+        return w;
     }
 };
 
 // ==== epilogues of the row-inverse pass ====================================
+
+// As the prologues, in two steps: pre (a pair's operands) and out2p.  PREF:
+// the operands are requested with the spectrum, before the transform (FP32);
+// otherwise after it, up to eight pairs together.
 
 // fftcg_apply: y = d * x (FP64) + C x.
 template <typename T>
@@ -715,14 +733,20 @@ struct EpiApply {
     static constexpr bool PREF = false;
     using Gate = GateAlways;
     static __device__ __forceinline__ bool begin(const SlotDesc&) { return true; }
+    struct Pre {
+        cx<double> d, x;
+    };
     template <int L>
-    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, T c0, T c1, double*) {
-        const size_t idx = (size_t)row * L + col;
-        cx<double> dv = ld2<double>(sd.d + idx);
-        cx<double> xv = ld2<double>(sd.x + idx);
-        st2<double>(sd.y + idx, mkc(dv.x * xv.x + (double)c0, dv.y * xv.y + (double)c1));
+    static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
+        const unsigned idx = (unsigned)row * L + col;
+        return Pre{ld2<double>(sd.d, idx), ld2<double>(sd.x, idx)};
     }
-    static __device__ __forceinline__ void finish(const SlotDesc&, const double*, int) {}
+    template <int L>
+    static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, T c0, T c1, const Pre& pr,
+                                                 double*) {
+        st2<double>(sd.y, (unsigned)row * L + col,
+                    mkc(pr.d.x * pr.x.x + (double)c0, pr.d.y * pr.x.y + (double)c1));
+    }
 };
 
 // CG iteration: q = d p + C p; partial p . q (FP64 accumulation).
@@ -741,24 +765,20 @@ struct EpiCG {
     };
     template <int L>
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
-        const size_t idx = (size_t)row * L + col;
+        const unsigned idx = (unsigned)row * L + col;
         Pre v;
-        v.p = ld2<W>(reinterpret_cast<const W*>(sd.p) + idx);
+        v.p = ld2<W>(reinterpret_cast<const W*>(sd.p), idx);
         if constexpr (sizeof(W) == 4) {
-            v.d = ld2<float>(sd.d32 + idx);
+            v.d = ld2<float>(sd.d32, idx);
         } else {
-            v.d = ld2<double>(sd.d + idx);
+            v.d = ld2<double>(sd.d, idx);
         }
         return v;
     }
     template <int L>
-    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, W c0, W c1, double* acc) {
-        out2p<L>(sd, row, col, c0, c1, pre<L>(sd, row, col), acc);
-    }
-    template <int L>
     static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, W c0, W c1, const Pre& pr,
                                                  double* acc) {
-        const size_t idx = (size_t)row * L + col;
+        const unsigned idx = (unsigned)row * L + col;
         W* q = reinterpret_cast<W*>(sd.q);
         const cx<W> pv = pr.p, dv = pr.d;
         cx<W> qv = mkc(dv.x * pv.x + c0, dv.y * pv.y + c1);
@@ -766,7 +786,7 @@ struct EpiCG {
             const Mask2 mk = mask2(sd, idx);
             qv = mkc(qv.x * (W)mk.m0, qv.y * (W)mk.m1);
         }
-        st2<W>(q + idx, qv);
+        st2<W>(q, idx, qv);
         acc[0] += (double)pv.x * (double)qv.x + (double)pv.y * (double)qv.y;
     }
     // q of a pair without storing it (the grid-synchronised update below)
@@ -776,7 +796,7 @@ struct EpiCG {
         const cx<W> pv = pr.p, dv = pr.d;
         cx<W> qv = mkc(dv.x * pv.x + c0, dv.y * pv.y + c1);
         if (sd.mask) {
-            const Mask2 mk = mask2(sd, (size_t)row * L + col);
+            const Mask2 mk = mask2(sd, (unsigned)row * L + col);
             qv = mkc(qv.x * (W)mk.m0, qv.y * (W)mk.m1);
         }
         acc[0] += (double)pv.x * (double)qv.x + (double)pv.y * (double)qv.y;
@@ -876,11 +896,11 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
     auto* flags = reinterpret_cast<unsigned long long*>(part + PS_BAR * stride);
     auto* rel = reinterpret_cast<unsigned long long*>(part + PS_BARREL * stride);
     auto put = [](unsigned long long* p, double v) {
-        (void)__hip_atomic_exchange(p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+        (void)__hip_atomic_exchange(gbl(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
                                     __HIP_MEMORY_SCOPE_AGENT);
     };
     auto get = [](const unsigned long long* p) {
-        return __builtin_bit_cast(double, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        return __builtin_bit_cast(double, __hip_atomic_load(gbl(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
     auto setp = [&](int a) {  // partials of set a (a small: no table in memory)
         const int ps = a == 0 ? sets[0] : (a == 1 ? sets[1] : (a == 2 ? sets[2] : sets[3]));
@@ -890,14 +910,14 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
     __syncthreads();
     for (int a = tid; a < N; a += NT) put(setp(a) + blockIdx.x, s_tot[a]);
     __builtin_amdgcn_s_waitcnt(0);  // the first wave's exchanges are complete
-    if (tid == 0) __hip_atomic_store(flags + blockIdx.x, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(gbl(flags + blockIdx.x), token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
     int ok = 1;
     if (blockIdx.x == 0) {
         for (;;) {
             int here = 1;
             for (unsigned int i = tid; i < nb; i += NT)
-                here &= __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
+                here &= __hip_atomic_load(gbl(flags + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
             const int expired = (long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit;
             // both decisions are taken by the whole workgroup
             if (__syncthreads_and(here)) break;
@@ -928,12 +948,12 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
             __syncthreads();
             for (int a = tid; a < N; a += NT) put(rel + 1 + a, s_tot[a]);
             __builtin_amdgcn_s_waitcnt(0);
-            if (tid == 0) __hip_atomic_store(rel, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) __hip_atomic_store(gbl(rel), token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
     } else {
         if (tid < cmin(N, NT)) {
-            while (__hip_atomic_load(rel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != token) {
+            while (__hip_atomic_load(gbl(rel), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != token) {
                 if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit) {
                     ok = 0;
                     break;
@@ -980,15 +1000,24 @@ struct EpiCheck {
         acc[7] += dv.x + dv.y;
         return mkc(w0, w1);
     }
+    struct Pre {
+        cx<double> x, b, d;
+        cx<W> r;
+        int checked;
+    };
     template <int L>
-    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, double c0, double c1,
-                                                double* acc) {
-        const size_t idx = (size_t)row * L + col;
-        const cx<double> xv = ld2<double>(sd.x + idx), bv = ld2<double>(sd.b + idx), dv = ld2<double>(sd.d + idx);
-        W* rp = reinterpret_cast<W*>(sd.r) + idx;
-        const bool checked = sd.st->checks > 0;  // the first check has no recursive residual yet
-        const cx<W> ro = checked ? ld2<W>(rp) : mkc(W(0), W(0));
-        st2<W>(rp, pair(xv, bv, dv, mask2(sd, idx), c0, c1, checked, ro, acc));
+    static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
+        const unsigned idx = (unsigned)row * L + col;
+        return Pre{ld2<double>(sd.x, idx), ld2<double>(sd.b, idx), ld2<double>(sd.d, idx),
+                   ld2<W>(reinterpret_cast<const W*>(sd.r), idx),
+                   *gbl(&sd.st->checks)};  // 0: the first check has no recursive residual yet
+    }
+    template <int L>
+    static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, double c0, double c1,
+                                                 const Pre& pr, double* acc) {
+        const unsigned idx = (unsigned)row * L + col;
+        st2<W>(reinterpret_cast<W*>(sd.r), idx,
+               pair(pr.x, pr.b, pr.d, mask2(sd, idx), c0, c1, pr.checked > 0, pr.r, acc));
     }
 };
 
@@ -1006,23 +1035,19 @@ struct EpiPre {
     };
     template <int L>
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
-        return Pre{ld2<W>(reinterpret_cast<const W*>(sd.r) + (size_t)row * L + col)};
-    }
-    template <int L>
-    static __device__ __forceinline__ void out2(const SlotDesc& sd, int row, int col, W c0, W c1, double* acc) {
-        out2p<L>(sd, row, col, c0, c1, pre<L>(sd, row, col), acc);
+        return Pre{ld2<W>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col)};
     }
     template <int L>
     static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, W c0, W c1, const Pre& pr,
                                                  double* acc) {
-        const size_t idx = (size_t)row * L + col;
+        const unsigned idx = (unsigned)row * L + col;
         const cx<W> rv = pr.r;
         if (sd.mask) {
             const Mask2 mk = mask2(sd, idx);
             c0 *= (W)mk.m0;
             c1 *= (W)mk.m1;
         }
-        st2<W>(reinterpret_cast<W*>(sd.z) + idx, mkc(c0, c1));
+        st2<W>(reinterpret_cast<W*>(sd.z), idx, mkc(c0, c1));
         acc[0] += (double)rv.x * (double)c0 + (double)rv.y * (double)c1;
     }
 };
@@ -1043,26 +1068,6 @@ struct ProLate<P, decltype((void)P::LATE_X)> {
     static constexpr bool value = P::LATE_X;
 };
 
-// A prologue's fetched operands kept for its late part (int otherwise).
-template <class P, bool = ProLate<P>::value>
-struct LateRaw {
-    using type = int;
-};
-template <class P>
-struct LateRaw<P, true> {
-    using type = typename P::Raw;
-};
-
-// Prefetched epilogue operands of an epilogue with PREF (its Pre type).
-template <class Epi, bool = Epi::PREF>
-struct EpiPreT {
-    using type = int;
-};
-template <class Epi>
-struct EpiPreT<Epi, true> {
-    using type = typename Epi::Pre;
-};
-
 // ==== kernels ==============================================================
 
 // The forward row transform of the thread's inputs v (the row's packed
@@ -1080,6 +1085,15 @@ __device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& 
     constexpr int NSTG = fft_nstages(N);
     fft_run<T, N, M, -1, false, PAD != 0>(v, lay, j, tab.tw);
     constexpr int RL = NSTG > 0 ? fft_radix(N, false, NSTG - 1) : 1;
+    // the unpack's twiddles, all of them before the first W store: a read
+    // behind a store waits for the store to complete, and sixteen such round
+    // trips in a row had been a third of the pass
+    cx<T> twk[E];
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+        const int qi = tid + s * NT;
+        twk[s] = gld(tab.tw, (unsigned)((qi / (TT * RPW)) * TT + qi % TT));
+    }
     if constexpr (NSTG > 1) __syncthreads();  // the transform's last reads before these writes
 #pragma unroll
     for (int u = 0; u < E / RL; ++u) lay.template st_run<RL, N / RL>(j + u * P, v + u * RL);
@@ -1093,17 +1107,13 @@ __device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& 
         const int kt = qi / (TT * RPW);
         const int k = kt * TT + kk;
         LdsLay<T, 1, 4, 1> rl2{lds + il * WORDS, 0};
-        const cx<T> Zk = rl2.ld(k);
-        cx<T> out;
-        if (k == 0) {
-            out = mkc(Zk.x + Zk.y, Zk.x - Zk.y);
-        } else {
-            const cx<T> B = conjc(rl2.ld(N - k));
-            const cx<T> s1 = Zk + B, d1 = Zk - B;
-            const cx<T> wd = cmul(tab.tw[k], d1);
-            out = mkc(T(0.5) * (s1.x + wd.y), T(0.5) * (s1.y - wd.x));
-        }
-        gst(Wb + ((size_t)kt * L + rb * RPW + il) * TT + kk, out);
+        const cx<T> Zk = rl2.ld(k), B = conjc(rl2.ld(N - k));
+        const cx<T> s1 = Zk + B, d1 = Zk - B;
+        const cx<T> wd = cmul(twk[s], d1);
+        cx<T> out = mkc(T(0.5) * (s1.x + wd.y), T(0.5) * (s1.y - wd.x));
+        // (k = 0 is among the first tiles: s = 0 alone, without a branch)
+        if ((s == 0 || NT < TT * RPW) && k == 0) out = mkc(Zk.x + Zk.y, Zk.x - Zk.y);
+        gst(Wb, ((unsigned)kt * L + rb * RPW + il) * TT + kk, out);
     }
 }
 
@@ -1126,43 +1136,48 @@ __global__ void __launch_bounds__(NT) k_row_fwd(Tab<T> tab, Slot slot, int npart
     constexpr int NSTG = fft_nstages(N);
     constexpr int R1 = NSTG > 0 ? fft_radix(N, false, 0) : 1;
     constexpr int RK = PAD ? R1 / 2 : R1;  // inputs per run (the rest are known zeros on the padded grid)
-    constexpr bool LATE = ProLate<Pro>::value;
-    typename LateRaw<Pro>::type late_raw[LATE ? (E / R1) * RK : 1];
-    if constexpr (Pro::PREF && (E / R1) * RK <= 8) {
-        // the inputs are requested before begin()'s reductions
+    constexpr int NI = (E / R1) * RK, GRP = cmin(NI, 8);  // a thread's inputs, fetched up to eight at a time
+    auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / R1)); };
+    constexpr bool LATE = ProLate<Pro>::value && NI <= 8;
+    static_assert(!ProLate<Pro>::value || Pro::PREF, "a late part needs the fetched operands");
+    typename Pro::Raw raw[GRP];
+    typename Pro::Sc sc;
+    if constexpr (Pro::PREF) {
+        // the (first) inputs are requested before begin()'s reductions
         if (!Pro::Gate::ok(sd)) return;
-        typename Pro::Raw raw[(E / R1) * RK];
 #pragma unroll
-        for (int u = 0; u < E / R1; ++u)
+        for (int i = 0; i < GRP; ++i) raw[i] = Pro::template fetch<L>(sd, row, col(i));
+    }
+    if (!Pro::begin(sd, sh, sc, npart_rr, stride)) return;
 #pragma unroll
-            for (int r = 0; r < RK; ++r)
-                raw[u * RK + r] = Pro::template fetch<L>(sd, row, 2 * ((j + u * P) + r * (N / R1)));
-        if (!Pro::begin(sd, sh, npart_rr, stride)) return;
+    for (int g = 0; g < NI; g += GRP) {
+        if (!Pro::PREF || g > 0) {
 #pragma unroll
-        for (int u = 0; u < E / R1; ++u)
-#pragma unroll
-            for (int r = 0; r < RK; ++r)
-                v[u * R1 + r] = Pro::template combine<L>(sd, sh, raw[u * RK + r], row,
-                                                         2 * ((j + u * P) + r * (N / R1)), &acc);
-        if constexpr (LATE) {
-#pragma unroll
-            for (int i = 0; i < (E / R1) * RK; ++i) late_raw[i] = raw[i];
+            for (int i = 0; i < GRP; ++i) raw[i] = Pro::template fetch<L>(sd, row, col(g + i));
         }
-    } else {
-        if (!Pro::begin(sd, sh, npart_rr, stride)) return;
 #pragma unroll
-        for (int u = 0; u < E / R1; ++u)
+        for (int i = 0; i < GRP; ++i)
+            v[((g + i) / RK) * R1 + (g + i) % RK] = Pro::template combine<L>(sd, sc, raw[i], row, col(g + i), &acc);
+        if constexpr (ProLate<Pro>::value && !LATE) {
+            // more pairs than a group: their late part cannot keep its operands
+            if (Pro::late_due(sc)) {
+                decltype(Pro::template late_fetch<L>(sd, 0, 0)) xv[GRP];
 #pragma unroll
-            for (int r = 0; r < RK; ++r)
-                v[u * R1 + r] = Pro::template load2<L>(sd, sh, row, 2 * ((j + u * P) + r * (N / R1)), &acc);
+                for (int i = 0; i < GRP; ++i) xv[i] = Pro::template late_fetch<L>(sd, row, col(g + i));
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) Pro::template late<L>(sd, sc, raw[i], xv[i], row, col(g + i));
+            }
+        }
     }
     row_fwd_out<T, M, PAD, NT>(v, lds, tab, sd, rb, tid);
-    if constexpr (LATE && Pro::PREF && (E / R1) * RK <= 8) {
+    if constexpr (LATE) {
+        if (Pro::late_due(sc)) {
+            decltype(Pro::template late_fetch<L>(sd, 0, 0)) xv[GRP];
 #pragma unroll
-        for (int u = 0; u < E / R1; ++u)
+            for (int i = 0; i < GRP; ++i) xv[i] = Pro::template late_fetch<L>(sd, row, col(i));
 #pragma unroll
-            for (int r = 0; r < RK; ++r)
-                Pro::template late<L>(sd, sh, late_raw[u * RK + r], row, 2 * ((j + u * P) + r * (N / R1)));
+            for (int i = 0; i < GRP; ++i) Pro::template late<L>(sd, sc, raw[i], xv[i], row, col(i));
+        }
     }
     if constexpr (Pro::NACC > 0) {
         const double s = block_sum<NT>(acc, fred);
@@ -1225,7 +1240,7 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
             const int mp = m <= M - m ? m : M - m;
             gpre[u * RL + r] = g[mp * TT + kk];
         }
-    const T c2 = PRE ? (T)((double)M * (double)M * sd.st->dbar) : T(0);
+    const T c2 = PRE ? (T)((double)M * (double)M * gbl(sd.st)->dbar) : T(0);
     const T c4 = (T)((double)M * (double)M * (double)M * (double)M);
     if constexpr (PRE) {
 #pragma unroll
@@ -1289,8 +1304,8 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
 
 // What follows the row-inverse transform in the preconditioned turns (v: its
 // outputs; pre: prefetched operands, or not where they are read here).
-template <typename T, int M, int PAD, class Epi, int NT, int TURN, class PreA>
-__device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, double* red, const Tab<T>& tab,
+template <typename T, int M, int PAD, class Epi, int NT, int TURN, bool HAVE>
+__device__ __forceinline__ void turn_pcg(cx<T>* v, typename Epi::Pre* pre, cx<T>* lds, double* red, const Tab<T>& tab,
                                          const SlotDesc& sd, int stride, unsigned long long token, int row0) {
     using G = Geo<T, M, PAD>;
     constexpr int N = G::N, E = G::ER, P = G::PR, RPW = G::RPW, L = G::L;
@@ -1299,9 +1314,9 @@ __device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, 
     static_assert(R1 == RL, "forward first radix and inverse last radix");
     constexpr int RK = (PAD && RL > 1) ? RL / 2 : RL, NO = (E / RL) * RK;
     const int tid = threadIdx.x, rl = tid / P, j = tid % P, row = row0 + rl;
-    SolveState* st = sd.st;
+    auto* st = gbl(sd.st);
     auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
-    auto at = [&](const void* p, int i) { return (T*)p + (size_t)row * L + col(i); };
+    auto at = [&](int i) { return (unsigned)row * L + col(i); };
     auto give_up = [&]() {
         if (tid == 0) {
             __hip_atomic_store(&st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1309,40 +1324,61 @@ __device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, 
             publish_status(sd, 1, ST_EGRID, st->gen, st->iters, st->last_check_iter);
         }
     };
-    constexpr bool HAVE = std::extent<std::remove_reference_t<PreA>>::value == NO;
+    // what the second half takes from the state, read before the barrier
+    // (one thread; LDS): iters, alpha and rho_prev change in the other turn
+    // only, the rest in no turn
+    __shared__ CheckIn s_ci;
+    __shared__ double s_in[3];
+    if (tid == 0) {
+        if constexpr (TURN == 2) s_ci = check_in(st);
+        s_in[0] = st->alpha;
+        s_in[1] = st->rho_prev;
+        s_in[2] = st->rho_cur;
+    }
     cx<T> w[NO];  // q, then the new r (TURN 1); z, then the new p (TURN 2)
     double acc[2] = {0.0, 0.0}, tot[2];
 #pragma unroll
-    for (int i = 0; i < NO; ++i) {
-        const cx<T> c = v[(i / RK) * RL + i % RK];
-        typename Epi::Pre pr;
-        if constexpr (HAVE)
-            pr = pre[i];
-        else
-            pr = Epi::template pre<L>(sd, row, col(i));
-        if constexpr (TURN == 1) {
-            w[i] = Epi::template outq<L>(sd, row, col(i), c.x, c.y, pr, acc);
-        } else {
-            w[i] = c;
-            if (sd.mask) {
-                const Mask2 mk = mask2(sd, (size_t)row * L + col(i));
-                w[i] = mkc(c.x * (T)mk.m0, c.y * (T)mk.m1);
+    for (int g = 0; g < NO; g += cmin(NO, 8)) {
+        if constexpr (!HAVE) {
+#pragma unroll
+            for (int i = 0; i < cmin(NO, 8); ++i) pre[i] = Epi::template pre<L>(sd, row, col(g + i));
+        }
+#pragma unroll
+        for (int h = 0; h < cmin(NO, 8); ++h) {
+            const int i = g + h;
+            const cx<T> c = v[(i / RK) * RL + i % RK];
+            const typename Epi::Pre pr = pre[HAVE ? i : h];
+            if constexpr (TURN == 1) {
+                w[i] = Epi::template outq<L>(sd, row, col(i), c.x, c.y, pr, acc);
+            } else {
+                w[i] = c;
+                if (sd.mask) {
+                    const Mask2 mk = mask2(sd, (unsigned)row * L + col(i));
+                    w[i] = mkc(c.x * (T)mk.m0, c.y * (T)mk.m1);
+                }
+                acc[0] += (double)pr.r.x * (double)w[i].x + (double)pr.r.y * (double)w[i].y;
+                acc[1] += (double)pr.r.x * (double)pr.r.x + (double)pr.r.y * (double)pr.r.y;
             }
-            acc[0] += (double)pr.r.x * (double)w[i].x + (double)pr.r.y * (double)w[i].y;
-            acc[1] += (double)pr.r.x * (double)pr.r.x + (double)pr.r.y * (double)pr.r.y;
         }
     }
     // the operands that the second half changes, requested before the barrier
     cx<T> o[NO];
 #pragma unroll
-    for (int i = 0; i < NO; ++i) o[i] = ld2<T>(at(TURN == 1 ? sd.r : sd.p, i));
+    for (int i = 0; i < NO; ++i) o[i] = ld2<T>((const T*)(TURN == 1 ? sd.r : sd.p), at(i));
+    // (the second turn's x accumulator as well)
+    T* xa = sizeof(T) == 8 ? (T*)sd.x : (T*)sd.e;
+    cx<T> xv[TURN == 2 ? NO : 1];
+    if constexpr (TURN == 2) {
+#pragma unroll
+        for (int i = 0; i < NO; ++i) xv[i] = ld2<T>(xa, at(i));
+    }
     if (!grid_sums<NT, TURN, G::SUM_GROUPS>(acc, sd.part, stride, token, st->bar_limit, red, tot)) {
         give_up();
         return;
     }
     cx<T> v2[E];
     if constexpr (TURN == 1) {
-        const double pq = tot[0], rho = st->rho_cur;
+        const double pq = tot[0], rho = s_in[2];
         if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
             if (blockIdx.x == 0 && tid == 0) {
                 st->status = ST_EBREAKDOWN;
@@ -1357,7 +1393,7 @@ __device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, 
         for (int i = 0; i < NO; ++i) {
             o[i].x -= a * w[i].x;
             o[i].y -= a * w[i].y;
-            st2<T>(at(sd.r, i), o[i]);
+            st2<T>((T*)sd.r, at(i), o[i]);
             v2[(i / RK) * RL + i % RK] = o[i];
         }
         if (blockIdx.x == 0 && tid == 0) {
@@ -1375,29 +1411,26 @@ __device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, 
             __builtin_amdgcn_sched_barrier(0);
         }
         const double s = block_sum<NT>(rr, red);
-        if (tid == 0) sd.part[PS_RR * stride + blockIdx.x] = s;
+        if (tid == 0) gbl(sd.part)[PS_RR * stride + blockIdx.x] = s;
     } else {
         const double rz = tot[0], rr = tot[1];
-        if (check_due(st, rr)) {
+        if (check_due(s_ci, rr, s_ci.iters)) {
             if (blockIdx.x == 0 && tid == 0) st->pause = 1;
             return;
         }
         // (an iteration always precedes, so this is no restart)
-        const T a = (T)st->alpha, beta = (T)(rz / st->rho_prev);
+        const T a = (T)s_in[0], beta = (T)(rz / s_in[1]);
+#pragma unroll
+        for (int i = 0; i < NO; ++i) asm volatile("" : "+v"(xv[i].x), "+v"(xv[i].y));
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
             const cx<T> p2 = mkc(w[i].x + beta * o[i].x, w[i].y + beta * o[i].y);
-            st2<T>(at(sd.p, i), p2);
+            st2<T>((T*)sd.p, at(i), p2);
             v2[(i / RK) * RL + i % RK] = p2;
-        }
-        if (a != T(0)) {
-            const void* xa = sizeof(T) == 8 ? (const void*)sd.x : (const void*)sd.e;
-#pragma unroll
-            for (int i = 0; i < NO; ++i) {
-                cx<T> xv = ld2<T>(at(xa, i));
-                xv.x += a * o[i].x;
-                xv.y += a * o[i].y;
-                st2<T>(at(xa, i), xv);
+            if (a != T(0)) {
+                xv[i].x += a * o[i].x;
+                xv[i].y += a * o[i].y;
+                st2<T>(xa, at(i), xv[i]);
             }
         }
         if (blockIdx.x == 0 && tid == 0) {
@@ -1410,6 +1443,7 @@ __device__ __forceinline__ void turn_pcg(cx<T>* v, const PreA& pre, cx<T>* lds, 
     asm volatile("" : "+s"(tab2.tw));
     int tid2 = tid;
     asm volatile("" : "+v"(tid2));
+    tid2 &= NT - 1;
     row_fwd_out<T, M, PAD, NT>(v2, lds, tab2, sd, __builtin_amdgcn_readfirstlane(row0 / RPW), tid2);
 }
 
@@ -1431,10 +1465,11 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     const int tid = threadIdx.x;
     const int rl = tid / P, j = tid % P;
     const int row0 = xcd_remap(blockIdx.x, gridDim.x) * RPW;
-    // FWD: the iteration count as this launch found it (block 0 advances
-    // st->iters after the first barrier; read before this workgroup arrives)
-    __shared__ int s_iters;
-    if (FWD && tid == 0) s_iters = sd.st->iters;
+    // FWD: the state that the check decision takes, as this launch found it
+    // (block 0 advances st->iters after the first barrier; read before this
+    // workgroup arrives)
+    __shared__ CheckIn s_ci;
+    if (FWD && EpiTurn<Epi>::value == 0 && tid == 0) s_ci = check_in(gbl(sd.st));
     const cx<T>* Wb = reinterpret_cast<const cx<T>*>(sd.W);
     // all of this thread's spectrum values are requested before the first
     // is stored to LDS (more reads in flight per wave)
@@ -1445,7 +1480,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
         const int kk = qi % TT;
         const int il = (qi / TT) % RPW;
         const int kt = qi / (TT * RPW);
-        wv[s] = gld(Wb + ((size_t)kt * L + row0 + il) * TT + kk);
+        wv[s] = gld(Wb, ((unsigned)kt * L + row0 + il) * TT + kk);
     }
     constexpr int NSTG = fft_nstages(N);
     constexpr int R1 = NSTG > 0 ? fft_radix(N, true, 0) : 1;
@@ -1455,7 +1490,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
 #pragma unroll
     for (int u = 0; u < E / R1; ++u)
 #pragma unroll
-        for (int r = 0; r < R1; ++r) twk[u * R1 + r] = gld(tab.tw + (j + u * P) + r * S1);
+        for (int r = 0; r < R1; ++r) twk[u * R1 + r] = gld(tab.tw, (unsigned)((j + u * P) + r * S1));
     constexpr int RL = NSTG > 0 ? fft_radix(N, true, NSTG - 1) : 1;
     constexpr int RK = (PAD && RL > 1) ? RL / 2 : RL;  // outputs kept per run (the rest are cropped)
     const int row = row0 + rl;
@@ -1463,15 +1498,16 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     // in the turn pass (FWD) on the largest rows (16 pairs a thread), which
     // keeps p of the pairs to its end and would otherwise exceed 128 VGPRs
     // (four workgroups per CU)
+    constexpr int NO = (E / RL) * RK;  // outputs (pairs) of this thread
     constexpr bool PF = Epi::PREF && !(FWD && E >= 16);
-    using PreT = typename EpiPreT<Epi>::type;
-    PreT pre[PF ? (E / RL) * RK : 1];
+    auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
+    // (without the prefetch in groups of up to eight pairs; the check's pairs
+    // take 56 bytes, four fit the registers)
+    constexpr int GRP = cmin(NO, sizeof(typename Epi::Pre) > 40 ? 4 : 8);
+    typename Epi::Pre pre[PF ? NO : GRP];
     if constexpr (PF) {
 #pragma unroll
-        for (int u = 0; u < E / RL; ++u)
-#pragma unroll
-            for (int r = 0; r < RK; ++r)
-                pre[u * RK + r] = Epi::template pre<L>(sd, row, 2 * ((j + u * P) + r * (N / RL)));
+        for (int i = 0; i < NO; ++i) pre[i] = Epi::template pre<L>(sd, row, col(i));
     }
 #pragma unroll
     for (int s = 0; s < E; ++s) {
@@ -1487,26 +1523,22 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     cx<T> v[E];
 #pragma unroll
     for (int u = 0; u < E / R1; ++u) {
-        // Y at k = jj + r S1, and the partners N - k = (S1 - jj) + (R1-1-r) S1
-        // (jj > 0) or (R1 - r) S1 (jj == 0), read as two runs
+        // Y at k = jj + r S1, and the partners N - k = (S1 - jj) + (R1-1-r) S1,
+        // read as two runs (k = 0 has no partner: position N is the row's
+        // last word of padding, read and not used)
         const int jj = j + u * P;
         cx<T> A[R1], Bv[R1];
         lay.template ld_run<R1, S1>(jj, A);
-        lay.template ld_run<R1, S1>(jj == 0 ? 0 : S1 - jj, Bv);
+        lay.template ld_run<R1, S1>(S1 - jj, Bv);
 #pragma unroll
         for (int r = 0; r < R1; ++r) {
-            const int k = jj + r * S1;
             const cx<T> Y = A[r];
-            cx<T> Z;
-            if (k == 0) {
-                Z = mkc(Y.x + Y.y, Y.x - Y.y);
-            } else {
-                const cx<T> B = conjc(jj == 0 ? Bv[(R1 - r) % R1] : Bv[R1 - 1 - r]);
-                const cx<T> s1 = Y + B, d1 = Y - B;
-                const cx<T> wd = cmul(conjc(twk[u * R1 + r]), d1);
-                Z = mkc(s1.x - wd.y, s1.y + wd.x);
-            }
-            v[u * R1 + r] = Z;
+            const cx<T> B = conjc(Bv[R1 - 1 - r]);
+            const cx<T> s1 = Y + B, d1 = Y - B;
+            const cx<T> wd = cmul(conjc(twk[u * R1 + r]), d1);
+            v[u * R1 + r] = mkc(s1.x - wd.y, s1.y + wd.x);
+            // k = jj + r S1 = 0: u = r = 0 alone
+            if (u == 0 && r == 0 && jj == 0) v[0] = mkc(Y.x + Y.y, Y.x - Y.y);
         }
     }
     __syncthreads();
@@ -1517,41 +1549,38 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     if constexpr (Epi::NACC > 4) acc[4] = 1.0e300;
     constexpr bool UPD = EpiUpd<Epi>::value;
     constexpr int TURN = EpiTurn<Epi>::value;
-    constexpr int NO = (E / RL) * RK;  // outputs (pairs) of this thread
     if constexpr (TURN > 0) {
-        turn_pcg<T, M, PAD, Epi, NT, TURN>(v, pre, lds, red, tab, sd, stride, token, row0);
+        turn_pcg<T, M, PAD, Epi, NT, TURN, PF>(v, pre, lds, red, tab, sd, stride, token, row0);
         return;
     }
     cx<T> qk[UPD ? NO : 1], rk[UPD ? NO : 1];
     static_assert(!FWD || UPD, "the fused forward pass follows the folded update");
     cx<T> pk[FWD ? NO : 1];  // FWD: p of the pairs, for the next direction and the x update
+    // all operands of a group are requested together
 #pragma unroll
-    for (int u = 0; u < E / RL; ++u)
+    for (int g = 0; g < NO; g += GRP) {
+        if constexpr (!PF) {
 #pragma unroll
-        for (int r = 0; r < RK; ++r) {
-            const int n = (j + u * P) + r * (N / RL);
+            for (int i = 0; i < GRP; ++i) pre[i] = Epi::template pre<L>(sd, row, col(g + i));
+        }
+        if constexpr (UPD) {
+#pragma unroll
+            for (int i = 0; i < GRP; ++i)
+                rk[g + i] = ld2<T>(reinterpret_cast<const T*>(sd.r), (unsigned)row * L + col(g + i));
+        }
+#pragma unroll
+        for (int i = 0; i < GRP; ++i) {
+            const cx<T> c = v[((g + i) / RK) * RL + (g + i) % RK];
             if constexpr (UPD) {
-                // p and d prefetched with the spectrum (PF), or read here
-                typename Epi::Pre pr;
-                if constexpr (PF)
-                    pr = pre[u * RK + r];
-                else
-                    pr = Epi::template pre<L>(sd, row, 2 * n);
-                qk[u * RK + r] = Epi::template outq<L>(sd, row, 2 * n, v[u * RL + r].x, v[u * RL + r].y, pr, acc);
-                if constexpr (FWD) pk[u * RK + r] = pr.p;
-            } else if constexpr (Epi::PREF) {
-                Epi::template out2p<L>(sd, row, 2 * n, v[u * RL + r].x, v[u * RL + r].y, pre[u * RK + r], acc);
+                qk[g + i] = Epi::template outq<L>(sd, row, col(g + i), c.x, c.y, pre[PF ? g + i : i], acc);
+                if constexpr (FWD) pk[g + i] = pre[PF ? g + i : i].p;
             } else {
-                Epi::template out2<L>(sd, row, 2 * n, v[u * RL + r].x, v[u * RL + r].y, acc);
+                Epi::template out2p<L>(sd, row, col(g + i), c.x, c.y, pre[PF ? g + i : i], acc);
             }
         }
+    }
     if constexpr (UPD) {
-        // r of the same pairs, and their parts of r.r, r.q and q.q
-#pragma unroll
-        for (int u = 0; u < E / RL; ++u)
-#pragma unroll
-            for (int r = 0; r < RK; ++r)
-                rk[u * RK + r] = ld2<T>(reinterpret_cast<const T*>(sd.r) + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL)));
+        // the parts of r.r, r.q and q.q
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
             const cx<double> rv = mkc((double)rk[i].x, (double)rk[i].y), qv = mkc((double)qk[i].x, (double)qk[i].y);
@@ -1585,7 +1614,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
         }
     }
     if constexpr (UPD) {
-        SolveState* st = sd.st;
+        auto* st = gbl(sd.st);
         // the grid was not resident as a whole: the solve is abandoned and
         // the host repeats it with the separate update kernel
         auto give_up = [&]() {
@@ -1613,17 +1642,18 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
         const T a = (T)alpha;
         double rrn;
         const bool sure = next_rr(tot, (double)a, &rrn);
+        cx<T> xk[FWD ? NO : 1];  // FWD: the x accumulator of the pairs, requested before the first store
+        T* xa = reinterpret_cast<T*>(sizeof(T) == 8 ? (void*)sd.x : (void*)sd.e);
+        if constexpr (FWD) {
 #pragma unroll
-        for (int u = 0; u < E / RL; ++u)
+            for (int i = 0; i < NO; ++i) xk[i] = ld2<T>(xa, (unsigned)row * L + col(i));
+        }
 #pragma unroll
-            for (int r = 0; r < RK; ++r) {
-                cx<T> rv = rk[u * RK + r];
-                const cx<T> qv = qk[u * RK + r];
-                rv.x -= a * qv.x;
-                rv.y -= a * qv.y;
-                st2<T>(reinterpret_cast<T*>(sd.r) + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL)), rv);
-                rk[u * RK + r] = rv;
-            }
+        for (int i = 0; i < NO; ++i) {
+            rk[i].x -= a * qk[i].x;
+            rk[i].y -= a * qk[i].y;
+            st2<T>(reinterpret_cast<T*>(sd.r), (unsigned)row * L + col(i), rk[i]);
+        }
         // the totals are the same in every workgroup, so all take this branch
         // or none
         if (!sure) {
@@ -1649,35 +1679,29 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             // beta p, the transform, and the pending x update x <- x + alpha
             // p_old.  The forward pass's first radix equals this pass's last,
             // so the thread holds the same pairs of r and p in both.
-            if (check_due(st, rrn, s_iters + 1)) {
+            if (check_due(s_ci, rrn, s_ci.iters + 1)) {
                 if (blockIdx.x == 0 && tid == 0) st->pause = 1;
                 return;
             }
             const T beta = (T)(rrn / rho);
+            // x has arrived here (one wait, instead of one for all stores so
+            // far before each pair's)
+#pragma unroll
+            for (int i = 0; i < NO; ++i) asm volatile("" : "+v"(xk[i].x), "+v"(xk[i].y));
             constexpr int R1 = NSTG > 0 ? fft_radix(N, false, 0) : 1;
             static_assert(R1 == RL, "forward first radix and inverse last radix");
             cx<T> v2[E];
 #pragma unroll
-            for (int u = 0; u < E / RL; ++u)
-#pragma unroll
-                for (int r = 0; r < RK; ++r) {
-                    const cx<T> rv = rk[u * RK + r], po = pk[u * RK + r];
-                    const cx<T> p2 = mkc(rv.x + beta * po.x, rv.y + beta * po.y);
-                    st2<T>(reinterpret_cast<T*>(sd.p) + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL)), p2);
-                    v2[u * RL + r] = p2;
+            for (int i = 0; i < NO; ++i) {
+                const cx<T> po = pk[i];
+                const cx<T> p2 = mkc(rk[i].x + beta * po.x, rk[i].y + beta * po.y);
+                st2<T>(reinterpret_cast<T*>(sd.p), (unsigned)row * L + col(i), p2);
+                v2[(i / RK) * RL + i % RK] = p2;
+                if (a != T(0)) {
+                    xk[i].x += a * po.x;
+                    xk[i].y += a * po.y;
+                    st2<T>(xa, (unsigned)row * L + col(i), xk[i]);
                 }
-            if (a != T(0)) {
-                T* xa = reinterpret_cast<T*>(sizeof(T) == 8 ? (void*)sd.x : (void*)sd.e);
-#pragma unroll
-                for (int u = 0; u < E / RL; ++u)
-#pragma unroll
-                    for (int r = 0; r < RK; ++r) {
-                        T* xp = xa + (size_t)row * L + 2 * ((j + u * P) + r * (N / RL));
-                        cx<T> xv = ld2<T>(xp);
-                        xv.x += a * pk[u * RK + r].x;
-                        xv.y += a * pk[u * RK + r].y;
-                        st2<T>(xp, xv);
-                    }
             }
             // the forward transform reads its twiddles afresh (the pointer is
             // opaque to the compiler) rather than reusing the inverse half's
@@ -1687,6 +1711,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
             asm volatile("" : "+s"(tab2.tw));
             int tid2 = tid;
             asm volatile("" : "+v"(tid2));
+            tid2 &= NT - 1;  // (its range, for the index arithmetic)
             row_fwd_out<T, M, PAD, NT>(v2, lds, tab2, sd, __builtin_amdgcn_readfirstlane(row0 / RPW), tid2);
         }
     }
@@ -1818,7 +1843,7 @@ __global__ void __launch_bounds__(NT) k_check_zero(ByPtr slot, int stride) {
 #pragma unroll
         for (int r = 0; r < RK; ++r) {
             const size_t idx = (size_t)row * L + 2 * ((j + u * P) + r * (N / RL));
-            const cx<double> b2 = ld2<double>(sd.b + idx), d2 = ld2<double>(sd.d + idx);
+            const cx<double> b2 = ld2<double>(sd.b, idx), d2 = ld2<double>(sd.d, idx);
             st2<W>(reinterpret_cast<W*>(sd.r) + idx,
                    EpiCheck<W>::pair(mkc(0.0, 0.0), b2, d2, mask2(sd, idx), 0.0, 0.0, false, mkc(W(0), W(0)), acc));
         }

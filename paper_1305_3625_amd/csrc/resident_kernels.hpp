@@ -357,6 +357,22 @@ __device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>*
     constexpr int RL = fft_radix(N, false, NSTG - 1);
     const int tid = threadIdx.x;
     const int rl = tid / P, j = tid % P;
+    // the unpack's twiddles, where they are read from memory, before the
+    // first store to W (a read behind a store waits for it to complete)
+    constexpr bool TWM = std::is_pointer<TW>::value;
+    constexpr int CNT = RowShare<T, M, PAD>::COUNT;
+    cx<T> twk[TWM ? CNT : 1];
+    auto load_tw = [&]() {
+        if constexpr (TWM) {
+            if (!R::WROW || tid < R::RT) {
+#pragma unroll
+                for (int s = 0; s < CNT; ++s) {
+                    const RowShare<T, M, PAD> e(s);
+                    twk[s] = twl(tw, e.kt * R::CW + e.kk);
+                }
+            }
+        }
+    };
     if (!R::WVR || tid < R::RT) {
         const LdsLay<T, 1, 4, 1> lay{lds + rl * WORDS, 0};
         fft_run<T, N, M, -1, false, PAD != 0, LdsLay<T, 1, 4, 1>, false, R::WVR>(v, lay, j, tw);
@@ -364,16 +380,22 @@ __device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>*
 #pragma unroll
         for (int u = 0; u < E / RL; ++u) lay.template st_run<RL, N / RL>(j + u * P, v + u * RL);
     }
+    load_tw();
     xsync<R::WROW>();
     if (!R::WROW || tid < R::RT) {
 #pragma unroll
-        for (int s = 0; s < RowShare<T, M, PAD>::COUNT; ++s) {
+        for (int s = 0; s < CNT; ++s) {
             const RowShare<T, M, PAD> e(s);
             const int k = e.kt * R::CW + e.kk;
             const LdsLay<T, 1, 4, 1> lay{lds + e.il * WORDS, 0};
-            const cx<T> Zk = lay.ld(k), B = conjc(lay.ld((N - k) & (N - 1)));
+            const cx<T> Zk = lay.ld(k), B = conjc(lay.ld(N - k));
             const cx<T> s1 = Zk + B, d1 = Zk - B;
-            const cx<T> wd = cmul(twl(tw, k), d1);
+            cx<T> wk;
+            if constexpr (TWM)
+                wk = twk[s];
+            else
+                wk = twl(tw, k);
+            const cx<T> wd = cmul(wk, d1);
             cx<T> out = mkc(T(0.5) * (s1.x + wd.y), T(0.5) * (s1.y - wd.x));
             if (k == 0) out = mkc(Zk.x + Zk.y, Zk.x - Zk.y);
             gst_all<!R::ONEX>(Wb + w_at<T, M, PAD>(e.kt, rb * R::RPW + e.il, e.kk), out);
@@ -516,12 +538,12 @@ __device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const 
             const int jj = j + u * P;
             cx<T> A[R1], Bv[R1];
             lay.template ld_run<R1, S1>(jj, A);
-            lay.template ld_run<R1, S1>(jj == 0 ? 0 : S1 - jj, Bv);
+            lay.template ld_run<R1, S1>(S1 - jj, Bv);
 #pragma unroll
             for (int r = 0; r < R1; ++r) {
                 const int k = jj + r * S1;
                 const cx<T> Y = A[r];
-                const cx<T> B = conjc(jj == 0 ? Bv[(R1 - r) % R1] : Bv[R1 - 1 - r]);
+                const cx<T> B = conjc(Bv[R1 - 1 - r]);
                 const cx<T> s1 = Y + B, d1 = Y - B;
                 const cx<T> wd = cmul(conjc(twl(tw, k)), d1);
                 v[u * R1 + r] = mkc(s1.x - wd.y, s1.y + wd.x);
@@ -697,10 +719,13 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
             cx<double> v[E], xv[NO];
             if (rows) {
                 const unsigned o = row0();
+                if constexpr (MIXED) {
+#pragma unroll
+                    for (int i = 0; i < NO; ++i) xv[i] = zero ? mkc(0.0, 0.0) : ld2<double>(sd.x + o + rel(i));
+                }
 #pragma unroll
                 for (int i = 0; i < NO; ++i) {
                     if constexpr (MIXED) {
-                        xv[i] = zero ? mkc(0.0, 0.0) : ld2<double>(sd.x + o + rel(i));
                         xv[i].x += (double)x[i].x;
                         xv[i].y += (double)x[i].y;
                     } else {
