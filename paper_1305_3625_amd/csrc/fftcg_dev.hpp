@@ -347,18 +347,6 @@ template <typename T>
 __device__ __forceinline__ cx<T> twl(const cx<T>* tw, int m) {
     return gld(tw + m);
 }
-// A twiddle table in constant memory: its loads are invariant, so a kernel
-// that loops over transforms keeps its twiddles in registers.
-template <typename T>
-struct ConstTw {
-    const cx<T>* p;
-};
-template <typename T>
-__device__ __forceinline__ cx<T> twl(ConstTw<T> tw, int m) {
-    typedef __attribute__((address_space(4))) const typename VecT<T, 2>::type V;
-    const auto v = ((V*)tw.p)[m];
-    return mkc(v.x, v.y);
-}
 template <typename T, int R, class TW>
 __device__ __forceinline__ void tw_load(cx<T>* pb, TW tw, int m) {
     pb[0] = twl(tw, m);

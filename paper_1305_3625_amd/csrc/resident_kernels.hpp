@@ -57,11 +57,25 @@ struct RGeo {
     // one per XCD
     static constexpr int NG = cmax(1, G::SUM_GROUPS), GM = NB / NG;  // groups, members of a group
     static constexpr bool ONEX = NG == 1;
-    // twiddles in registers for the whole launch, where they fit beside the rest
-    static constexpr bool HOIST = (int)sizeof(T) * M <= 2048;
     static constexpr bool OK = G::SUM_GROUPS > 0 && NB % NG == 0 && GM <= 64 && RT % 64 == 0 && N % NB == 0 && CW * G::PC == U * NT && CU * U == CW && RPW >= 2 &&
                                (size_t)LDS_WORDS * sizeof(cx<T>) <= 140 * 1024;
 };
+
+// The thread's index, opaque to the compiler, taken afresh in every phase.
+// What the phases derive from it (LDS and W offsets, twiddles, the meetings'
+// addresses) does not change from one iteration to the next, and the compiler
+// would compute it all once before the loop: several hundred values that end
+// in accumulation registers and in scratch memory, whose reads wait behind
+// the stores to W.  Afresh, against kept (twiddles with it where they fit),
+// us per iteration: M = 64 periodic FP32 7.0, was 7.5; padded L = 128 FP32
+// 7.3, was 7.6; M = 256 periodic FP32 8.6, was 9.4; M = 512 periodic FP32
+// 15.6, was 18.6, FP64 17.5, was 22.0; M = 1024 periodic FP32 18.8, was 20.2;
+// padded L = 512 the same.
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t & 1023;
+}
 
 // ---- accesses between workgroups ----------------------------------------------
 // Loads that miss the CU's L1 and see what any XCD has stored with scope
@@ -70,14 +84,14 @@ struct RGeo {
 // loads above are served: 0.2 us from one workgroup to another, against 0.4
 // to 0.5 us through the memory side).
 template <typename T>
-__device__ __forceinline__ cx<T> gld_all(const cx<T>* p) {
+__device__ __forceinline__ cx<T> gld_all(const cx<T>* base, unsigned idx) {
     using U = unsigned long long;
-    const auto* w = reinterpret_cast<const U*>(p);
+    const auto* w = at_byte<const U>(const_cast<cx<T>*>(base), idx * (unsigned)sizeof(cx<T>));
     if constexpr (sizeof(T) == 4) {
-        return __builtin_bit_cast(cx<T>, __hip_atomic_load(gbl(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        return __builtin_bit_cast(cx<T>, __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     } else {
-        const U a = __hip_atomic_load(gbl(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const U b = __hip_atomic_load(gbl(w + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const U a = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const U b = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return mkc(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
     }
 }
@@ -92,15 +106,16 @@ __device__ __forceinline__ unsigned long long word_get(const unsigned long long*
     return __hip_atomic_load(gbl(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <bool ALL, typename T>
-__device__ __forceinline__ void gst_all(cx<T>* p, cx<T> c) {
+__device__ __forceinline__ void gst_all(cx<T>* base, unsigned idx, cx<T> c) {
     using U = unsigned long long;
+    auto* w = at_byte<U>(base, idx * (unsigned)sizeof(cx<T>));
     if constexpr (!ALL) {
-        gst(p, c);
+        gst(base, idx, c);
     } else if constexpr (sizeof(T) == 4) {
-        word_put<true>(reinterpret_cast<U*>(p), __builtin_bit_cast(U, c));
+        __hip_atomic_store(w, __builtin_bit_cast(U, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-        word_put<true>(reinterpret_cast<U*>(p), __builtin_bit_cast(U, c.x));
-        word_put<true>(reinterpret_cast<U*>(p) + 1, __builtin_bit_cast(U, c.y));
+        __hip_atomic_store(w, __builtin_bit_cast(U, c.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(w + 1, __builtin_bit_cast(U, c.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -156,7 +171,7 @@ struct Meet {
     // by the workgroup's first wave: arrival with `token`, and the wait until
     // all have arrived (tokens only grow)
     __device__ __forceinline__ bool arrive(unsigned long long token) const {
-        const int lane = threadIdx.x & 63;
+        const int lane = fresh_tid() & 63;
         if (lane == 0) word_put<false>(base + FLAG + g * GS + i, token);
         auto members = [&] { return lane >= GM || word_get(base + FLAG + g * GS + lane) >= token; };
         if constexpr (NG == 1) {
@@ -212,7 +227,7 @@ struct Meet {
     }
     // Empties this workgroup's words of the sets in `mask`, in a ring half.
     __device__ __forceinline__ void empty(int ring, unsigned mask) const {
-        const int set = threadIdx.x;
+        const int set = fresh_tid();
         if (set < SETS && ((mask >> set) & 1u)) {
             word_put<false>(part(ring, set) + i, kEmpty);
             if (ALL && i == 0) {
@@ -236,7 +251,7 @@ struct Meet {
     __device__ __forceinline__ bool sums(const double* acc, int set0, int ring, double* sh, double* s_tot, int* s_ok,
                                          double* tot) const {
         constexpr int NW = RT / 64;
-        const int tid = threadIdx.x, lane = tid & 63;
+        const int tid = fresh_tid(), lane = tid & 63;
         auto is_min = [](int a) { return ((MINMASK >> a) & 1u) != 0; };
         if (tid < RT) {
             double w[N];
@@ -338,10 +353,10 @@ struct RowShare {
     static constexpr int THREADS = R::WROW ? 64 : R::NT, ROWS = R::WROW ? R::RWV : R::RPW;
     static constexpr int COUNT = ROWS * G::N / THREADS;
     int il, kt, kk;
-    __device__ __forceinline__ RowShare(int s) {
-        const int qi = (R::WROW ? (threadIdx.x & 63) : threadIdx.x) + s * THREADS;
+    __device__ __forceinline__ RowShare(int tid, int s) {
+        const int qi = (R::WROW ? (tid & 63) : tid) + s * THREADS;
         kk = qi % R::CW;
-        il = (qi / R::CW) % ROWS + (R::WROW ? (threadIdx.x >> 6) * R::RWV : 0);
+        il = (qi / R::CW) % ROWS + (R::WROW ? (tid >> 6) * R::RWV : 0);
         kt = qi / (R::CW * ROWS);
     }
 };
@@ -355,24 +370,12 @@ __device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>*
     constexpr int N = G::N, E = G::ER, P = G::PR, WORDS = G::ROW_WORDS;
     constexpr int NSTG = fft_nstages(N);
     constexpr int RL = fft_radix(N, false, NSTG - 1);
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid() & (R::NT - 1);
     const int rl = tid / P, j = tid % P;
-    // the unpack's twiddles, where they are read from memory, before the
-    // first store to W (a read behind a store waits for it to complete)
-    constexpr bool TWM = std::is_pointer<TW>::value;
+    // the unpack's twiddles, before the first store to W (a read behind a
+    // store waits for it to complete)
     constexpr int CNT = RowShare<T, M, PAD>::COUNT;
-    cx<T> twk[TWM ? CNT : 1];
-    auto load_tw = [&]() {
-        if constexpr (TWM) {
-            if (!R::WROW || tid < R::RT) {
-#pragma unroll
-                for (int s = 0; s < CNT; ++s) {
-                    const RowShare<T, M, PAD> e(s);
-                    twk[s] = twl(tw, e.kt * R::CW + e.kk);
-                }
-            }
-        }
-    };
+    cx<T> twk[CNT];
     if (!R::WVR || tid < R::RT) {
         const LdsLay<T, 1, 4, 1> lay{lds + rl * WORDS, 0};
         fft_run<T, N, M, -1, false, PAD != 0, LdsLay<T, 1, 4, 1>, false, R::WVR>(v, lay, j, tw);
@@ -380,25 +383,26 @@ __device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>*
 #pragma unroll
         for (int u = 0; u < E / RL; ++u) lay.template st_run<RL, N / RL>(j + u * P, v + u * RL);
     }
-    load_tw();
+    if (!R::WROW || tid < R::RT) {
+#pragma unroll
+        for (int s = 0; s < CNT; ++s) {
+            const RowShare<T, M, PAD> e(tid, s);
+            twk[s] = twl(tw, e.kt * R::CW + e.kk);
+        }
+    }
     xsync<R::WROW>();
     if (!R::WROW || tid < R::RT) {
 #pragma unroll
         for (int s = 0; s < CNT; ++s) {
-            const RowShare<T, M, PAD> e(s);
+            const RowShare<T, M, PAD> e(tid, s);
             const int k = e.kt * R::CW + e.kk;
             const LdsLay<T, 1, 4, 1> lay{lds + e.il * WORDS, 0};
             const cx<T> Zk = lay.ld(k), B = conjc(lay.ld(N - k));
             const cx<T> s1 = Zk + B, d1 = Zk - B;
-            cx<T> wk;
-            if constexpr (TWM)
-                wk = twk[s];
-            else
-                wk = twl(tw, k);
-            const cx<T> wd = cmul(wk, d1);
+            const cx<T> wd = cmul(twk[s], d1);
             cx<T> out = mkc(T(0.5) * (s1.x + wd.y), T(0.5) * (s1.y - wd.x));
             if (k == 0) out = mkc(Zk.x + Zk.y, Zk.x - Zk.y);
-            gst_all<!R::ONEX>(Wb + w_at<T, M, PAD>(e.kt, rb * R::RPW + e.il, e.kk), out);
+            gst_all<!R::ONEX>(Wb, w_at<T, M, PAD>(e.kt, rb * R::RPW + e.il, e.kk), out);
         }
     }
 }
@@ -408,10 +412,10 @@ template <typename T, int M, int PAD>
 struct ColOf {
     using R = RGeo<T, M, PAD>;
     int kk, j, cl;  // column of the workgroup, thread of the column, LDS region
-    __device__ __forceinline__ ColOf(int u) {
+    __device__ __forceinline__ ColOf(int tid, int u) {
         constexpr int P = R::G::PC;
-        cl = R::WVC ? threadIdx.x / P : threadIdx.x % R::CU;
-        j = R::WVC ? threadIdx.x % P : threadIdx.x / R::CU;
+        cl = R::WVC ? tid / P : tid % R::CU;
+        j = R::WVC ? tid % P : tid / R::CU;
         kk = u * R::CU + cl;
     }
 };
@@ -425,7 +429,7 @@ struct ResSpec {
         constexpr int E = G::EC, P = G::PC, RL = fft_radix(M, false, fft_nstages(M) - 1), TT = G::TT;
 #pragma unroll
         for (int u = 0; u < R::U; ++u) {
-            const ColOf<T, M, PAD> c(u);
+            const ColOf<T, M, PAD> c(threadIdx.x, u);
             const int k = blk * R::CW + c.kk;
             const T* gc = tab.ghq + (size_t)(k / TT) * G::MH * TT + k % TT;
 #pragma unroll
@@ -450,6 +454,7 @@ __device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, 
     using G = Geo<T, M, PAD>;
     using Lay = typename R::ColLay;
     constexpr int E = G::EC, P = G::PC;
+    const int tid = fresh_tid() & (R::NT - 1);
     constexpr int NSTG = fft_nstages(M);
     constexpr int R1 = fft_radix(M, false, 0), RL = fft_radix(M, false, NSTG - 1), RZ = fft_radix(M, true, NSTG - 1);
     auto mul = [&](T g) {
@@ -461,17 +466,17 @@ __device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, 
     cx<T> v[R::U][E];
 #pragma unroll
     for (int u = 0; u < R::U; ++u) {
-        const ColOf<T, M, PAD> c(u);
+        const ColOf<T, M, PAD> c(tid, u);
 #pragma unroll
         for (int i = 0; i < E; ++i) {
             if (PAD && i % R1 >= R1 / 2) continue;
             const int n = (c.j + (i / R1) * P) + (i % R1) * (M / R1);
-            v[u][i] = gld_all(Wb + w_at<T, M, PAD>(blk, n, c.kk));
+            v[u][i] = gld_all(Wb, w_at<T, M, PAD>(blk, n, c.kk));
         }
     }
 #pragma unroll
     for (int u = 0; u < R::U; ++u) {
-        const ColOf<T, M, PAD> c(u);
+        const ColOf<T, M, PAD> c(tid, u);
         const Lay lay{lds + c.cl * R::CWORDS, 0};
         // (LEAD: the column before may still be read)
         fft_run<T, M, M, -1, false, PAD != 0, Lay, (R::U > 1), R::WVC>(v[u], lay, c.j, tw);
@@ -499,7 +504,7 @@ __device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, 
         for (int i = 0; i < E; ++i) {
             if (PAD && i % RZ >= RZ / 2) continue;
             const int n = (c.j + (i / RZ) * P) + (i % RZ) * (M / RZ);
-            gst_all<!R::ONEX>(Wb + w_at<T, M, PAD>(blk, n, c.kk), v[u][i]);
+            gst_all<!R::ONEX>(Wb, w_at<T, M, PAD>(blk, n, c.kk), v[u][i]);
         }
     }
 }
@@ -514,18 +519,18 @@ __device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const 
     constexpr int N = G::N, E = G::ER, P = G::PR, WORDS = G::ROW_WORDS;
     constexpr int R1 = fft_radix(N, true, 0), S1 = N / R1;
     constexpr int COUNT = RowShare<T, M, PAD>::COUNT;
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid() & (R::NT - 1);
     const int rl = tid / P, j = tid % P;
     if (!R::WROW || tid < R::RT) {
         cx<T> wv[COUNT];
 #pragma unroll
         for (int s = 0; s < COUNT; ++s) {
-            const RowShare<T, M, PAD> e(s);
-            wv[s] = gld_all(Wb + w_at<T, M, PAD>(e.kt, rb * R::RPW + e.il, e.kk));
+            const RowShare<T, M, PAD> e(tid, s);
+            wv[s] = gld_all(Wb, w_at<T, M, PAD>(e.kt, rb * R::RPW + e.il, e.kk));
         }
 #pragma unroll
         for (int s = 0; s < COUNT; ++s) {
-            const RowShare<T, M, PAD> e(s);
+            const RowShare<T, M, PAD> e(tid, s);
             const LdsLay<T, 1, 4, 1> l2{lds + e.il * WORDS, 0};
             l2.st(e.kt * R::CW + e.kk, wv[s]);
         }
@@ -621,16 +626,6 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
     const Meet<R::NG, R::GM> all{ra.words, st.bar_limit, blk % R::NG, blk / R::NG};
     cx<T>* Wb = reinterpret_cast<cx<T>*>(sd.W);
     unsigned long long token = ra.token;
-    auto twiddles = [&]() {
-        if constexpr (R::HOIST) {
-            return ConstTw<T>{tab.tw};
-        } else {
-            // opaque to the compiler: read afresh in every phase
-            const cx<T>* t = tab.tw;
-            asm volatile("" : "+s"(t));
-            return t;
-        }
-    };
     auto give_up = [&]() {
         if (tid == 0) {
             __hip_atomic_store(&sd.st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -640,7 +635,6 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
     // all sums' words are empty before the first meeting
     all.empty(0, ITER_SETS | CHECK_SETS);
     all.empty(1, ITER_SETS | CHECK_SETS);
-    auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
     // (recomputed where they are used, not kept in registers across the loop)
     auto row0 = [&]() {
         unsigned o = (unsigned)row * L + 2 * j;
@@ -691,7 +685,7 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
         for (int i = 0; i < NO; ++i) v[(i / RK) * RL + i % RK] = r[i];
         const T c2 = (T)((double)M * (double)M * st.dbar);
         const T c4 = (T)((double)M * (double)M * (double)M * (double)M);
-        if (!res_product<T, M, PAD, true>(v, lds, twiddles(), sp, c2, c4, Wb, rb, blk, all, token, &s_ok)) return false;
+        if (!res_product<T, M, PAD, true>(v, lds, tab.tw, sp, c2, c4, Wb, rb, blk, all, token, &s_ok)) return false;
         token += 2;
         if (rows) {
             const unsigned o = row0();
@@ -826,20 +820,23 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
         cx<T> v[E];
 #pragma unroll
         for (int i = 0; i < NO; ++i) v[(i / RK) * RL + i % RK] = p[i];
-        if (!res_product<T, M, PAD, false>(v, lds, twiddles(), sp, T(0), T(0), Wb, rb, blk, all, token, &s_ok))
+        if (!res_product<T, M, PAD, false>(v, lds, tab.tw, sp, T(0), T(0), Wb, rb, blk, all, token, &s_ok))
             return give_up();
         token += 2;
         constexpr int NS = PCG ? 1 : 4;
         double acc[4] = {0.0, 0.0, 0.0, 0.0}, tot[4];
         cx<T> q[NO];
         if (rows) {
+            int row1 = row, j1 = j;  // (the mask's offsets, as row0)
+            asm volatile("" : "+v"(row1), "+v"(j1));
+            auto col1 = [&](int i) { return 2 * ((j1 + (i / RK) * P) + (i % RK) * (N / RL)); };
 #pragma unroll
             for (int i = 0; i < NO; ++i) {
                 const cx<T> c = v[(i / RK) * RL + i % RK];
                 typename EpiCGU<T>::Pre pr;
                 pr.p = p[i];
                 pr.d = d[i];
-                q[i] = EpiCGU<T>::template outq<L>(sd, row, col(i), c.x, c.y, pr, acc);
+                q[i] = EpiCGU<T>::template outq<L>(sd, row1, col1(i), c.x, c.y, pr, acc);
             }
             if constexpr (!PCG) {
 #pragma unroll
