@@ -361,10 +361,16 @@ template <int NG, bool MIN = false, class GET>
 __device__ __forceinline__ double group_sum(unsigned int n, double none, GET get) {
     const unsigned int lane = threadIdx.x & 63;
     double mine = none;  // the lane's group (lane & 7)
+    double v[NG];        // all of them requested together (n > 0)
+#pragma unroll
     for (unsigned int g = 0; g < NG; ++g) {
         const unsigned int i = g + NG * lane;
-        const double v = i < n ? get(i) : none;
-        const double t = MIN ? wave_min(v) : wave_sum(v);
+        v[g] = get(i < n ? i : 0u);
+        v[g] = i < n ? v[g] : none;
+    }
+#pragma unroll
+    for (unsigned int g = 0; g < NG; ++g) {
+        const double t = MIN ? wave_min(v[g]) : wave_sum(v[g]);
         if (NG == 1 || (lane & 7) == g) mine = t;
     }
     if (NG == 1) return mine;
@@ -1863,6 +1869,10 @@ __global__ void __launch_bounds__(NT) k_check_zero(ByPtr slot, int stride) {
 // Single-block finaliser of an FP64 check: stop decision, residual
 // replacement, restart guard, and status for the host.
 // NG: the order of its sums (group_sum; 0: sum_partials').
+// One serial chain, so its reads are put side by side: the state as a whole
+// in registers (thread 0; decided on there and stored once) beside the
+// partials, whose sets the waves share (with eight slots of
+// L = 512 7.3 us, 15.3 when each field and set was read by itself).
 template <int NT, int NG>
 __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, int npart_rr, int stride, int n) {
     __shared__ double red[8 * ((NT + 63) / 64)];
@@ -1870,29 +1880,33 @@ __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, i
     __shared__ int s_update;
     const SlotDesc& sd = slot.get();
     if (!sd.active) return;
-    SolveState* st = sd.st;
-    if (st->done || !st->pause) {
-        if (threadIdx.x == 0) publish_status(sd, st->done, st->status, st->gen, st->iters, st->last_check_iter);
+    const int tid = threadIdx.x;
+    const auto pd = pause_done(sd.st);
+    SolveState st;
+    if (tid == 0) st = *reinterpret_cast<const SolveState*>(sd.st);
+    if (pd.y != 0 || pd.x == 0) {
+        if (tid == 0) publish_status(sd, st.done, st.status, st.gen, st.iters, st.last_check_iter);
         return;
     }
     // the eight partial sets, each summed (min d: minimised) by thread t over
     // t, t + NT, ... and then over the block, all in one exchange; the order
     // is that of sum_partials / block_min
-    const int sets[8] = {PS_CHK_R, PS_CHK_X, PS_CHK_B, PS_CHK_RW, PS_CHK_DMIN, PS_CHK_BAD, PS_CHK_DIFF, PS_CHK_DSUM};
+    constexpr int sets[8] = {PS_CHK_R,    PS_CHK_X,   PS_CHK_B,    PS_CHK_RW,
+                             PS_CHK_DMIN, PS_CHK_BAD, PS_CHK_DIFF, PS_CHK_DSUM};
     double acc[8] = {0.0, 0.0, 0.0, 0.0, 1.0e300, 0.0, 0.0, 0.0};
     const auto* part = gbl(sd.part);
-    if constexpr (NG > 0) {
-        if (threadIdx.x < 64) {
+    if constexpr (NG > 0 && NT % 64 == 0) {
+        constexpr int NW = NT / 64;
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const auto* pa = part + sets[a] * stride;
-                const auto get = [&](unsigned int i) { return pa[i]; };
-                const double t = a == 4 ? group_sum<NG, true>(npart_chk, 1.0e300, get) : group_sum<NG>(npart_chk, 0.0, get);
-                if (threadIdx.x == 0) s_tot[a] = t;
-            }
+        for (int a = 0; a < 8; ++a) {
+            if (a % NW != __builtin_amdgcn_readfirstlane(tid >> 6)) continue;
+            const auto* pa = part + sets[a] * stride;
+            const auto get = [&](unsigned int i) { return pa[i]; };
+            const double t = a == 4 ? group_sum<NG, true>(npart_chk, 1.0e300, get) : group_sum<NG>(npart_chk, 0.0, get);
+            if ((tid & 63) == 0) s_tot[a] = t;
         }
     } else {
-        for (int i = threadIdx.x; i < npart_chk; i += NT) {
+        for (int i = tid; i < npart_chk; i += NT) {
 #pragma unroll
             for (int a = 0; a < 8; ++a) {
                 const double v = part[sets[a] * stride + i];
@@ -1900,24 +1914,24 @@ __global__ void __launch_bounds__(NT) k_check_final(ByPtr slot, int npart_chk, i
             }
         }
         const double tot = block_reduce_n<NT, 8, 1u << 4>(acc, red);
-        if (threadIdx.x < 8) s_tot[threadIdx.x] = tot;
+        if (tid < 8) s_tot[tid] = tot;
     }
     __syncthreads();
-    const double R = s_tot[0], X = s_tot[1], B = s_tot[2], RW = s_tot[3];
-    const double dmin = s_tot[4], BAD = s_tot[5], DIFF = s_tot[6], DSUM = s_tot[7];
-    if (threadIdx.x == 0) {
-        if (st->checks == 0) st->dbar = DSUM / (double)n;
-        s_update = check_decide(st, R, X, B, RW, BAD, DIFF, dmin);
-        if (s_update) st->rho_next = RW;  // r.r for the folded update's iterations
+    const double RW = s_tot[3];
+    if (tid == 0) {
+        if (st.checks == 0) st.dbar = s_tot[7] / (double)n;
+        s_update = check_decide(&st, s_tot[0], s_tot[1], s_tot[2], RW, s_tot[5], s_tot[6], s_tot[4]);
+        if (s_update) st.rho_next = RW;  // r.r for the folded update's iterations
         // preconditioned CG: z = P^{-1} r of the replaced residual comes next
-        st->need_pre = (s_update && st->pcg) ? 1 : 0;
-        publish_status(sd, st->done, st->status, st->gen, st->iters, st->last_check_iter);
+        st.need_pre = (s_update && st.pcg) ? 1 : 0;
+        *sd.st = st;
+        publish_status(sd, st.done, st.status, st.gen, st.iters, st.last_check_iter);
     }
     __syncthreads();
     if (s_update) {
         // residual replacement: the next iteration's rho is |r|^2 of the new r
-        double* prr = sd.part + PS_RR * stride;
-        for (int i = threadIdx.x; i < npart_rr; i += NT) prr[i] = (i == 0) ? RW : 0.0;
+        auto* prr = gbl(sd.part) + PS_RR * stride;
+        for (int i = tid; i < npart_rr; i += NT) prr[i] = (i == 0) ? RW : 0.0;
     }
 }
 
