@@ -357,13 +357,21 @@ void finish_request(fftcg_server_s* srv, Request* q, int status, const SolveStat
 }
 
 // One chunk of the multi-pass engine over slots 0..nsl-1: chunk_iters CG
-// iterations, then an FP64-check sequence (kernel launches only).
+// iterations, with an FP64-check sequence after every kCheckEvery of them and
+// after the last (kernel launches only).  A slot that needs a check waits for
+// the next sequence (its kernels return at once until then); when that comes
+// changes nothing in its result.  Eight load-stepped sequences of six steps at
+// L = 512, chunks of ten iterations: 26.5 ms with the check at the end only,
+// 25.2 after every 5, 25.4 / 25.9 / 25.8 after every 4 / 3 / 2.
+constexpr int kCheckEvery = 5;
 void launch_chunk(fftcg_server_s* srv, Class* c, int nsl, bool pcg) {
     const EngineOps* ops = c->plan->ops;
     const auto iter = pcg ? ops->iter_pcg : ops->iter;
     const auto check = pcg ? ops->check_pcg : ops->check;
-    for (int k = 0; k < srv->opts.chunk_iters; ++k)
+    for (int k = 0; k < srv->opts.chunk_iters; ++k) {
+        if (k > 0 && k % kCheckEvery == 0) check(c->precision, c->plan->tabs, c->d_table, nsl, c->plan->stride, c->stream);
         iter(c->precision, c->plan->tabs, c->d_table, nsl, c->plan->stride, c->stream);
+    }
     check(c->precision, c->plan->tabs, c->d_table, nsl, c->plan->stride, c->stream);
 }
 
