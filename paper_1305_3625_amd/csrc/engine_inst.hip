@@ -126,11 +126,9 @@ template <typename W>
 constexpr bool kResBuilt = M >= 32 && G<W>::SUM_GROUPS > 0 && RGeo<W, M, PAD>::OK;
 
 // The turn pass saves the reads of r and p and one launch per iteration.
-// Measured when it still had a second barrier, against the folded update
-// alone (whole mixed solves, alternating in one process): padded L = 2048
-// +4.2%, periodic M = 2048 +5.2%; but padded L = 1024 (M = 2048) -1.2%, so it
-// is not offered there.
-constexpr bool kTurnPays = !(PAD && M == 2048);
+// Against the folded update alone (whole solves, alternating in one process):
+// padded L = 1024 mixed 4117 -> 3887 us, FP64 5227 -> 4842; padded L = 2048
+// mixed 9076 -> 8289; periodic M = 2048 mixed 4188 -> 3824.
 // Built above the resident kernel's grids, where its own grid can be resident
 // at once: not in FP64 on rows of 16 pairs a thread and more (over 200 VGPRs,
 // two workgroups per CU).
@@ -208,7 +206,7 @@ bool turn_capable_t() {
     if constexpr (!kTurnBuilt<W>)
         return false;
     else
-        return kTurnPays && grid_capable_t<W>() &&
+        return grid_capable_t<W>() &&
                whole_grid_resident<RT, RB>(reinterpret_cast<const void*>(k_row_turn<W, M, PAD, ByPtr, RT>));
 }
 
