@@ -97,7 +97,7 @@ void iter_t(const PlanTabs& pt, const SlotDesc* slots, int nslots, int stride, h
                        sp);
     hipLaunchKernelGGL((k_row_inv<W, M, PAD, EpiCG<W>, ByPtr, RT>), dim3(G<W>::ROW_BLOCKS, nslots), dim3(RT), 0,
                        s, tab, sp, stride);
-    hipLaunchKernelGGL((k_update<W, UPD_NT>), dim3(g4_blocks(), nslots), dim3(UPD_NT), 0, s, sp, LL * LL,
+    hipLaunchKernelGGL((k_update<W, UPD_NT, LL>), dim3(g4_blocks(), nslots), dim3(UPD_NT), 0, s, sp, LL * LL,
                        G<W>::ROW_BLOCKS, stride);
 }
 
@@ -161,7 +161,7 @@ void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, 
                               sp, stride);
     } else if (pass == 3) {
         if (!grid)
-            hipExtLaunchKernelGGL((k_update<W, UPD_NT>), dim3(g4_blocks()), dim3(UPD_NT), 0, s, e0, e1, 0, sp,
+            hipExtLaunchKernelGGL((k_update<W, UPD_NT, LL>), dim3(g4_blocks()), dim3(UPD_NT), 0, s, e0, e1, 0, sp,
                                   LL * LL, RB, stride);
     } else if constexpr (kTurnBuilt<W>) {
         if (grid)

@@ -131,8 +131,7 @@ void Workspace::release() {
 
 size_t workspace_bytes(int L, int M, int stride) {
     const size_t n = (size_t)L * L;
-    const size_t N = (size_t)M / 2;
-    return N * L * 16 + 4 * n * 8 + 2 * n * 4 + (size_t)NPART_SETS * stride * 8 + sizeof(SolveState) +
+    return w_bytes(L, M) + 4 * n * 8 + 2 * n * 4 + (size_t)NPART_SETS * stride * 8 + sizeof(SolveState) +
            sizeof(SlotDesc) + 4096;
 }
 
@@ -141,8 +140,7 @@ int Workspace::init(int L_, int M_, int stride_) {
     M = M_;
     stride = stride_;
     const size_t n = (size_t)L * L;
-    const size_t N = (size_t)M / 2;
-    HIPCHK(hipMalloc(&W, std::max<size_t>(N * L * 16, 256)));
+    HIPCHK(hipMalloc(&W, w_bytes(L, M)));
     HIPCHK(hipMalloc(&r, n * 8));
     HIPCHK(hipMalloc(&p, n * 8));
     HIPCHK(hipMalloc(&q, n * 8));
@@ -298,7 +296,7 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
         if (r2 == FFTCG_OK) r2 = upload(&p->ghq64, build_ghq<double>(kernel_spectrum, M, p->ops->tt64), &bytes);
         if (r2 == FFTCG_OK) r2 = upload(&p->ghN32, build_ghN<float>(kernel_spectrum, M), &bytes);
         if (r2 == FFTCG_OK) r2 = upload(&p->ghN64, build_ghN<double>(kernel_spectrum, M), &bytes);
-        if (r2 == FFTCG_OK && hipMalloc(&p->apply_W, std::max<size_t>((size_t)(M / 2) * L * 16, 256)) != hipSuccess)
+        if (r2 == FFTCG_OK && hipMalloc(&p->apply_W, w_bytes(L, M)) != hipSuccess)
             r2 = FFTCG_ENOMEM;
         bytes += (size_t)(M / 2) * L * 16;
         if (r2 == FFTCG_OK && hipEventCreateWithFlags(&p->apply_ev, hipEventDisableTiming) != hipSuccess)

@@ -87,6 +87,12 @@ struct Geo {
     // pass 137 -> 105 us); W keeps its pairs, for the row passes' 32-byte
     // runs (with tiles of one column the row passes lost 33 us).
     static constexpr int CT = (M >= 8192 && TT > 1) ? 1 : TT;
+    // a tile of W; on the largest grid with 128 bytes behind it: a row's
+    // elements lie a tile apart, a power of two without them (row-forward
+    // pass at M = 8192 FP32 113 -> 101 us, FP64 174 -> 148; at M = 4096 no
+    // gain, FP64 37.4 us with, 35.0 without)
+    static constexpr int WT = L * TT + (M >= 8192 ? 128 / (int)sizeof(cx<T>) : 0);
+    static_assert((N / TT) * (size_t)WT * sizeof(cx<T>) <= w_bytes(L, M), "W holds the padded tiles");
     static constexpr int COL_SH = ilog2c(16 * CT);
     static constexpr int COL_THREADS = CT * PC;
     static constexpr int NTILE = N / TT;
@@ -324,6 +330,37 @@ __device__ __forceinline__ void st2(T* base, unsigned idx, cx<T> c) {
     v.y = c.y;
     *at_byte<typename VecT<T, 2>::type>(base, idx * (unsigned)sizeof(T)) = v;
 }
+// Pairs of the grid's vectors (r, p, q, x, ...; L: the grid).  On the largest
+// grids an iteration's data (470 MB at L = 4096 FP32) exceeds the 256 MB
+// last-level cache; the vectors then pass through it without being kept, and
+// W, which is written and read by three passes in a row, stays (mixed solve of
+// L = 4096: 79.9 ms kept, 68.8 passing; column pass 133 -> 110 us, row passes
+// 133 and 89 -> 113 and 76).  Not q's store: the update reads it next (68.8
+// against 69.3 ms).  Below, everything fits (L = 2048: 117 MB FP32, 235 MB
+// FP64), and passing costs: FP32 13.8 -> 14.4 ms, FP64 16.0 -> 18.7.
+template <int L>
+constexpr bool kStream = L >= 4096;
+template <typename T, int L>
+__device__ __forceinline__ cx<T> ldv(const T* base, unsigned idx) {
+    const auto* p = at_byte<const typename VecT<T, 2>::type>(const_cast<T*>(base), idx * (unsigned)sizeof(T));
+    typename VecT<T, 2>::type v;
+    if constexpr (kStream<L>)
+        v = __builtin_nontemporal_load(p);
+    else
+        v = *p;
+    return mkc(v.x, v.y);
+}
+template <typename T, int L>
+__device__ __forceinline__ void stv(T* base, unsigned idx, cx<T> c) {
+    typename VecT<T, 2>::type v;
+    v.x = c.x;
+    v.y = c.y;
+    auto* p = at_byte<typename VecT<T, 2>::type>(base, idx * (unsigned)sizeof(T));
+    if constexpr (kStream<L>)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
 template <typename T>
 __device__ __forceinline__ cx<T> gld(const cx<T>* base, unsigned idx) {
     return ld2<T>(reinterpret_cast<const T*>(base), 2 * idx);
@@ -411,7 +448,7 @@ struct ProApply {
     static __device__ __forceinline__ bool begin(const SlotDesc&, Sh&, Sc&, int, int) { return true; }
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
-        return ld2<double>(sd.x, (unsigned)row * L + col);
+        return ldv<double, L>(sd.x, (unsigned)row * L + col);
     }
     template <int L>
     static __device__ __forceinline__ cx<T> combine(const SlotDesc&, const Sc&, const Raw& v, int, int, double*) {
@@ -471,9 +508,9 @@ struct ProCG {
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
         Raw w;
-        w.r = ld2<W>(reinterpret_cast<const W*>(sd.r), idx);
-        w.p = ld2<W>(reinterpret_cast<const W*>(sd.p), idx);
-        if constexpr (!LATE_X) w.x = ld2<XA>(xacc(sd), idx);
+        w.r = ldv<W, L>(reinterpret_cast<const W*>(sd.r), idx);
+        w.p = ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx);
+        if constexpr (!LATE_X) w.x = ldv<XA, L>(xacc(sd), idx);
         return w;
     }
     template <int L>
@@ -488,24 +525,24 @@ struct ProCG {
                 cx<XA> xv = w.x;
                 xv.x += (XA)sc.alpha * (XA)po.x;
                 xv.y += (XA)sc.alpha * (XA)po.y;
-                st2<XA>(xacc(sd), idx, xv);
+                stv<XA, L>(xacc(sd), idx, xv);
             }
         }
-        st2<W>(reinterpret_cast<W*>(sd.p), idx, p2);
+        stv<W, L>(reinterpret_cast<W*>(sd.p), idx, p2);
         return p2;
     }
     // the pending x update of a pair, after the transform (LATE_X), in two steps
     static __device__ __forceinline__ bool late_due(const Sc& sc) { return !sc.restart && sc.alpha != W(0); }
     template <int L>
     static __device__ __forceinline__ cx<XA> late_fetch(const SlotDesc& sd, int row, int col) {
-        return ld2<XA>(xacc(sd), (unsigned)row * L + col);
+        return ldv<XA, L>(xacc(sd), (unsigned)row * L + col);
     }
     template <int L>
     static __device__ __forceinline__ void late(const SlotDesc& sd, const Sc& sc, const Raw& w, cx<XA> xv, int row,
                                                 int col) {
         xv.x += (XA)sc.alpha * (XA)w.p.x;
         xv.y += (XA)sc.alpha * (XA)w.p.y;
-        st2<XA>(xacc(sd), (unsigned)row * L + col, xv);
+        stv<XA, L>(xacc(sd), (unsigned)row * L + col, xv);
     }
 };
 
@@ -536,7 +573,7 @@ struct ProCheck {
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Raw{ld2<double>(sd.x, idx), ld2<float>(sd.e, idx), ld2<W>(reinterpret_cast<const W*>(sd.p), idx)};
+        return Raw{ldv<double, L>(sd.x, idx), ldv<float, L>(sd.e, idx), ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx)};
     }
     template <int L>
     static __device__ __forceinline__ cx<double> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
@@ -546,7 +583,7 @@ struct ProCheck {
         if (sc.mixed) {
             xv.x += (double)w.e.x;
             xv.y += (double)w.e.y;
-            st2<float>(sd.e, idx, mkc(0.0f, 0.0f));
+            stv<float, L>(sd.e, idx, mkc(0.0f, 0.0f));
         }
         if (sc.alpha != 0.0) {
             xv.x += sc.alpha * (double)w.p.x;
@@ -555,7 +592,7 @@ struct ProCheck {
         const Mask2 mk = mask2(sd, idx);  // broken entries carry no force
         xv.x *= mk.m0;
         xv.y *= mk.m1;
-        st2<double>(sd.x, idx, xv);
+        stv<double, L>(sd.x, idx, xv);
         return xv;
     }
 };
@@ -626,8 +663,8 @@ struct ProPCG {
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Raw{ld2<W>(reinterpret_cast<const W*>(sd.z), idx), ld2<W>(reinterpret_cast<const W*>(sd.p), idx),
-                   ld2<XA>(xacc(sd), idx)};
+        return Raw{ldv<W, L>(reinterpret_cast<const W*>(sd.z), idx), ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx),
+                   ldv<XA, L>(xacc(sd), idx)};
     }
     template <int L>
     static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
@@ -640,9 +677,9 @@ struct ProPCG {
             cx<XA> xv = w.x;
             xv.x += (XA)sc.alpha * (XA)po.x;
             xv.y += (XA)sc.alpha * (XA)po.y;
-            st2<XA>(xacc(sd), idx, xv);
+            stv<XA, L>(xacc(sd), idx, xv);
         }
-        st2<W>(reinterpret_cast<W*>(sd.p), idx, p2);
+        stv<W, L>(reinterpret_cast<W*>(sd.p), idx, p2);
         return p2;
     }
 };
@@ -692,14 +729,14 @@ struct ProUpdPre {
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Raw{ld2<W>(reinterpret_cast<const W*>(sd.r), idx), ld2<W>(reinterpret_cast<const W*>(sd.q), idx)};
+        return Raw{ldv<W, L>(reinterpret_cast<const W*>(sd.r), idx), ldv<W, L>(reinterpret_cast<const W*>(sd.q), idx)};
     }
     template <int L>
     static __device__ __forceinline__ cx<W> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
                                                     int col, double* acc) {
         const unsigned idx = (unsigned)row * L + col;
         const cx<W> rn = mkc(w.r.x - sc.alpha * w.q.x, w.r.y - sc.alpha * w.q.y);
-        st2<W>(reinterpret_cast<W*>(sd.r), idx, rn);
+        stv<W, L>(reinterpret_cast<W*>(sd.r), idx, rn);
         acc[0] += (double)rn.x * (double)rn.x + (double)rn.y * (double)rn.y;
         return rn;
     }
@@ -718,7 +755,7 @@ struct ProPre {
     static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh&, Sc&, int, int) { return GatePre::ok(sd); }
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
-        return ld2<W>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col);
+        return ldv<W, L>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col);
     }
     template <int L>
     static __device__ __forceinline__ cx<W> combine(const SlotDesc&, const Sc&, const Raw& w, int, int, double*) {
@@ -745,7 +782,7 @@ struct EpiApply {
     template <int L>
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Pre{ld2<double>(sd.d, idx), ld2<double>(sd.x, idx)};
+        return Pre{ldv<double, L>(sd.d, idx), ldv<double, L>(sd.x, idx)};
     }
     template <int L>
     static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, T c0, T c1, const Pre& pr,
@@ -773,11 +810,11 @@ struct EpiCG {
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
         Pre v;
-        v.p = ld2<W>(reinterpret_cast<const W*>(sd.p), idx);
+        v.p = ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx);
         if constexpr (sizeof(W) == 4) {
-            v.d = ld2<float>(sd.d32, idx);
+            v.d = ldv<float, L>(sd.d32, idx);
         } else {
-            v.d = ld2<double>(sd.d, idx);
+            v.d = ldv<double, L>(sd.d, idx);
         }
         return v;
     }
@@ -1014,8 +1051,8 @@ struct EpiCheck {
     template <int L>
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Pre{ld2<double>(sd.x, idx), ld2<double>(sd.b, idx), ld2<double>(sd.d, idx),
-                   ld2<W>(reinterpret_cast<const W*>(sd.r), idx),
+        return Pre{ldv<double, L>(sd.x, idx), ldv<double, L>(sd.b, idx), ldv<double, L>(sd.d, idx),
+                   ldv<W, L>(reinterpret_cast<const W*>(sd.r), idx),
                    *gbl(&sd.st->checks)};  // 0: the first check has no recursive residual yet
     }
     template <int L>
@@ -1041,7 +1078,7 @@ struct EpiPre {
     };
     template <int L>
     static __device__ __forceinline__ Pre pre(const SlotDesc& sd, int row, int col) {
-        return Pre{ld2<W>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col)};
+        return Pre{ldv<W, L>(reinterpret_cast<const W*>(sd.r), (unsigned)row * L + col)};
     }
     template <int L>
     static __device__ __forceinline__ void out2p(const SlotDesc& sd, int row, int col, W c0, W c1, const Pre& pr,
@@ -1119,7 +1156,7 @@ __device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& 
         cx<T> out = mkc(T(0.5) * (s1.x + wd.y), T(0.5) * (s1.y - wd.x));
         // (k = 0 is among the first tiles: s = 0 alone, without a branch)
         if ((s == 0 || NT < TT * RPW) && k == 0) out = mkc(Zk.x + Zk.y, Zk.x - Zk.y);
-        gst(Wb, ((unsigned)kt * L + rb * RPW + il) * TT + kk, out);
+        gst(Wb, (unsigned)kt * G::WT + (rb * RPW + il) * TT + kk, out);
     }
 }
 
@@ -1221,7 +1258,7 @@ __global__ void __launch_bounds__(NT) k_col(Tab<T> tab, Slot slot) {
         kk = i % TT;
     }
     Lay lay{lds, kl};
-    cx<T>* Wt = reinterpret_cast<cx<T>*>(sd.W) + (size_t)kt * L * TT;
+    cx<T>* Wt = reinterpret_cast<cx<T>*>(sd.W) + (size_t)kt * G::WT;
     cx<T> v[E];
     constexpr int NSTG = fft_nstages(M);
     constexpr int R1 = fft_radix(M, false, 0);
@@ -1486,7 +1523,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
         const int kk = qi % TT;
         const int il = (qi / TT) % RPW;
         const int kt = qi / (TT * RPW);
-        wv[s] = gld(Wb, ((unsigned)kt * L + row0 + il) * TT + kk);
+        wv[s] = gld(Wb, (unsigned)kt * G::WT + (row0 + il) * TT + kk);
     }
     constexpr int NSTG = fft_nstages(N);
     constexpr int R1 = NSTG > 0 ? fft_radix(N, true, 0) : 1;
@@ -1756,12 +1793,13 @@ k_row_turn_pcg(Tab<T> tab, Slot slot, int stride, unsigned long long token) {
 
 // r <- r - alpha q, partial r . r.  alpha = rho / (p . q) from the partials
 // of the row-inverse pass (all blocks reduce them in the same order).
-template <typename W, int NT>
+// L: the grid (n = L L).
+template <typename W, int NT, int L>
 __global__ void __launch_bounds__(NT) k_update(ByPtr slot, int n, int npart_pq, int stride) {
     __shared__ double red[(NT + 63) / 64];
     const SlotDesc& sd = slot.get();
     if (!GateIter::ok(sd)) return;
-    SolveState* st = sd.st;
+    auto* st = gbl(sd.st);
     constexpr int VW = sizeof(W) == 4 ? 4 : 2;
     using V = typename VecT<W, VW>::type;
     const int nv = n / VW;
@@ -1770,18 +1808,28 @@ __global__ void __launch_bounds__(NT) k_update(ByPtr slot, int n, int npart_pq, 
     const int hi = lo + per < nv ? lo + per : nv;
     auto* r = gbl(reinterpret_cast<V*>(sd.r));
     const auto* q = gbl(reinterpret_cast<const V*>(sd.q));
-    // the first PF vectors of r and q are requested before the p.q reduction
-    // so its latency overlaps the HBM reads
+    // PF vectors of r and q at a time: the first before the p.q reduction, so
+    // its latency overlaps the HBM reads, each of the others before the stores
+    // of those before it
     constexpr int PF = 4;
+    auto ld = [](const auto* v) {
+        if constexpr (kStream<L>)
+            return __builtin_nontemporal_load(v);
+        else
+            return *v;
+    };
     V rp[PF], qp[PF];
+    auto fetch = [&](int i0) {
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-        const int i = lo + threadIdx.x + u * NT;
-        if (i < hi) {
-            rp[u] = r[i];
-            qp[u] = q[i];
+        for (int u = 0; u < PF; ++u) {
+            const int i = i0 + u * NT;
+            if (i < hi) {
+                rp[u] = ld(r + i);
+                qp[u] = ld(q + i);
+            }
         }
-    }
+    };
+    fetch(lo + threadIdx.x);
     const double pq = sum_partials<NT>(sd.part + PS_PQ * stride, npart_pq, red);
     const double rho = st->rho_cur;
     if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rho)) {
@@ -1815,12 +1863,21 @@ __global__ void __launch_bounds__(NT) k_update(ByPtr slot, int n, int npart_pq, 
         }
         return rv;
     };
+    for (int i0 = lo + threadIdx.x; i0 < hi; i0 += PF * NT) {
+        V rn[PF];
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-        const int i = lo + threadIdx.x + u * NT;
-        if (i < hi) r[i] = upd(rp[u], qp[u]);
+        for (int u = 0; u < PF; ++u)
+            if (i0 + u * NT < hi) rn[u] = upd(rp[u], qp[u]);
+        fetch(i0 + PF * NT);
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            if (i0 + u * NT >= hi) continue;
+            if constexpr (kStream<L>)
+                __builtin_nontemporal_store(rn[u], r + i0 + u * NT);
+            else
+                r[i0 + u * NT] = rn[u];
+        }
     }
-    for (int i = lo + threadIdx.x + PF * NT; i < hi; i += NT) r[i] = upd(r[i], q[i]);
     const double s = block_sum<NT>(acc, red);
     if (threadIdx.x == 0) sd.part[PS_RR * stride + blockIdx.x] = s;
 }

@@ -54,6 +54,14 @@ struct SolveState {
     long long bar_limit;  // wait limit of the update's grid-wide barrier, ticks of the 100 MHz clock
 };
 
+// Bytes of a workspace's W (FP64 at most): the half spectrum, and room for
+// kWPad bytes after every column, hence after every tile of columns.
+constexpr size_t kWPad = 128;
+constexpr size_t w_bytes(int L, int M) {
+    const size_t N = (size_t)M / 2;
+    return N * L * 16 + N * kWPad < 256 ? 256 : N * L * 16 + N * kWPad;
+}
+
 // Internal solve status (never returned to callers): a grid-wide barrier
 // gave up waiting, so the host repeats the solve without it.
 constexpr int ST_EGRID = -100;
