@@ -82,11 +82,11 @@ def bytes_model(L, M):
 def pass_kernels(M):
     """Kernel names (as the rocprofv3 summary lists them) of the FP32 CG
     iteration's passes on an M-grid with zero padding."""
-    return dict(row_fwd=f"k_row_fwd<float, {M}, 1, ProCG<float, float, 256>, ByPtr, 256>",
+    return dict(row_fwd=f"k_row_fwd<float, {M}, 1, ProCG<float, float, 256, true>, ByPtr, 256>",
                 col=f"k_col<float, {M}, 1, GateIter, ByPtr, 512, false>",
                 row_inv=f"k_row_inv<float, {M}, 1, EpiCG<float>, ByPtr, 256>",
                 row_inv_upd=f"k_row_inv_upd<float, {M}, 1, ByPtr, 256>",
-                update="k_update<float, 256>",
+                update=f"k_update<float, 256, {M // 2}>",
                 turn=f"k_row_turn<float, {M}, 1, ByPtr, 256>")
 
 
