@@ -84,7 +84,8 @@ struct Geo {
     // largest grid, where a tile takes 140 KB of LDS and leaves one workgroup
     // per CU, whose loads, transform and stores then run one after another.
     // Two workgroups of a column each overlap them (M = 8192 FP32: column
-    // pass 137 -> 105 us); W keeps its pairs, for the row passes' 32-byte
+    // pass 137 -> 115 us; at M = 4096, where two workgroups of a tile fit, 24.5 ->
+    // 26.4, so not there); W keeps its pairs, for the row passes' 32-byte
     // runs (with tiles of one column the row passes lost 33 us).
     static constexpr int CT = (M >= 8192 && TT > 1) ? 1 : TT;
     // a tile of W; on the largest grid with 128 bytes behind it: a row's
@@ -1129,8 +1130,10 @@ __device__ __forceinline__ void row_fwd_out(cx<T>* v, cx<T>* lds, const Tab<T>& 
     fft_run<T, N, M, -1, false, PAD != 0>(v, lay, j, tab.tw);
     constexpr int RL = NSTG > 0 ? fft_radix(N, false, NSTG - 1) : 1;
     // the unpack's twiddles, all of them before the first W store: a read
-    // behind a store waits for the store to complete, and sixteen such round
-    // trips in a row had been a third of the pass
+    // behind a store waits for the store to complete, sixteen times in a row.
+    // With the operands likewise (fetch, combine) the turn pass at M = 4096
+    // went from 47.4 to 41.5 us, FP64 check passes from 42.7 and 53.5 to 37.3
+    // and 43.2
     cx<T> twk[E];
 #pragma unroll
     for (int s = 0; s < E; ++s) {
