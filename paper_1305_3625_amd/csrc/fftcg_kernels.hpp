@@ -1549,7 +1549,12 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
     auto col = [&](int i) { return 2 * ((j + (i / RK) * P) + (i % RK) * (N / RL)); };
     // (without the prefetch in groups of up to eight pairs; the check's pairs
     // take 56 bytes, four fit the registers)
-    constexpr int GRP = cmin(NO, sizeof(typename Epi::Pre) > 40 ? 4 : 8);
+    // (with the folded update in FP64 and eight pairs a thread, two: the pairs'
+    // q and r are kept, and the grid has to be resident as a whole, at most 128
+    // VGPRs; with groups of eight the pass took 188, so that periodic L = 2048
+    // had to use the separate update, 7.2 ms a solve instead of 6.8)
+    constexpr bool TIGHT = EpiUpd<Epi>::value && sizeof(T) == 8 && NO >= 8;
+    constexpr int GRP = cmin(NO, TIGHT ? 2 : (sizeof(typename Epi::Pre) > 40 ? 4 : 8));
     typename Epi::Pre pre[PF ? NO : GRP];
     if constexpr (PF) {
 #pragma unroll
@@ -1624,6 +1629,7 @@ __device__ __forceinline__ void row_inv_body(const Tab<T>& tab, const Slot& slot
                 Epi::template out2p<L>(sd, row, col(g + i), c.x, c.y, pre[PF ? g + i : i], acc);
             }
         }
+        if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (UPD) {
         // the parts of r.r, r.q and q.q
