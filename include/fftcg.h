@@ -204,9 +204,30 @@ int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode);
 #define FFTCG_GRID_ON_TURN     4 /* as FFTCG_GRID_ON, with the turn pass    */
 
 /* fftcg_plan_get_grid_sync -- *state = one of FFTCG_GRID_* for solves in
- * `precision` on this plan.  FFTCG_EINVAL for a NULL argument or another
+ * `precision` on this plan: whether the folded update (without a
+ * preconditioner) and its turn pass apply on this grid.  It says nothing
+ * about the resident kernel and the preconditioned turns, and a solve that
+ * runs the resident kernel uses neither pass; fftcg_plan_get_solve_routes
+ * says what the solves ran.  FFTCG_EINVAL for a NULL argument or another
  * precision.                                                               */
 int fftcg_plan_get_grid_sync(fftcg_plan_t plan, int precision, int* state);
+
+/* What the plan's single solves ran (fftcg_solve, and every step of
+ * fftcg_fracture), counted since the plan was made: each solve counts once,
+ * where its result came from (an attempt abandoned at a barrier does not
+ * count, its repeat does).                                                  */
+typedef struct {
+    unsigned long long fused;     /* the fused engine                         */
+    unsigned long long resident;  /* the resident kernel                      */
+    unsigned long long turn;      /* passes, with the turn pass (or the
+                                     preconditioned turns)                    */
+    unsigned long long folded;    /* passes, with the folded update           */
+    unsigned long long separate;  /* passes, with the separate update         */
+} fftcg_solve_routes;
+
+/* fftcg_plan_get_solve_routes -- *out = the counts so far.  FFTCG_EINVAL for
+ * a NULL argument.                                                         */
+int fftcg_plan_get_solve_routes(fftcg_plan_t plan, fftcg_solve_routes* out);
 
 /* Reports L, M, padded, and the plan's device bytes (any pointer may be NULL). */
 int fftcg_plan_info(fftcg_plan_t plan, int* L, int* M, int* padded, size_t* device_bytes);

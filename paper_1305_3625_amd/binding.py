@@ -30,7 +30,8 @@ STATUS_NAMES = {0: "OK", 1: "PENDING", -1: "EINVAL", -2: "ENOMEM", -3: "ENOTSPD"
 # every symbol include/fftcg.h declares
 EXPORTS = [
     "fftcg_plan", "fftcg_plan_destroy", "fftcg_plan_set_engine", "fftcg_plan_set_precond",
-    "fftcg_plan_set_error_target", "fftcg_plan_set_grid_sync", "fftcg_plan_get_grid_sync", "fftcg_plan_info",
+    "fftcg_plan_set_error_target", "fftcg_plan_set_grid_sync", "fftcg_plan_get_grid_sync", "fftcg_plan_get_solve_routes",
+    "fftcg_plan_info",
     "fftcg_apply", "fftcg_profile_apply", "fftcg_profile_iteration", "fftcg_stream_probe", "fftcg_solve", "fftcg_loadstep", "fftcg_loadstep_noalloc", "fftcg_fracture",
     "fftcg_server_create", "fftcg_submit", "fftcg_submit_sequence", "fftcg_poll",
     "fftcg_poll_sequence", "fftcg_server_completed", "fftcg_server_get_stats", "fftcg_server_reserve", "fftcg_server_class_slots", "fftcg_server_shutdown",
@@ -57,6 +58,10 @@ class Info(ctypes.Structure):
 
     def as_dict(self):
         return {k: getattr(self, k) for k, _ in self._fields_}
+
+
+class SolveRoutes(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_ulonglong) for k in ("fused", "resident", "turn", "folded", "separate")]
 
 
 class ServerOpts(ctypes.Structure):
@@ -101,6 +106,7 @@ def load(path: str = LIB_PATH):
         "fftcg_plan_set_error_target": (I, [P, I, D]),
         "fftcg_plan_set_grid_sync": (I, [P, I]),
         "fftcg_plan_get_grid_sync": (I, [P, I, ctypes.POINTER(I)]),
+        "fftcg_plan_get_solve_routes": (I, [P, ctypes.POINTER(SolveRoutes)]),
         "fftcg_plan_info": (I, [P, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(I),
                                 ctypes.POINTER(S)]),
         "fftcg_apply": (I, [P, I, P, P, P, P]),
@@ -236,6 +242,15 @@ class Plan:
         if st != OK:
             raise FftcgError(st, "fftcg_plan_get_grid_sync")
         return v.value
+
+    def solve_routes(self):
+        """Single solves so far by what they ran: a dict of the counts
+        fused, resident, turn, folded, separate."""
+        r = SolveRoutes()
+        st = load().fftcg_plan_get_solve_routes(self.h, ctypes.byref(r))
+        if st != OK:
+            raise FftcgError(st, "fftcg_plan_get_solve_routes")
+        return {k: int(getattr(r, k)) for k, _ in SolveRoutes._fields_}
 
     def info(self):
         L, M, p = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()

@@ -422,6 +422,16 @@ extern "C" int fftcg_plan_get_grid_sync(fftcg_plan_t plan, int precision, int* s
     return FFTCG_OK;
 } FFTCG_ABI_CATCH
 
+extern "C" int fftcg_plan_get_solve_routes(fftcg_plan_t plan, fftcg_solve_routes* out) try {
+    if (!plan || !out) return FFTCG_EINVAL;
+    out->fused = plan->routes[ROUTE_FUSED].load();
+    out->resident = plan->routes[ROUTE_RESIDENT].load();
+    out->turn = plan->routes[ROUTE_TURN].load();
+    out->folded = plan->routes[ROUTE_FOLDED].load();
+    out->separate = plan->routes[ROUTE_SEPARATE].load();
+    return FFTCG_OK;
+} FFTCG_ABI_CATCH
+
 extern "C" int fftcg_plan_info(fftcg_plan_t plan, int* L, int* M, int* padded, size_t* device_bytes) try {
     if (!plan) return FFTCG_EINVAL;
     if (L) *L = plan->L;
@@ -882,6 +892,7 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
         if (hold.held() && resident_words(w, s)) {
             const int rc = solve_resident(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, hold.first());
             if (rc != ST_EGRID) {
+                plan->routes[ROUTE_RESIDENT] += 1;
                 plan_release(plan, w);
                 return rc;
             }
@@ -906,7 +917,10 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
         hipMemcpyAsync(w->q, x, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
         grid = false;
     rc = solve_multipass_once(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, grid);
+    Route route = ROUTE_SEPARATE;
+    if (grid) route = plan->precond != FFTCG_PRECOND_NONE || plan_turn(plan, precision) ? ROUTE_TURN : ROUTE_FOLDED;
     if (rc == ST_EGRID) {
+        route = ROUTE_SEPARATE;
         // the grid was not resident as a whole (other work on the device):
         // the plan falls back to the separate update kernel, and the solve
         // is repeated from its start
@@ -918,6 +932,7 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
             rc = solve_multipass_once(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, false);
         if (rc == ST_EGRID) rc = FFTCG_EDEVICE;
     }
+    plan->routes[route] += 1;
     plan_release(plan, w);
     return rc;
 }

@@ -75,6 +75,7 @@ int solve_validate(fftcg_plan_t plan, int precision, const void* d, const void* 
 
 namespace fftcg {
 struct FusedOps;
+enum Route { ROUTE_FUSED, ROUTE_RESIDENT, ROUTE_TURN, ROUTE_FOLDED, ROUTE_SEPARATE, ROUTES };
 }
 
 struct fftcg_plan_s {
@@ -117,6 +118,8 @@ struct fftcg_plan_s {
     // asked yet (the first solve does), 0 no, 1 yes
     std::atomic<int> res_cap[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};
     std::atomic<int> grid_broken{0};
+    // single solves by what they ran (fftcg_solve_routes, in its order)
+    std::atomic<unsigned long long> routes[fftcg::ROUTES] = {};
     std::mutex mu;
     std::vector<fftcg::Workspace*> free_ws;
     std::vector<fftcg::Workspace*> all_ws;

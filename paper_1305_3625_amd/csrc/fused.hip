@@ -148,6 +148,7 @@ int fused_solve(fftcg_plan_s* p, int precision, const double* d, const double* b
             info->device_ms = ms;
         }
     } while (0);
+    p->routes[ROUTE_FUSED] += 1;
     plan_release(p, w);
     return rc;
 }
