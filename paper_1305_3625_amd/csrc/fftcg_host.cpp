@@ -881,14 +881,21 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
                                 const double* x0, double tol, int maxit, double* x, fftcg_info* info,
                                 hipStream_t s, const uint8_t* mask, bool grid);
 
+// small: a solve of AUTO on a grid of the fused engine (M <= 64).  Where the
+// resident kernel finds no room, or a meeting gives up, the fused engine takes
+// it: one workgroup, no meetings, and faster than the passes there (periodic
+// M = 64 FP64 476 us, 759 as passes).
 static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, const double* b, const double* x0,
                            double tol, int maxit, double* x, fftcg_info* info, hipStream_t s,
-                           const uint8_t* mask = nullptr) {
-    Workspace* w = plan_acquire(plan);
-    if (!w) return FFTCG_ENOMEM;
+                           const uint8_t* mask = nullptr, bool small = false) {
+    Workspace* w = nullptr;
     const size_t n = (size_t)plan->L * plan->L;
     if (plan_resident(plan, precision)) {
         XcdHold hold(plan->device, plan->ops->resident_xcds(precision));
+        if (hold.held()) {
+            w = plan_acquire(plan);
+            if (!w) return FFTCG_ENOMEM;
+        }
         if (hold.held() && resident_words(w, s)) {
             const int rc = solve_resident(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, hold.first());
             if (rc != ST_EGRID) {
@@ -905,6 +912,14 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
             }
         }
     }
+    if (small) {
+        // (w is given back after the solve, which waits for the copy from w->q)
+        const int rc = fused_solve(plan, precision, d, b, x0, tol, maxit, x, info, s);
+        if (w) plan_release(plan, w);
+        return rc;
+    }
+    if (!w) w = plan_acquire(plan);
+    if (!w) return FFTCG_ENOMEM;
     // the folded update (any mode but 0), or the preconditioned turns (1, 2)
     bool grid = !plan->grid_broken.load() &&
                 (plan->precond == FFTCG_PRECOND_NONE
@@ -1050,11 +1065,11 @@ extern "C" int fftcg_solve(fftcg_plan_t plan, int precision, const double* d, co
     // 1e-10, fused -> resident: periodic M = 64 FP64 476 -> 241 us, padded
     // M = 64 467 -> 298 us, periodic M = 32 241 -> 204 us), else the fused
     // engine
-    if (plan_engine(plan) == FFTCG_ENGINE_FUSED &&
-        !(plan->engine == FFTCG_ENGINE_AUTO && plan_resident(plan, precision)))
+    const bool fused = plan_engine(plan) == FFTCG_ENGINE_FUSED;
+    if (fused && !(plan->engine == FFTCG_ENGINE_AUTO && plan_resident(plan, precision)))
         return fused_solve(plan, precision, d, b, x0, tol, maxit, x, info, s);
     if (!plan->ops) return FFTCG_EINVAL;
-    return solve_multipass(plan, precision, d, b, x0, tol, maxit, x, info, s);
+    return solve_multipass(plan, precision, d, b, x0, tol, maxit, x, info, s, nullptr, fused);
 } FFTCG_ABI_CATCH
 
 // ---- load step ---------------------------------------------------------------

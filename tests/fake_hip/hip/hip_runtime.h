@@ -1,9 +1,10 @@
 /*
  * Test double of the HIP runtime for host-only builds of the server
- * (tests/test_server_fake.py): the scheduler's own code, compiled with g++
- * against these declarations and linked with tests/fake_hip/fake_exec.cpp,
- * runs on the CPU with a simulated device.  Only what server.cpp and the
- * headers it includes use is declared.  Not part of the product library.
+ * (tests/test_server_fake.py) and of the solves (tests/test_host_fake.py):
+ * the library's own host code, compiled with g++ against these declarations
+ * and linked with fake_exec.cpp or fake_host.cpp, runs on the CPU with a
+ * simulated device.  Only what those sources and the headers they include
+ * use is declared.  Not part of the product library.
  */
 #ifndef FFTCG_FAKE_HIP_RUNTIME_H
 #define FFTCG_FAKE_HIP_RUNTIME_H
@@ -71,6 +72,18 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s);
 hipError_t hipEventQuery(hipEvent_t e);
 hipError_t hipEventDestroy(hipEvent_t e);
 hipError_t hipGetDeviceCount(int* n);
+// (the solves' host code, fake_host.cpp)
+struct hipDeviceProp_t {
+    char gcnArchName[256];
+};
+hipError_t hipGetDevice(int* d);
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int d);
+hipError_t hipDeviceSynchronize();
+hipError_t hipMemset(void* dst, int v, size_t n);
+hipError_t hipEventCreate(hipEvent_t* e);
+hipError_t hipEventSynchronize(hipEvent_t e);
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b);
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 hipError_t hipSetDevice(int d);
 hipError_t hipGetLastError();
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode mode);

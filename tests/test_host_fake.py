@@ -1,0 +1,173 @@
+"""The host side of plans and single solves (paper_1305_3625_amd/csrc/
+fftcg_host.cpp and fused.hip, unmodified) on a simulated device, on the CPU
+(tests/fake_hip/fake_host.cpp): which route a solve takes when others are in
+flight or a meeting gives up.  A solve is held in flight by blocking inside
+its launch."""
+
+import ctypes
+import os
+import subprocess
+import threading
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+BUILD = os.path.join(ROOT, "_build", "fake")
+P, I, D, S = ctypes.c_void_p, ctypes.c_int, ctypes.c_double, ctypes.c_size_t
+FP64, MIXED = 0, 1
+APPLY, RESIDENT, CHUNK, SEPARATE, FUSED = range(5)
+ROUTES = ("fused", "resident", "turn", "folded", "separate")
+HOOK = ctypes.CFUNCTYPE(None, I, I, I)
+
+
+class Info(ctypes.Structure):
+    _fields_ = [("status", I), ("iterations", I), ("iterations_literal", I), ("checks", I),
+                ("true_relres", D), ("error_bound", D), ("lambda_lb", D), ("device_ms", D)]
+
+
+class Fake:
+    def __init__(self):
+        os.makedirs(BUILD, exist_ok=True)
+        out = os.path.join(BUILD, "libfftcg_host_fake.so")
+        csrc = os.path.join(ROOT, "paper_1305_3625_amd", "csrc")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-Wall", "-Wno-unused-function",
+                        "-I" + os.path.join(ROOT, "tests", "fake_hip"), "-I" + os.path.join(ROOT, "include"),
+                        "-I" + csrc, os.path.join(csrc, "fftcg_host.cpp"),
+                        os.path.join(ROOT, "tests", "fake_hip", "fake_host.cpp"), "-x", "c++",
+                        os.path.join(csrc, "fused.hip"), "-o", out, "-lpthread"], check=True)
+        self.lib = lib = ctypes.CDLL(out)
+        lib.fftcg_plan.argtypes = [I, I, P, ctypes.POINTER(P)]
+        lib.fftcg_plan_destroy.argtypes = [P]
+        for n in ("fftcg_plan_set_engine", "fftcg_plan_set_precond", "fftcg_plan_set_grid_sync"):
+            getattr(lib, n).argtypes = [P, I]
+        lib.fftcg_plan_get_grid_sync.argtypes = [P, I, ctypes.POINTER(I)]
+        lib.fftcg_plan_get_solve_routes.argtypes = [P, P]
+        lib.fftcg_plan_info.argtypes = [P, P, P, P, ctypes.POINTER(S)]
+        lib.fftcg_apply.argtypes = [P, I, P, P, P, P]
+        lib.fftcg_solve.argtypes = [P, I, P, P, P, D, I, P, ctypes.POINTER(Info), P]
+        lib.fake_fail_memset.argtypes = [S]
+        lib.fake_meet_bytes.restype = S
+        lib.fake_set_hook.argtypes = [P]
+        self.gates = {}  # thread -> (kind, entered, go on)
+        self.hook = HOOK(self._hook)
+        lib.fake_set_hook(ctypes.cast(self.hook, P))
+
+    def _hook(self, kind, M, precision):
+        g = self.gates.get(threading.get_ident())
+        if g is not None and (g[0] is None or g[0] == kind) and not g[1].is_set():
+            g[1].set()
+            assert g[2].wait(20)
+
+    def plan(self, L, padded, precond=0):
+        M = 2 * L if padded else L
+        h = P()
+        g = np.ones((M, M))
+        assert self.lib.fftcg_plan(L, padded, g.ctypes.data_as(P), ctypes.byref(h)) == 0
+        assert self.lib.fftcg_plan_set_precond(h, precond) == 0
+        return Plan(self, h, L)
+
+
+class Plan:
+    def __init__(self, fake, h, L):
+        self.f, self.lib, self.h, self.L = fake, fake.lib, h, L
+
+    def routes(self):
+        r = (ctypes.c_ulonglong * 5)()
+        assert self.lib.fftcg_plan_get_solve_routes(self.h, r) == 0
+        return dict(zip(ROUTES, r))
+
+    def solve(self, precision=MIXED, in_place=False, stream=None):
+        """Solves with a right-hand side of ones; returns the route taken."""
+        n = self.L * self.L
+        d, b = np.ones(n), np.ones(n)
+        x = np.full(n, 7.0) if in_place else np.zeros(n)
+        info = Info()
+        p = lambda a: a.ctypes.data_as(P)  # noqa: E731
+        before = self.routes()
+        st = self.lib.fftcg_solve(self.h, precision, p(d), p(b), p(x) if in_place else None, 1e-8, 100, p(x),
+                                  ctypes.byref(info), stream)
+        assert st == 0 and info.status == 0 and (x == 0.5).all()
+        after = self.routes()
+        return [k for k in ROUTES if after[k] > before[k]]
+
+    def close(self):
+        assert self.lib.fftcg_plan_destroy(self.h) == 0
+
+
+class InFlight:
+    """A call in a thread of its own, held inside its first launch of `kind`
+    (None: of any)."""
+
+    def __init__(self, fake, call, kind=None):
+        self.fake, self.call, self.kind = fake, call, kind
+        self.entered, self.go, self.out = threading.Event(), threading.Event(), None
+
+    def _run(self):
+        self.fake.gates[threading.get_ident()] = (self.kind, self.entered, self.go)
+        try:
+            self.out = self.call()
+        finally:
+            self.fake.gates.pop(threading.get_ident())
+            self.entered.set()
+
+    def __enter__(self):
+        self.t = threading.Thread(target=self._run)
+        self.t.start()
+        assert self.entered.wait(20)
+        return self
+
+    def __exit__(self, *a):
+        self.go.set()
+        self.t.join()
+
+
+@pytest.fixture(scope="module")
+def fake():
+    return Fake()
+
+
+@pytest.mark.parametrize("L,padded,precond,want", [(64, 0, 0, "resident"), (16, 0, 0, "fused"), (128, 1, 0, "resident"),
+                                                   (512, 1, 1, "resident"), (1024, 1, 0, "turn"),
+                                                   (2048, 1, 1, "turn"), (8, 1, 1, "separate")])
+def test_alone(fake, L, padded, precond, want):
+    p = fake.plan(L, padded, precond)
+    assert p.solve() == [want]
+    p.close()
+
+
+def test_small_solve_without_room_is_fused(fake):
+    """AUTO at M <= 64: nine solves at once, and one beside a solve that has
+    the whole device, leave no XCD; the fused engine needs none."""
+    p = fake.plan(64, 0)
+    held = [InFlight(fake, p.solve, RESIDENT).__enter__() for _ in range(8)]
+    try:
+        assert p.solve(FP64) == ["fused"]
+    finally:
+        for h in held:
+            h.__exit__()
+    assert p.routes()["resident"] == 8
+    q = fake.plan(512, 1)
+    with InFlight(fake, q.solve, RESIDENT):
+        assert p.solve() == ["fused"]
+    assert p.solve() == ["resident"]
+    p.close()
+    q.close()
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+def test_small_solve_that_gave_up_is_fused(fake, in_place):
+    """A meeting that gave up: the repeat is the fused engine's, and so are
+    the plan's later solves."""
+    p = fake.plan(32, 1)
+    fake.lib.fake_give_up(1)
+    try:
+        assert p.solve(in_place=in_place) == ["fused"]
+    finally:
+        fake.lib.fake_give_up(0)
+    assert p.solve() == ["fused"]
+    st = I()
+    assert fake.lib.fftcg_plan_get_grid_sync(p.h, MIXED, ctypes.byref(st)) == 0 and st.value == 3
+    assert fake.lib.fftcg_plan_set_grid_sync(p.h, 1) == 0
+    assert p.solve() == ["resident"]
+    p.close()
