@@ -66,8 +66,9 @@ extern "C" {
 /* ---- engines (fftcg_plan_set_engine) -----------------------------------
  * AUTO     : the fused engine for M <= 64 in products and in single solves
  *            (there only where the multi-pass engine's resident kernel,
- *            fftcg_plan_set_grid_sync, does not apply) and for M <= 128 in
- *            server classes, the multi-pass engine above.
+ *            fftcg_plan_set_grid_sync, does not apply, finds no room or
+ *            gives up) and for M <= 128 in server classes, the multi-pass
+ *            engine above.
  * MULTIPASS: three HBM passes per product (row R2C, column FFT*ghat*IFFT,
  *            row C2R + epilogue); every grid.
  * FUSED    : one workgroup per solve, whole CG loop in one kernel, the
@@ -181,9 +182,17 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          in one resident kernel instead, checks included, with bitwise the
  *          result of mode 3: r, p, x and d stay in registers, and the
  *          workgroups of one XCD (M <= 256) or of the whole device meet three
- *          times per product.  At most one such kernel per XCD, or one on the
- *          whole device, runs at a time in a process; a solve that finds no
- *          room runs the passes.
+ *          times per product.  Such a solve holds its XCD (or the device)
+ *          until it ends, so it starts only where an XCD (the whole device)
+ *          is free of others of this process, and no other solve's passes,
+ *          server at work or product of another stream is in flight; beside
+ *          passes of solves of its own kind it may start on the grids where
+ *          they run on undisturbed (M <= 512, and FP32 without a
+ *          preconditioner at M = 1024).  A solve that finds no room runs the
+ *          passes, with the same result; with AUTO at M <= 64 the fused
+ *          engine.  A grid-wide barrier is used where its grid fits the
+ *          device beside the grids of the barriers in flight, else this
+ *          solve runs the separate update.
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.

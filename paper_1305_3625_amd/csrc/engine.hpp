@@ -65,9 +65,9 @@ struct EngineOps {
     // records ev0 as the kernel starts and ev1 as it ends
     void (*iter_pass)(int prec, int pass, bool grid, const PlanTabs& t, const SlotDesc* slot, int stride,
                       unsigned long long token, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
-    // whether the folded update (below) applies on the current device: the
-    // whole row-inverse grid resident at once
-    bool (*grid_capable)(int prec);
+    // whether the folded update (below) applies on the current device: how
+    // many whole row-inverse grids are resident at once (0: not one)
+    int (*grid_capable)(int prec);
     // K (>= 1) CG iterations of a single slot, as a chunk, with the update
     // folded into the row-inverse pass behind a grid-wide barrier.  With
     // turn, the row-inverse pass of every iteration but the last goes on into
@@ -77,16 +77,15 @@ struct EngineOps {
     // launches use (each unique on the slot's partial-sum buffer).
     void (*iter_grid_chunk)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride,
                             unsigned long long* token, int K, bool turn, hipStream_t s);
-    // whether the turn pass is resident as a whole as well (implies
-    // grid_capable)
-    bool (*turn_capable)(int prec);
+    // the same of the turn pass
+    int (*turn_capable)(int prec);
     // K preconditioned iterations of a single slot as a chunk, with the two
     // turns behind grid-wide barriers: row_fwd, (col, turn, col) with a turn
     // between them, row_inv.  *token as above.
     void (*iter_pcg_chunk)(int prec, const PlanTabs& t, const SlotDesc* slot, int stride, unsigned long long* token,
                            int K, hipStream_t s);
-    // whether that is built and resident as a whole
-    bool (*turn_pcg_capable)(int prec);
+    // the same of these two (0 also where they are not built)
+    int (*turn_pcg_capable)(int prec);
     // a single solve, or K of its iterations, in one launch
     // (k_solve_resident); pcg: with the circulant preconditioner.  st: the
     // state it begins with (run.first), else taken from the slot's.

@@ -178,39 +178,39 @@ void iter_pass_fn(int prec, int pass, bool grid, const PlanTabs& pt, const SlotD
         iter_pass_t<float>(pass, grid, pt, slot, stride, token, e0, e1, s);
 }
 
-// whether every workgroup of kernel `kern` (RB of RT threads) can be
-// resident at once on the current device
+// how many grids of kernel `kern` (RB workgroups of RT threads) can be
+// resident as a whole at once on the current device
 template <int RT, int RB>
-bool whole_grid_resident(const void* kern) {
+int whole_grids_resident(const void* kern) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return false;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, RT, 0) != hipSuccess) return false;
-    return (long)per_cu * cus >= RB;
+        return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, RT, 0) != hipSuccess) return 0;
+    return per_cu * cus / RB;
 }
 
 template <typename W>
-bool grid_capable_t() {
+int grid_capable_t() {
     constexpr int RT = G<W>::ROW_THREADS, RB = G<W>::ROW_BLOCKS;
-    return whole_grid_resident<RT, RB>(reinterpret_cast<const void*>(k_row_inv_upd<W, M, PAD, ByPtr, RT>));
+    return whole_grids_resident<RT, RB>(reinterpret_cast<const void*>(k_row_inv_upd<W, M, PAD, ByPtr, RT>));
 }
 
-bool grid_capable_fn(int prec) {
+int grid_capable_fn(int prec) {
     return prec == 0 ? grid_capable_t<double>() : grid_capable_t<float>();
 }
 
 template <typename W>
-bool turn_capable_t() {
+int turn_capable_t() {
     constexpr int RT = G<W>::ROW_THREADS, RB = G<W>::ROW_BLOCKS;
     if constexpr (!kTurnBuilt<W>)
-        return false;
+        return 0;
     else
-        return grid_capable_t<W>() &&
-               whole_grid_resident<RT, RB>(reinterpret_cast<const void*>(k_row_turn<W, M, PAD, ByPtr, RT>));
+        return cmin(grid_capable_t<W>(),
+                    whole_grids_resident<RT, RB>(reinterpret_cast<const void*>(k_row_turn<W, M, PAD, ByPtr, RT>)));
 }
 
-bool turn_capable_fn(int prec) {
+int turn_capable_fn(int prec) {
     return prec == 0 ? turn_capable_t<double>() : turn_capable_t<float>();
 }
 
@@ -280,7 +280,7 @@ bool resident_capable_t(bool pcg) {
         const void* k = pcg ? reinterpret_cast<const void*>(k_solve_resident<W, M, PAD, R::NT, true>)
                             : reinterpret_cast<const void*>(k_solve_resident<W, M, PAD, R::NT, false>);
         // on one XCD: an eighth of the CUs
-        return whole_grid_resident<R::NT, R::NB * (R::ONEX ? 8 : 1)>(k);
+        return whole_grids_resident<R::NT, R::NB * (R::ONEX ? 8 : 1)>(k) > 0;
     }
 }
 
@@ -359,19 +359,19 @@ template <typename W>
 constexpr bool kTurnPcgBuilt = !kResBuilt<W> && sizeof(W) == 4 && M >= 2048 && M <= 4096;
 
 template <typename W>
-bool turn_pcg_capable_t() {
+int turn_pcg_capable_t() {
     if constexpr (!kTurnPcgBuilt<W>) {
-        return false;
+        return 0;
     } else {
         constexpr int RT = G<W>::ROW_THREADS, RB = G<W>::ROW_BLOCKS;
-        return whole_grid_resident<RT, RB>(
-                   reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnR<W>, ByPtr, RT>)) &&
-               whole_grid_resident<RT, RB>(
-                   reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnZ<W>, ByPtr, RT>));
+        return cmin(whole_grids_resident<RT, RB>(
+                        reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnR<W>, ByPtr, RT>)),
+                    whole_grids_resident<RT, RB>(
+                        reinterpret_cast<const void*>(k_row_turn_pcg<W, M, PAD, EpiTurnZ<W>, ByPtr, RT>)));
     }
 }
 
-bool turn_pcg_capable_fn(int prec) {
+int turn_pcg_capable_fn(int prec) {
     return prec == 0 ? turn_pcg_capable_t<double>() : turn_pcg_capable_t<float>();
 }
 

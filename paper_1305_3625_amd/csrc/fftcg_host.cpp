@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "device_use.hpp"
 #include "engine.hpp"
 #include "fftcg.h"
 #include "fftcg_internal.hpp"
@@ -175,6 +176,24 @@ int Workspace::init(int L_, int M_, int stride_) {
 using namespace fftcg;
 
 // ---- plan -------------------------------------------------------------------
+// The plans of this process, for the products they have in flight: a product
+// returns before its passes have run, so it is looked for by its event.
+static std::mutex g_plans_mu;
+static std::vector<fftcg_plan_t>& listed_plans() {
+    static auto* v = new std::vector<fftcg_plan_t>();  // (never destroyed: a plan may outlive the statics)
+    return *v;
+}
+
+static void list_plan(fftcg_plan_t plan) {
+    std::lock_guard<std::mutex> lk(g_plans_mu);
+    listed_plans().push_back(plan);
+}
+static void unlist_plan(fftcg_plan_t plan) {
+    std::lock_guard<std::mutex> lk(g_plans_mu);
+    auto& v = listed_plans();
+    v.erase(std::remove(v.begin(), v.end(), plan), v.end());
+}
+
 static int plan_stride(const EngineOps* ops, int L) {
     int s = std::max(64, L);
     if (ops) s = std::max({s, ops->rowblk32, ops->rowblk64, ops->g4});
@@ -267,8 +286,8 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
     if (p->ops) {
         p->grid_cap[0] = p->ops->grid_capable(FFTCG_FP64);
         p->grid_cap[1] = p->ops->grid_capable(FFTCG_MIXED);
-        p->turn_cap[0] = p->grid_cap[0] && p->ops->turn_capable(FFTCG_FP64);
-        p->turn_cap[1] = p->grid_cap[1] && p->ops->turn_capable(FFTCG_MIXED);
+        p->turn_cap[0] = std::min(p->grid_cap[0], p->ops->turn_capable(FFTCG_FP64));
+        p->turn_cap[1] = std::min(p->grid_cap[1], p->ops->turn_capable(FFTCG_MIXED));
         p->turn_pcg_cap[0] = p->ops->turn_pcg_capable(FFTCG_FP64);
         p->turn_pcg_cap[1] = p->ops->turn_pcg_capable(FFTCG_MIXED);
     }
@@ -307,6 +326,7 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
     p->tabs = PlanTabs{p->tw32, p->ghq32, p->ghN32, p->tw64, p->ghq64, p->ghN64};
     p->device_bytes = bytes + p->fused_bytes;
     p->engine = FFTCG_ENGINE_AUTO;
+    list_plan(p);
     *out = owner.release();
     return FFTCG_OK;
 } FFTCG_ABI_CATCH
@@ -315,6 +335,7 @@ extern "C" int fftcg_plan_destroy(fftcg_plan_t plan) try {
     if (!plan) return FFTCG_EINVAL;
     if (plan->refs.load() > 0) return FFTCG_EINVAL;
     (void)hipDeviceSynchronize();
+    unlist_plan(plan);
     delete plan;
     return FFTCG_OK;
 } FFTCG_ABI_CATCH
@@ -399,6 +420,18 @@ static bool plan_resident(fftcg_plan_t plan, int precision) {
     return c != 0;
 }
 
+// Grids of the barrier that solves in `precision` on this plan meet at (the
+// folded update's in any mode but 0, the turns' in modes 1 and 2) that the
+// device holds at once; 0: they run the separate update.
+static int plan_barrier_fits(fftcg_plan_t plan, int precision) {
+    const int m = precision == FFTCG_MIXED;
+    if (plan->grid_broken.load()) return 0;
+    if (plan->precond != FFTCG_PRECOND_NONE)
+        return plan->grid_mode == 1 || plan->grid_mode == 2 ? plan->turn_pcg_cap[m] : 0;
+    if (plan->grid_mode == 0) return 0;
+    return plan_turn(plan, precision) ? plan->turn_cap[m] : plan->grid_cap[m];
+}
+
 extern "C" int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode) try {
     if (!plan) return FFTCG_EINVAL;
     if (mode < 0 || mode > 3) return FFTCG_EINVAL;
@@ -453,6 +486,20 @@ static bool overlap(const void* a, const void* b, size_t n) {
     return x < y + n && y < x + n;
 }
 
+// whether products of another stream than s are in flight on the device (one
+// of s itself comes before the solve)
+static bool applies_in_flight(int device, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(g_plans_mu);
+    for (fftcg_plan_t p : listed_plans()) {
+        if (p->device != device || !p->apply_pending.load() || p->apply_stream.load() == s) continue;
+        const hipError_t e = hipEventQuery(p->apply_ev);
+        if (e != hipSuccess) (void)hipGetLastError();
+        if (e == hipErrorNotReady) return true;
+        p->apply_pending.store(false);
+    }
+    return false;
+}
+
 extern "C" int fftcg_apply(fftcg_plan_t plan, int precision, const double* d, const double* x, double* y,
                            void* stream) try {
     if (!plan || !d || !x || !y) return FFTCG_EINVAL;
@@ -469,6 +516,11 @@ extern "C" int fftcg_apply(fftcg_plan_t plan, int precision, const double* d, co
     plan->ops->apply(precision, plan->tabs, d, x, y, plan->apply_W, s);
     HIPCHK(hipGetLastError());
     HIPCHK(hipEventRecord(plan->apply_ev, s));
+    // (a captured product is not in flight, and its event cannot be queried)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    plan->apply_stream.store(s);
+    plan->apply_pending.store(eager);
     return FFTCG_OK;
 } FFTCG_ABI_CATCH
 
@@ -481,6 +533,8 @@ extern "C" int fftcg_profile_apply(fftcg_plan_t plan, int precision, const doubl
     if (!plan->ops || plan_engine(plan) == FFTCG_ENGINE_FUSED) return FFTCG_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     std::lock_guard<std::mutex> lk(plan->mu);
+    DeviceUse use(plan->device);
+    (void)use.passes(DeviceUse::LARGE, 0);
     hipEvent_t ev[4];
     for (int i = 0; i < 4; ++i)
         if (hipEventCreate(&ev[i]) != hipSuccess) return FFTCG_EDEVICE;
@@ -525,6 +579,8 @@ extern "C" int fftcg_profile_iteration(fftcg_plan_t plan, int precision, const d
     const bool grid = plan->grid_mode != 0 && !plan->grid_broken.load() && plan->grid_cap[precision == FFTCG_MIXED];
     const bool turn = grid && plan_turn(plan, precision);
     if (turn && reps < 2) return FFTCG_EINVAL;
+    DeviceUse use(plan->device);
+    (void)use.passes(DeviceUse::LARGE, grid ? (turn ? plan->turn_cap : plan->grid_cap)[precision == FFTCG_MIXED] : 0);
     // the launches in the order a solve's chunk makes them: with the turn
     // pass row_fwd, col, (turn, col) x (reps - 1), row_inv; else per
     // iteration row_fwd, col, row_inv and (without the folded update) update
@@ -788,39 +844,6 @@ struct ChunkPlanner {
     }
 };
 
-// The XCDs that resident solves of this process hold, per device (a bit
-// each): two resident kernels never wait for each other's workgroups to make
-// room.  A solve that finds none free runs the iteration's passes instead,
-// with bitwise the same result.
-class XcdHold {
-    static constexpr int kDevices = 64;
-    static std::mutex mu_;
-    static unsigned used_[kDevices];
-    int dev_;
-    unsigned mask_ = 0;
-
-public:
-    XcdHold(int dev, int xcds) : dev_(dev) {
-        if (dev < 0 || dev >= kDevices) return;
-        std::lock_guard<std::mutex> lk(mu_);
-        if (xcds == 8) {
-            if (used_[dev] == 0) mask_ = 0xff;
-        } else {
-            for (int i = 0; i < 8 && !mask_; ++i)
-                if (!(used_[dev] & (1u << i))) mask_ = 1u << i;
-        }
-        used_[dev] |= mask_;
-    }
-    ~XcdHold() {
-        if (!mask_) return;
-        std::lock_guard<std::mutex> lk(mu_);
-        used_[dev_] &= ~mask_;
-    }
-    XcdHold(const XcdHold&) = delete;
-    XcdHold& operator=(const XcdHold&) = delete;
-    bool held() const { return mask_ != 0; }
-    int first() const { return mask_ ? __builtin_ctz(mask_) : 0; }
-};
 // The words through which the workspace's resident launches meet, zeroed once
 // (tokens start at 1 and only grow).
 static bool resident_words(Workspace* w, hipStream_t s) {
@@ -833,9 +856,6 @@ static bool resident_words(Workspace* w, hipStream_t s) {
     w->meet = (unsigned long long*)p;
     return hipMemsetAsync(p, 0, kMeetWords * 8, s) == hipSuccess;
 }
-
-std::mutex XcdHold::mu_;
-unsigned XcdHold::used_[XcdHold::kDevices] = {};
 
 // A solve by the resident kernel: one launch, or one per kResidentIters
 // iterations.  The state travels as a kernel argument and comes back at the
@@ -881,6 +901,18 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
                                 const double* x0, double tol, int maxit, double* x, fftcg_info* info,
                                 hipStream_t s, const uint8_t* mask, bool grid);
 
+// Light solves whose passes a resident solve of this plan may start beside
+// (DeviceUse): any number up to M = 512, where the workgroups of every pass
+// fit beside resident ones (112 registers beside at most 394 of 512).  At M =
+// 1024 a workgroup of the FP64 column pass takes 220 registers of a SIMD, and
+// the resident kernel 272 (FP32), 300 (FP32 preconditioned) or 382 and more
+// (FP64): only the first leaves room, for two such solves (with three more
+// solves beside it four threads solve 1,275 per second, 1,410 as passes).
+static int resident_beside(fftcg_plan_t plan, int precision) {
+    if (plan->M <= 512) return 1 << 30;
+    return plan->precond == FFTCG_PRECOND_NONE && precision == FFTCG_MIXED ? 2 : 0;
+}
+
 // small: a solve of AUTO on a grid of the fused engine (M <= 64).  Where the
 // resident kernel finds no room, or a meeting gives up, the fused engine takes
 // it: one workgroup, no meetings, and faster than the passes there (periodic
@@ -890,14 +922,17 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
                            const uint8_t* mask = nullptr, bool small = false) {
     Workspace* w = nullptr;
     const size_t n = (size_t)plan->L * plan->L;
+    DeviceUse use(plan->device);
+    const int beside = resident_beside(plan, precision);
     if (plan_resident(plan, precision)) {
-        XcdHold hold(plan->device, plan->ops->resident_xcds(precision));
-        if (hold.held()) {
+        const bool room = !applies_in_flight(plan->device, s) && use.resident(plan->ops->resident_xcds(precision), beside);
+        if (room) {
             w = plan_acquire(plan);
             if (!w) return FFTCG_ENOMEM;
         }
-        if (hold.held() && resident_words(w, s)) {
-            const int rc = solve_resident(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, hold.first());
+        if (room && resident_words(w, s)) {
+            const int rc =
+                solve_resident(plan, w, precision, d, b, x0, tol, maxit, x, info, s, mask, use.first_xcd());
             if (rc != ST_EGRID) {
                 plan->routes[ROUTE_RESIDENT] += 1;
                 plan_release(plan, w);
@@ -911,6 +946,7 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
                 return FFTCG_EDEVICE;
             }
         }
+        use.end();
     }
     if (small) {
         // (w is given back after the solve, which waits for the copy from w->q)
@@ -920,11 +956,13 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
     }
     if (!w) w = plan_acquire(plan);
     if (!w) return FFTCG_ENOMEM;
-    // the folded update (any mode but 0), or the preconditioned turns (1, 2)
-    bool grid = !plan->grid_broken.load() &&
-                (plan->precond == FFTCG_PRECOND_NONE
-                     ? plan->grid_mode != 0 && plan->grid_cap[precision == FFTCG_MIXED]
-                     : (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->turn_pcg_cap[precision == FFTCG_MIXED]);
+    // the folded update (any mode but 0), or the preconditioned turns (1, 2),
+    // where their grids find room
+    const int fits = plan_barrier_fits(plan, precision);
+    const DeviceUse::Kind kind = !plan_resident(plan, precision) ? DeviceUse::LARGE
+                                 : beside > 0                     ? DeviceUse::LIGHT
+                                                                  : DeviceUse::HEAVY;
+    bool grid = use.passes(kind, fits);
     int rc = FFTCG_OK;
     // a warm start in place is kept in q, which the grid-synchronised path
     // never writes, so that a solve abandoned at a barrier can be repeated

@@ -99,6 +99,8 @@ struct fftcg_plan_s {
     size_t device_bytes = 0;
     void* apply_W = nullptr;
     hipEvent_t apply_ev = nullptr;
+    std::atomic<bool> apply_pending{false};  // passes of a product may be in flight (apply_ev says)
+    std::atomic<hipStream_t> apply_stream{nullptr};
     // fused (single-workgroup) engine: compiled size and constant tables
     int fused_ok = 0;
     const fftcg::FusedOps* fops = nullptr;
@@ -111,9 +113,10 @@ struct fftcg_plan_s {
     // plan creation; set once a barrier gave up (the plan then keeps the
     // separate update kernel until the mode is set again)
     int grid_mode = 1;
-    bool grid_cap[2] = {false, false};
-    bool turn_cap[2] = {false, false};  // the turn pass (k_row_turn) resident as a whole, per precision
-    bool turn_pcg_cap[2] = {false, false};  // the preconditioned turns, likewise
+    // (capabilities: how many such grids the device holds at once, 0: not one)
+    int grid_cap[2] = {0, 0};
+    int turn_cap[2] = {0, 0};      // the turn pass (k_row_turn), per precision
+    int turn_pcg_cap[2] = {0, 0};  // the preconditioned turns, likewise
     // the resident kernel, per precision, plain and preconditioned: -1 not
     // asked yet (the first solve does), 0 no, 1 yes
     std::atomic<int> res_cap[2][2] = {{{-1}, {-1}}, {{-1}, {-1}}};

@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "device_use.hpp"
 #include "engine.hpp"
 #include "fftcg.h"
 #include "fftcg_internal.hpp"
@@ -578,6 +579,9 @@ void serve_reservations(fftcg_server_s* srv) {
 
 void scheduler(fftcg_server_s* srv) {
     (void)hipSetDevice(srv->opts.device);
+    // single solves of the process keep clear of a server at work
+    DeviceUse use(srv->opts.device);
+    bool used = false;
     while (!srv->stop.load()) {
         serve_reservations(srv);
         std::vector<Class*> cls;
@@ -594,6 +598,13 @@ void scheduler(fftcg_server_s* srv) {
             } catch (...) {
                 busy = true;
             }
+        }
+        if (busy != used) {
+            if (busy)
+                (void)use.passes(DeviceUse::LARGE, 0);
+            else
+                use.end();
+            used = busy;
         }
         if (!busy) {
             std::unique_lock<std::mutex> lk(srv->mu);

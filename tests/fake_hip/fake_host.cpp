@@ -112,6 +112,10 @@ hipError_t hipEventDestroy(hipEvent_t e) {
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
+    *c = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipGetDeviceCount(int* n) {
     *n = 1;
     return hipSuccess;
@@ -131,7 +135,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 namespace {
 // capabilities as on the device: the resident kernel for 32 <= M <= 1024 (one
 // XCD up to M = 256), barriers everywhere, the preconditioned turns at M =
-// 2048 and 4096 in FP32; above M = 2048 one grid fills the device
+// 2048 and 4096 in FP32; above M = 2048 one grid fills the device, at 2048 four do, below sixteen
 template <int M, int PAD>
 struct Fake {
     static constexpr int L = PAD ? M / 2 : M;
@@ -183,8 +187,8 @@ struct Fake {
             o.iter_pass = iter_pass;
             o.iter_grid_chunk = grid_chunk;
             o.iter_pcg_chunk = pcg_chunk;
-            o.grid_capable = [](int) -> decltype(o.grid_capable(0)) { return M > 2048 ? 1 : 4; };
-            o.turn_capable = [](int) -> decltype(o.turn_capable(0)) { return M > 2048 ? 1 : (M > 1024 ? 4 : 0); };
+            o.grid_capable = [](int) -> decltype(o.grid_capable(0)) { return M > 2048 ? 1 : (M > 1024 ? 4 : 16); };
+            o.turn_capable = [](int) -> decltype(o.turn_capable(0)) { return M > 2048 ? 1 : (M > 1024 ? 4 : 16); };
             o.turn_pcg_capable = [](int prec) -> decltype(o.turn_pcg_capable(0)) {
                 return prec != FFTCG_MIXED || M < 2048 || M > 4096 ? 0 : (M > 2048 ? 1 : 4);
             };

@@ -2,7 +2,13 @@
 fftcg_host.cpp and fused.hip, unmodified) on a simulated device, on the CPU
 (tests/fake_hip/fake_host.cpp): which route a solve takes when others are in
 flight or a meeting gives up.  A solve is held in flight by blocking inside
-its launch."""
+its launch.
+
+A resident kernel keeps its CUs for a whole solve, and every launch of
+another solve's passes whose workgroups do not fit beside it waits for its
+end: resident solves start only where no passes are in flight but those of
+light solves (up to M = 512, and plain FP32 ones of M = 1024) that found no
+room themselves."""
 
 import ctypes
 import os
@@ -78,7 +84,8 @@ class Plan:
         return dict(zip(ROUTES, r))
 
     def solve(self, precision=MIXED, in_place=False, stream=None):
-        """Solves with a right-hand side of ones; returns the route taken."""
+        """Solves with a right-hand side of ones; returns the route taken
+        (and those of the plan's solves that ended meanwhile)."""
         n = self.L * self.L
         d, b = np.ones(n), np.ones(n)
         x = np.full(n, 7.0) if in_place else np.zeros(n)
@@ -171,3 +178,115 @@ def test_small_solve_that_gave_up_is_fused(fake, in_place):
     assert fake.lib.fftcg_plan_set_grid_sync(p.h, 1) == 0
     assert p.solve() == ["resident"]
     p.close()
+
+
+def _hold(fake, p, kind=None, **kw):
+    return InFlight(fake, lambda: p.solve(**kw), kind)
+
+
+@pytest.mark.parametrize("big,precond", [((2048, 1), 0), ((2048, 1), 1), ((1024, 0), 0)])
+def test_no_resident_solve_beside_passes(fake, big, precond):
+    p, small, mid, tiny = fake.plan(*big, precond), fake.plan(128, 1), fake.plan(512, 1), fake.plan(64, 0)
+    if big[0] == 1024:  # a grid that has the resident kernel, with the passes asked for
+        assert fake.lib.fftcg_plan_set_grid_sync(p.h, 3) == 0
+    with _hold(fake, p):
+        for q in (small, mid):
+            # a grid that fills the device leaves no room for their barriers either
+            assert q.solve() == ["separate" if big[0] == 2048 else "turn"]
+        assert tiny.solve() == ["fused"]
+    for q in (small, mid, tiny):
+        assert q.solve() == ["resident"]
+    for q in (p, small, mid, tiny):
+        q.close()
+
+
+def test_resident_solves_beside_each_other(fake):
+    """On one XCD each: eight, and the ninth by passes; while that runs, an XCD
+    that becomes free is taken again.  On the whole device: one, alone."""
+    p, q = fake.plan(128, 1), fake.plan(512, 1, 1)
+    held = [_hold(fake, p, RESIDENT).__enter__() for _ in range(8)]
+    with _hold(fake, p, CHUNK) as ninth:
+        held.pop().__exit__()
+        assert p.solve() == ["resident"]
+        assert q.solve() == ["separate"]  # (preconditioned at M = 1024: no turns)
+    assert "turn" in ninth.out
+    for h in held:
+        h.__exit__()
+    with _hold(fake, q, RESIDENT):
+        with _hold(fake, q, SEPARATE) as other:
+            assert p.solve() == ["turn"]
+    assert other.out == ["separate"]
+    with _hold(fake, q, SEPARATE, precision=FP64) as first:  # alone: not the passes
+        pass
+    assert first.out == ["resident"] and q.solve() == ["resident"]
+    p.close()
+    q.close()
+
+
+def test_resident_beside_light_passes(fake):
+    """M = 512: any number of solves of its kind; M = 1024: plain FP32 beside
+    two of them, FP64 and the preconditioned alone."""
+    p, q, h = fake.plan(256, 1), fake.plan(512, 1), fake.plan(512, 1, 1)
+    for plan, n in ((p, 5), (q, 2)):
+        first = _hold(fake, plan, RESIDENT).__enter__()
+        held = [_hold(fake, plan, CHUNK).__enter__() for _ in range(n)]
+        first.__exit__()
+        with _hold(fake, plan, RESIDENT):  # entered: the resident kernel again
+            pass
+        before = plan.routes()["resident"]
+        assert q.solve(FP64) == ["turn"] and h.solve() == ["separate"]
+        assert p.solve() == ["resident"] and plan.routes()["resident"] == before + (plan is p)
+        if plan is q:
+            with _hold(fake, q, RESIDENT):
+                held.append(_hold(fake, q, CHUNK).__enter__())
+            assert q.solve() == ["turn"]  # beside three
+        for x in held:
+            x.__exit__()
+    with _hold(fake, h, RESIDENT):
+        with _hold(fake, q, CHUNK, precision=FP64):
+            assert p.solve() == ["turn"]
+    assert q.solve(FP64) == ["resident"] and h.solve() == ["resident"]
+    for x in (p, q, h):
+        x.close()
+
+
+def test_barriers_share_the_device(fake):
+    """Barriers of grids that do not fit the device together are not tried:
+    the later solve runs the separate update, and its plan does not fall
+    back."""
+    p, q, r = fake.plan(2048, 1), fake.plan(1024, 1), fake.plan(128, 1)
+    with _hold(fake, p, CHUNK) as first:
+        assert p.solve() == ["separate"] and q.solve() == ["separate"]
+    assert "turn" in first.out and p.solve() == ["turn"]
+    held = [_hold(fake, q, CHUNK).__enter__() for _ in range(4)]  # four fit
+    assert q.solve() == ["separate"]
+    for h in held:
+        h.__exit__()
+        assert "turn" in h.out
+    with _hold(fake, r, RESIDENT):
+        assert p.solve() == ["separate"] and q.solve() == ["separate"]
+    assert p.solve() == ["turn"] and q.solve() == ["turn"]
+    st = I()
+    for x in (p, q):
+        assert fake.lib.fftcg_plan_get_grid_sync(x.h, MIXED, ctypes.byref(st)) == 0 and st.value == 4
+        x.close()
+    r.close()
+
+
+def test_products_in_flight(fake):
+    """A product returns before its passes have run; on the solve's own
+    stream they come before it, on another they run beside it."""
+    p, q = fake.plan(2048, 1), fake.plan(128, 1)
+    a = [np.zeros(2048 * 2048) for _ in range(3)]
+    ptr = [v.ctypes.data_as(P) for v in a]
+    fake.lib.fake_hold_events(1)
+    try:
+        assert fake.lib.fftcg_apply(p.h, FP64, *ptr, P(16)) == 0
+        assert q.solve(stream=P(32)) == ["turn"]
+        assert q.solve(stream=P(16)) == ["resident"]
+    finally:
+        fake.lib.fake_hold_events(0)
+    assert q.solve(stream=P(32)) == ["resident"]
+    p.close()
+    assert q.solve(stream=P(32)) == ["resident"]
+    q.close()
