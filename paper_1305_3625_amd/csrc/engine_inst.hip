@@ -129,11 +129,13 @@ constexpr bool kResBuilt = M >= 32 && G<W>::SUM_GROUPS > 0 && RGeo<W, M, PAD>::O
 // Against the folded update alone (whole solves, alternating in one process):
 // padded L = 1024 mixed 4117 -> 3887 us, FP64 5227 -> 4842; padded L = 2048
 // mixed 9076 -> 8289; periodic M = 2048 mixed 4188 -> 3824.
-// Built above the resident kernel's grids, where its own grid can be resident
-// at once: not in FP64 on rows of 16 pairs a thread and more (over 200 VGPRs,
-// two workgroups per CU).
+// On the resident kernel's grids it serves solves that find no room for that
+// (four threads of FP64 L = 512: 1,153 solves a second, 910 with the folded
+// update alone; of mixed L = 256 2,580 and 2,440).
+// Built where its grid can be resident at once: not in FP64 on rows of 16
+// pairs a thread and more (over 200 VGPRs, two workgroups per CU).
 template <typename W>
-constexpr bool kTurnBuilt = !kResBuilt<W> && !(sizeof(W) == 8 && G<W>::ER >= 16);
+constexpr bool kTurnBuilt = !(sizeof(W) == 8 && G<W>::ER >= 16);
 
 template <typename W>
 void iter_pass_t(int pass, bool grid, const PlanTabs& pt, const SlotDesc* slot, int stride, unsigned long long token,

@@ -121,3 +121,45 @@ def test_residual_falls_at_once_in_turn_pass():
     ref = np.real(np.fft.ifft2(np.fft.fft2(b) / (1.0 + g)))
     assert relerr(out[1][0], ref) <= 1e-8
     plan.close()
+
+
+@pytest.mark.parametrize("precision", [binding.FP64, binding.MIXED])
+@pytest.mark.parametrize("L,padded", [(128, 1), (256, 1), (512, 1), (256, 0), (512, 0)])
+def test_refused_solve_runs_turn_pass(L, padded, precision):
+    """Beside a large solve's passes the resident kernel does not start; such
+    a solve has the turn pass, with bitwise the result of mode 3."""
+    import threading
+    import torch
+    inst = (padded_instance if padded else periodic_instance)(L, [35, L, padded], eps=1e-3)
+    big = padded_instance(2048, [35, 1], eps=1e-4)
+    plan, other = binding.Plan(L, padded, inst["ghat"]), binding.Plan(2048, 1, big["ghat"])
+    other.set_grid_sync(0)  # no barrier: it leaves the device's share to the others
+    banner("route-refused", L, padded, precision)
+    assert plan.grid_sync(precision) == binding.GRID_ON_TURN
+    plan.set_grid_sync(3)
+    want, winfo, got = _route(plan, inst, precision)
+    assert got == "folded"
+    plan.set_grid_sync(1)
+    D, B = dev(big["d"]), dev(big["b"])
+    X = torch.zeros((2048, 2048), dtype=torch.float64, device="cuda")
+    d, b = dev(inst["d"]), dev(inst["b"])
+    torch.cuda.synchronize()
+    before = plan.solve_routes()
+    th = threading.Thread(target=lambda: other.solve(D, B, X, tol=1e-12, maxit=200, precision=binding.FP64,
+                                                     stream=torch.cuda.Stream(), raise_on_error=False))
+    th.start()
+    s, n = torch.cuda.Stream(), 0
+    while th.is_alive() or n == 0:
+        x = torch.zeros((L, L), dtype=torch.float64, device="cuda")
+        torch.cuda.current_stream().synchronize()
+        info = plan.solve(d, b, x, tol=1e-8, precision=precision, stream=s)
+        assert np.array_equal(host(x), want) and info["iterations"] == winfo["iterations"]
+        n += 1
+    th.join()
+    after = plan.solve_routes()
+    print(n, after)
+    assert plan.grid_sync(precision) == binding.GRID_ON_TURN
+    assert after["turn"] > before["turn"] and after["folded"] == before["folded"]
+    assert after["separate"] == before["separate"]
+    plan.close()
+    other.close()
