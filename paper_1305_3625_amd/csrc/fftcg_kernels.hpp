@@ -997,8 +997,11 @@ __device__ inline bool grid_sums(const double* acc, double* part, int stride, un
         __syncthreads();
     } else {
         if (tid < cmin(N, NT)) {
-            while (__hip_atomic_load(gbl(rel), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != token) {
-                if ((long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit) {
+            // the lanes that fetch the totals wait together, and give up together
+            for (;;) {
+                const bool here = __hip_atomic_load(gbl(rel), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
+                if (__all(here)) break;
+                if (__any((long long)(__builtin_amdgcn_s_memrealtime() - t0) > limit)) {
                     ok = 0;
                     break;
                 }
