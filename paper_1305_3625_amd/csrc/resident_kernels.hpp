@@ -585,6 +585,33 @@ struct ResArgs {
     int zero;                   // ... from x = 0
 };
 
+// A meeting gave up: the solve is abandoned and the host repeats it.
+__device__ __forceinline__ void res_give_up(const SlotDesc& sd) {
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&sd.st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&sd.st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The end of a launch: a last meeting, after which every workgroup's results
+// are stored, and then the first workgroup stores the state.  It alone may
+// also report that this meeting gave up: another one that does so may be
+// late only to see that all have arrived, and would then write into the state
+// that the first one stores (a solve stopped at its launch's last iteration
+// could be left marked as done, with its status of a solve that goes on).
+template <class MT>
+__device__ __forceinline__ void res_end(const MT& all, unsigned long long token, int* s_ok, int blk,
+                                        const SlotDesc& sd, const SolveState& st) {
+    if (!all.meet(token, s_ok)) {
+        if (blk == 0) res_give_up(sd);
+        return;
+    }
+    if (blk == 0 && threadIdx.x == 0) {
+        *sd.st = st;
+        publish_status(sd, st.done, st.status, st.gen, st.iters, st.last_check_iter);
+    }
+}
+
 // A solve, or up to K of its iterations: FP64 checks (check_decide) and CG
 // iterations until the solve is done.  Plain CG repeats the folded passes'
 // arithmetic, PCG (circulant preconditioner) that of iter_pcg.
@@ -615,7 +642,6 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
     const int blk = R::ONEX ? blockIdx.x >> 3 : blockIdx.x;
     const SlotDesc& sd = ra.sd;
     const int tid = threadIdx.x;
-    const bool lead = blk == 0 && tid == 0;
     if (tid == 0) st = ra.first ? init : *sd.st;
     __syncthreads();
     if (st.done) return;
@@ -626,12 +652,7 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
     const Meet<R::NG, R::GM> all{ra.words, st.bar_limit, blk % R::NG, blk / R::NG};
     cx<T>* Wb = reinterpret_cast<cx<T>*>(sd.W);
     unsigned long long token = ra.token;
-    auto give_up = [&]() {
-        if (tid == 0) {
-            __hip_atomic_store(&sd.st->status, ST_EGRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&sd.st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    };
+    auto give_up = [&]() { res_give_up(sd); };
     // all sums' words are empty before the first meeting
     all.empty(0, ITER_SETS | CHECK_SETS);
     all.empty(1, ITER_SETS | CHECK_SETS);
@@ -902,11 +923,7 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
             if (!MIXED || !st.done) st2<T>(xa + o + rel(i), x[i]);
         }
     }
-    if (!all.meet(token, &s_ok)) return give_up();
-    if (lead) {
-        *sd.st = st;
-        publish_status(sd, st.done, st.status, st.gen, st.iters, st.last_check_iter);
-    }
+    res_end(all, token, &s_ok, blk, sd, st);
 }
 
 }  // namespace FFTCG_RADIX_NS

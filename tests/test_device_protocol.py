@@ -12,11 +12,11 @@ CSRC = os.path.join(ROOT, "paper_1305_3625_amd", "csrc")
 BUILD = os.path.join(ROOT, "_build", "fake")
 
 
-def _function(header, start):
-    """The text of the function template whose definition contains `start`,
-    from its template line to its closing brace."""
+def _function(header, start, head="template"):
+    """The text of the function whose definition contains `start`, from the
+    line before it that begins with `head` to its closing brace."""
     src = open(os.path.join(CSRC, header)).read()
-    i = src.rindex("\ntemplate", 0, src.index(start)) + 1
+    i = src.rindex("\n" + head, 0, src.index(start)) + 1
     return src[i:src.index("\n}\n", i) + 3]
 
 
@@ -124,3 +124,87 @@ def test_grid_sums_gives_up_as_one():
     for blind, (same, ok, right) in enumerate(out):
         assert same and (right or not ok), (blind, same, ok, right)
     assert out[0] == (1, 1, 1)
+
+
+RES_END = r"""
+#include <stdio.h>
+#include <string.h>
+#include <functional>
+#define __device__
+#define __forceinline__ inline
+struct Idx { unsigned x; };
+static const Idx threadIdx{0};
+#include "fftcg_types.hpp"
+using namespace fftcg;
+static void publish_status(const SlotDesc&, int, int, int, int, int) {}
+// runs the other workgroup's part before the n-th store to the state
+static int store_no;
+static std::function<void(int)> before_store;
+template <class T> void store(T* p, T v) {
+    before_store(store_no++);
+    *p = v;
+}
+#define __hip_atomic_store(p, v, o, s) store(p, v)
+struct Meeting {
+    bool met;
+    bool meet(unsigned long long, int*) const { return met; }
+};
+@GIVE_UP@
+@END@
+int main() {
+    // workgroup 0 meets the others; workgroup 1 gives up as they arrive.  The
+    // solve goes on (done = 0), or has ended with a status of its own.
+    for (int done = 0; done < 2; ++done)
+        for (int when = 0; when < 3; ++when) {
+            SolveState mem, st;
+            memset(&mem, 0, sizeof mem);
+            memset(&st, 0, sizeof st);
+            st.done = done;
+            st.status = done ? -4 : 0;
+            SlotDesc sd;
+            memset(&sd, 0, sizeof sd);
+            sd.st = &mem;
+            int s_ok = 0;
+            bool ran = false;
+            auto first = [&] {
+                if (ran) return;
+                ran = true;
+                auto f = before_store;
+                before_store = [](int) {};
+                res_end(Meeting{true}, 9, &s_ok, 0, sd, st);
+                before_store = f;
+            };
+            store_no = 0;
+            before_store = [&](int n) {
+                if (n == when) first();
+            };
+            res_end(Meeting{false}, 9, &s_ok, 1, sd, st);
+            first();
+            printf("%d:%d:%d:%d\n", done, when, mem.done, mem.status);
+        }
+    // and where workgroup 0 gives up
+    SolveState mem, st;
+    memset(&mem, 0, sizeof mem);
+    memset(&st, 0, sizeof st);
+    SlotDesc sd;
+    memset(&sd, 0, sizeof sd);
+    sd.st = &mem;
+    int s_ok = 0;
+    before_store = [](int) {};
+    res_end(Meeting{false}, 9, &s_ok, 0, sd, st);
+    printf("2:0:%d:%d\n", mem.done, mem.status == ST_EGRID);
+}
+"""
+
+
+def test_end_of_resident_launch():
+    """The state after the last meeting is the first workgroup's, or says
+    that the solve was abandoned; never parts of both."""
+    code = RES_END.replace("@GIVE_UP@", _function("resident_kernels.hpp", "void res_give_up(", "__device__"))
+    code = code.replace("@END@", _function("resident_kernels.hpp", "void res_end("))
+    for line in _run("res_end", code):
+        kind, when, done, status = map(int, line.split(":"))
+        if kind == 2:
+            assert (done, status) == (1, 1)
+        else:
+            assert (done, status) in ((kind, -4 if kind else 0), (1, -100)), line
