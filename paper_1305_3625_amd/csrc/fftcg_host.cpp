@@ -853,8 +853,15 @@ static bool resident_words(Workspace* w, hipStream_t s) {
         (void)hipGetLastError();
         return false;
     }
+    // (kept only once they are cleared: a meeting takes any word at or above
+    // its token for an arrival)
+    if (hipMemsetAsync(p, 0, kMeetWords * 8, s) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(p);
+        return false;
+    }
     w->meet = (unsigned long long*)p;
-    return hipMemsetAsync(p, 0, kMeetWords * 8, s) == hipSuccess;
+    return true;
 }
 
 // A solve by the resident kernel: one launch, or one per kResidentIters

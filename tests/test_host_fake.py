@@ -290,3 +290,15 @@ def test_products_in_flight(fake):
     p.close()
     assert q.solve(stream=P(32)) == ["resident"]
     q.close()
+
+
+def test_resident_words_cleared_or_not_used(fake):
+    """Meetings take any word at or above their token for an arrival, so the
+    words must be clear: a workspace whose clearing failed does not keep them
+    as cleared ones."""
+    p = fake.plan(128, 1)
+    fake.lib.fake_fail_memset(fake.lib.fake_meet_bytes())
+    assert p.solve() == ["turn"]
+    for _ in range(2):
+        assert p.solve() == ["resident"] and fake.lib.fake_words_clear() == 1
+    p.close()
