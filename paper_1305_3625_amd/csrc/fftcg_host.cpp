@@ -317,7 +317,7 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
         if (r2 == FFTCG_OK) r2 = upload(&p->ghN64, build_ghN<double>(kernel_spectrum, M), &bytes);
         if (r2 == FFTCG_OK && hipMalloc(&p->apply_W, w_bytes(L, M)) != hipSuccess)
             r2 = FFTCG_ENOMEM;
-        bytes += (size_t)(M / 2) * L * 16;
+        bytes += w_bytes(L, M);
         if (r2 == FFTCG_OK && hipEventCreateWithFlags(&p->apply_ev, hipEventDisableTiming) != hipSuccess)
             r2 = FFTCG_EDEVICE;
     }

@@ -302,3 +302,18 @@ def test_resident_words_cleared_or_not_used(fake):
     for _ in range(2):
         assert p.solve() == ["resident"] and fake.lib.fake_words_clear() == 1
     p.close()
+
+
+@pytest.mark.parametrize("L,padded", [(64, 0), (256, 1), (2048, 0)])
+def test_device_bytes_counts_the_product_buffer(fake, L, padded):
+    """device_bytes of a plan includes the half spectrum of its products, with
+    the 128 bytes behind every column that the buffer holds."""
+    M = 2 * L if padded else L
+    p = fake.plan(L, padded)
+    n = S()
+    assert fake.lib.fftcg_plan_info(p.h, None, None, None, ctypes.byref(n)) == 0
+    quarter = (M // 2 + 1) ** 2
+    tables = 2 * M * 12 + (M // 2) * (M // 2 + 1) * 12 + (M // 2 + 1) * 12
+    fused = 2 * M * 12 + quarter * 12 if M <= 256 else 0
+    assert n.value == tables + fused + (M // 2) * (L * 16 + 128)
+    p.close()
