@@ -286,8 +286,6 @@ extern "C" int fftcg_plan(int L, int padded, const double* kernel_spectrum, fftc
     if (p->ops) {
         p->grid_cap[0] = p->ops->grid_capable(FFTCG_FP64);
         p->grid_cap[1] = p->ops->grid_capable(FFTCG_MIXED);
-        p->turn_cap[0] = std::min(p->grid_cap[0], p->ops->turn_capable(FFTCG_FP64));
-        p->turn_cap[1] = std::min(p->grid_cap[1], p->ops->turn_capable(FFTCG_MIXED));
         p->turn_pcg_cap[0] = p->ops->turn_pcg_capable(FFTCG_FP64);
         p->turn_pcg_cap[1] = p->ops->turn_pcg_capable(FFTCG_MIXED);
     }
@@ -400,11 +398,19 @@ extern "C" int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, dou
     return FFTCG_OK;
 } FFTCG_ABI_CATCH
 
-// whether solves in `precision` on this plan use the turn pass (the folded
-// update's mode, and the turn pass's grid resident as a whole)
-static bool plan_turn(fftcg_plan_t plan, int precision) {
-    return (plan->grid_mode == 1 || plan->grid_mode == 2) && plan->turn_cap[precision == FFTCG_MIXED];
+// Grids of the turn pass that solves in `precision` on this plan use (the
+// folded update's modes but 3) that the device holds at once; 0: they do not.
+static int turn_fits(fftcg_plan_t plan, int precision) {
+    if (!plan->ops || (plan->grid_mode != 1 && plan->grid_mode != 2)) return 0;
+    const int m = precision == FFTCG_MIXED;
+    int c = plan->turn_cap[m].load();
+    if (c < 0) {
+        c = std::min(plan->grid_cap[m], plan->ops->turn_capable(precision));
+        plan->turn_cap[m].store(c);
+    }
+    return c;
 }
+static bool plan_turn(fftcg_plan_t plan, int precision) { return turn_fits(plan, precision) > 0; }
 
 // whether solves in `precision` on this plan run the resident kernel (the
 // same modes)
@@ -429,7 +435,8 @@ static int plan_barrier_fits(fftcg_plan_t plan, int precision) {
     if (plan->precond != FFTCG_PRECOND_NONE)
         return plan->grid_mode == 1 || plan->grid_mode == 2 ? plan->turn_pcg_cap[m] : 0;
     if (plan->grid_mode == 0) return 0;
-    return plan_turn(plan, precision) ? plan->turn_cap[m] : plan->grid_cap[m];
+    const int turn = turn_fits(plan, precision);
+    return turn > 0 ? turn : plan->grid_cap[m];
 }
 
 extern "C" int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode) try {
@@ -580,7 +587,7 @@ extern "C" int fftcg_profile_iteration(fftcg_plan_t plan, int precision, const d
     const bool turn = grid && plan_turn(plan, precision);
     if (turn && reps < 2) return FFTCG_EINVAL;
     DeviceUse use(plan->device);
-    (void)use.passes(DeviceUse::LARGE, grid ? (turn ? plan->turn_cap : plan->grid_cap)[precision == FFTCG_MIXED] : 0);
+    (void)use.passes(DeviceUse::LARGE, grid ? plan_barrier_fits(plan, precision) : 0);
     // the launches in the order a solve's chunk makes them: with the turn
     // pass row_fwd, col, (turn, col) x (reps - 1), row_inv; else per
     // iteration row_fwd, col, row_inv and (without the folded update) update

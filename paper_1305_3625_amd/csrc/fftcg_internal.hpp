@@ -115,7 +115,9 @@ struct fftcg_plan_s {
     int grid_mode = 1;
     // (capabilities: how many such grids the device holds at once, 0: not one)
     int grid_cap[2] = {0, 0};
-    int turn_cap[2] = {0, 0};      // the turn pass (k_row_turn), per precision
+    // the turn pass (k_row_turn), per precision: -1 not asked yet (a plan whose
+    // solves run the resident kernel seldom needs it)
+    std::atomic<int> turn_cap[2] = {{-1}, {-1}};
     int turn_pcg_cap[2] = {0, 0};  // the preconditioned turns, likewise
     // the resident kernel, per precision, plain and preconditioned: -1 not
     // asked yet (the first solve does), 0 no, 1 yes
