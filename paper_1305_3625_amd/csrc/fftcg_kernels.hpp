@@ -556,32 +556,35 @@ struct ProCheck {
     struct Sh {};
     struct Sc {
         double alpha;
-        int mixed;
     };
     using Gate = GateCheck;
     static __device__ __forceinline__ bool begin(const SlotDesc& sd, Sh&, Sc& sc, int, int) {
         if (!GateCheck::ok(sd)) return false;
         sc.alpha = gbl(sd.st)->alpha;
-        sc.mixed = gbl(sd.st)->mixed;
         return true;
     }
+    // (the correction e belongs to FP32 solves; p is read whether used or not)
+    static constexpr bool HAS_E = sizeof(W) == 4;
     struct Raw {
         cx<double> x;
         cx<float> e;
         cx<W> p;
     };
-    // (e is an array of every slot, e and p are read whether used or not)
     template <int L>
     static __device__ __forceinline__ Raw fetch(const SlotDesc& sd, int row, int col) {
         const unsigned idx = (unsigned)row * L + col;
-        return Raw{ldv<double, L>(sd.x, idx), ldv<float, L>(sd.e, idx), ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx)};
+        Raw w;
+        w.x = ldv<double, L>(sd.x, idx);
+        if constexpr (HAS_E) w.e = ldv<float, L>(sd.e, idx);
+        w.p = ldv<W, L>(reinterpret_cast<const W*>(sd.p), idx);
+        return w;
     }
     template <int L>
     static __device__ __forceinline__ cx<double> combine(const SlotDesc& sd, const Sc& sc, const Raw& w, int row,
                                                          int col, double*) {
         const unsigned idx = (unsigned)row * L + col;
         cx<double> xv = w.x;
-        if (sc.mixed) {
+        if constexpr (HAS_E) {
             xv.x += (double)w.e.x;
             xv.y += (double)w.e.y;
             stv<float, L>(sd.e, idx, mkc(0.0f, 0.0f));
