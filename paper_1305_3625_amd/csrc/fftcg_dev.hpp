@@ -343,16 +343,12 @@ template <int R>
 __host__ __device__ constexpr int tw_nb() {
     return R > 8 ? 4 : (R > 4 ? 3 : (R > 2 ? 2 : 1));
 }
-template <typename T>
-__device__ __forceinline__ cx<T> twl(const cx<T>* tw, int m) {
-    return gld(tw + m);
-}
-template <typename T, int R, class TW>
-__device__ __forceinline__ void tw_load(cx<T>* pb, TW tw, int m) {
-    pb[0] = twl(tw, m);
-    if constexpr (R > 2) pb[1] = twl(tw, 2 * m);
-    if constexpr (R > 4) pb[2] = twl(tw, 4 * m);
-    if constexpr (R > 8) pb[3] = twl(tw, 8 * m);
+template <typename T, int R>
+__device__ __forceinline__ void tw_load(cx<T>* pb, const cx<T>* tw, int m) {
+    pb[0] = gld(tw + m);
+    if constexpr (R > 2) pb[1] = gld(tw + 2 * m);
+    if constexpr (R > 4) pb[2] = gld(tw + 4 * m);
+    if constexpr (R > 8) pb[3] = gld(tw + 8 * m);
 }
 // The barrier of an LDS exchange: of the workgroup, or (WV) among the lanes
 // of one wave, whose LDS accesses are performed in order, so that only the
@@ -405,8 +401,8 @@ __device__ __forceinline__ void tw_apply(cx<T>* v, const cx<T>* pb) {
 // are therefore not fenced: a caller that writes the buffer after the
 // transform places a barrier first.
 // WV: the transform's threads are lanes of one wave.
-template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, int S, class Lay, bool LEAD, bool WV, class TW>
-__device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, TW tw, const cx<T>* pre) {
+template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, int S, class Lay, bool LEAD, bool WV>
+__device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, const cx<T>* tw, const cx<T>* pre) {
     constexpr int E = fft_elems(N);
     constexpr int P = N / E;
     constexpr int R = fft_radix(N, REV, S);
@@ -438,19 +434,18 @@ __device__ __forceinline__ void stages(cx<T>* v, const Lay& lay, int j, TW tw, c
         xsync<WV>();
 #pragma unroll
         for (int u = 0; u < NB2; ++u) lay.template ld_run<R2, N / R2>(j + u * P, v + u * R2);
-        stages<T, N, MTAB, DIR, REV, HALF_IN, S + 1, Lay, LEAD, WV, TW>(v, lay, j, tw, nxt);
+        stages<T, N, MTAB, DIR, REV, HALF_IN, S + 1, Lay, LEAD, WV>(v, lay, j, tw, nxt);
     }
 }
 
 // Full transform (all stages).  Length 1 is the identity.  LEAD: the caller
 // read the LDS buffer before (its reads are fenced before the first write).
 // Returns with the last exchange's reads unfenced (see stages).
-template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, class Lay, bool LEAD = false, bool WV = false,
-          class TW = const cx<T>*>
-__device__ __forceinline__ void fft_run(cx<T>* v, const Lay& lay, int j, TW tw) {
+template <typename T, int N, int MTAB, int DIR, bool REV, bool HALF_IN, class Lay, bool LEAD = false, bool WV = false>
+__device__ __forceinline__ void fft_run(cx<T>* v, const Lay& lay, int j, const cx<T>* tw) {
     // stage 0 has no twiddles (NS = 1)
     if constexpr (fft_nstages(N) > 0)
-        stages<T, N, MTAB, DIR, REV, HALF_IN, 0, Lay, LEAD, WV, TW>(v, lay, j, tw, nullptr);
+        stages<T, N, MTAB, DIR, REV, HALF_IN, 0, Lay, LEAD, WV>(v, lay, j, tw, nullptr);
 }
 
 // ---- reductions -----------------------------------------------------------

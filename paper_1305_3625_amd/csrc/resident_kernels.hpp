@@ -363,8 +363,8 @@ struct RowShare {
 
 // Forward transforms of the workgroup's rows to W (row_fwd_out's arithmetic).
 // Called by the row threads' waves only where rows stay in waves, else by all.
-template <typename T, int M, int PAD, class TW>
-__device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>* Wb, int rb) {
+template <typename T, int M, int PAD>
+__device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, const cx<T>* tw, cx<T>* Wb, int rb) {
     using R = RGeo<T, M, PAD>;
     using G = Geo<T, M, PAD>;
     constexpr int N = G::N, E = G::ER, P = G::PR, WORDS = G::ROW_WORDS;
@@ -387,7 +387,7 @@ __device__ __forceinline__ void res_rows_fwd(cx<T>* v, cx<T>* lds, TW tw, cx<T>*
 #pragma unroll
         for (int s = 0; s < CNT; ++s) {
             const RowShare<T, M, PAD> e(tid, s);
-            twk[s] = twl(tw, e.kt * R::CW + e.kk);
+            twk[s] = gld(tw + (e.kt * R::CW + e.kk));
         }
     }
     xsync<R::WROW>();
@@ -447,8 +447,8 @@ struct ResSpec {
 // transform, times ghat / M^2, inverse transform.  All values are requested
 // before the first transform.
 // PRE: times the preconditioner's multiplier (c2, c4: pre_mul's) instead.
-template <typename T, int M, int PAD, bool PRE, class TW>
-__device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, PAD>& sp, T c2, T c4, cx<T>* Wb,
+template <typename T, int M, int PAD, bool PRE>
+__device__ __forceinline__ void res_cols(cx<T>* lds, const cx<T>* tw, const ResSpec<T, M, PAD>& sp, T c2, T c4, cx<T>* Wb,
                                          int blk) {
     using R = RGeo<T, M, PAD>;
     using G = Geo<T, M, PAD>;
@@ -512,8 +512,8 @@ __device__ __forceinline__ void res_cols(cx<T>* lds, TW tw, const ResSpec<T, M, 
 // Inverse transforms of the workgroup's rows (row_inv_body's arithmetic):
 // v[u RL + r] holds the pair at n = (j + u P) + r N / RL.  Called as
 // res_rows_fwd.
-template <typename T, int M, int PAD, class TW>
-__device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const cx<T>* Wb, int rb) {
+template <typename T, int M, int PAD>
+__device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, const cx<T>* tw, const cx<T>* Wb, int rb) {
     using R = RGeo<T, M, PAD>;
     using G = Geo<T, M, PAD>;
     constexpr int N = G::N, E = G::ER, P = G::PR, WORDS = G::ROW_WORDS;
@@ -550,7 +550,7 @@ __device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const 
                 const cx<T> Y = A[r];
                 const cx<T> B = conjc(Bv[R1 - 1 - r]);
                 const cx<T> s1 = Y + B, d1 = Y - B;
-                const cx<T> wd = cmul(conjc(twl(tw, k)), d1);
+                const cx<T> wd = cmul(conjc(gld(tw + k)), d1);
                 v[u * R1 + r] = mkc(s1.x - wd.y, s1.y + wd.x);
                 if (k == 0) v[u * R1 + r] = mkc(Y.x + Y.y, Y.x - Y.y);
             }
@@ -562,8 +562,8 @@ __device__ __forceinline__ void res_rows_inv(cx<T>* v, cx<T>* lds, TW tw, const 
 
 // One product: the transform of the rows' pairs v (as the forward transform
 // takes them) to the rows of C v (as res_rows_inv leaves them).
-template <typename T, int M, int PAD, bool PRE, class TW, class MT>
-__device__ __forceinline__ bool res_product(cx<T>* v, cx<T>* lds, TW tw, const ResSpec<T, M, PAD>& sp, T c2, T c4,
+template <typename T, int M, int PAD, bool PRE, class MT>
+__device__ __forceinline__ bool res_product(cx<T>* v, cx<T>* lds, const cx<T>* tw, const ResSpec<T, M, PAD>& sp, T c2, T c4,
                                             cx<T>* Wb, int rb, int blk, const MT& all, unsigned long long token,
                                             int* s_ok) {
     res_rows_fwd<T, M, PAD>(v, lds, tw, Wb, rb);
