@@ -201,7 +201,11 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  * work can hold part of the device) abandons the solve, which is then
  * repeated from its start with mode 0 semantics; the plan keeps the separate
  * kernel from then on, until this call sets a mode again.  The result is
- * the same either way (up to the rounding of r.r, about 1e-13).
+ * the same either way, up to the rounding of the r.r that beta and the
+ * check decision take: FP64 at most 1e-12 of it, ordinarily some 1e-15; FP32
+ * at most 2^-23, ordinarily 2^-23 / L, as the stored residual is rounded
+ * after the sums were formed (beta itself is rounded by 2^-24).  alpha's r.r
+ * is summed from the stored residual either way.
  * FFTCG_EINVAL for a NULL plan or another mode.  Not to be called
  * concurrently with solves on the same plan.                               */
 int fftcg_plan_set_grid_sync(fftcg_plan_t plan, int mode);

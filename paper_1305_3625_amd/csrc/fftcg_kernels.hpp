@@ -899,8 +899,11 @@ struct EpiTurn<E, decltype((void)E::TURN)> {
 // the working precision, as the update uses it).  Where the residual falls
 // by so much that the difference cancels (below a hundredth of a^2 q.q; an
 // ordinary iteration leaves a tenth or more) the caller sums it anew behind
-// a second barrier, so the relative error stays near 1e-13.  False also for
-// NaN.
+// a second barrier.  So in FP64 the relative error stays below 1e-12 (the
+// terms are at most 441 times the result; a few 1e-15 in ordinary
+// iterations); in FP32 the stored residual differs by its rounding after the
+// update, which the sums do not see: at most 2^-23 of r.r, about 2^-23 / L
+// where the residual is spread over the grid.  False also for NaN.
 __device__ __forceinline__ bool next_rr(const double* t, double a, double* rr) {
     *rr = fma(a, fma(a, t[3], -2.0 * t[2]), t[1]);
     return *rr > 0.01 * (a * a * t[3]);
