@@ -31,7 +31,9 @@ CXXFLAGS = [
     # expression then rounds alike in every kernel it is inlined into, so the
     # engines' variants of one iteration agree bitwise (contraction across
     # expressions depends on the surrounding code; the instruction counts of
-    # the passes are the same either way)
+    # the passes are the same either way).  Error of a product against long
+    # double, this against contraction across expressions, over 15 grids and
+    # both engines: FP32 0.92 to 1.002 times, FP64 0.99 to 1.02 times
     "-ffp-contract=on",
     # code objects loadable by the HIP runtime bundled with PyTorch
     "-mcode-object-version=5",
@@ -58,8 +60,28 @@ def engine_radix(m: int) -> int:
 
 
 def engine_row_threads(m: int, pad: int) -> int:
-    """Threads of a row-pass workgroup (and with them the rows and the number
-    of workgroups of the resident kernel)."""
+    """Threads of a row-pass workgroup, and with them the rows and the number
+    of workgroups of the resident kernel, which is what they are chosen for
+    (above M = 1024 it is not built, and the passes take 256).  More
+    workgroups leave each less to do between two meetings, but meetings of
+    more than 64 cross the XCDs.
+    Whole plain solves with 64 / 128 / 256 threads, us, FP64 and mixed (the
+    preconditioned ones in the same order), * where the resident kernel does
+    not take the grid:
+      padded   M = 64    277 301 348     306 328 346
+               M = 128   366 426 508     400 435 488
+               M = 256   539 574 694     546 569 659
+               M = 512   1243 1964 1627  1160 1743 1267
+               M = 1024  3053* 1954 2474 2682* 1605 2013
+      periodic M = 64    258 285 333     264 280 311
+               M = 128   331 367 436     330 349 386
+               M = 256   667 540 597     625 472 481
+               M = 512   1072 1189 1806  942 1006 1465
+               M = 1024  3778* - 1764    2457* - 1259
+    (128 at periodic M = 1024 would take more words to meet through than a
+    workspace has).  The table holds the fastest, but for M = 256 and periodic
+    M = 512, where the next smaller size gains another 2 to 10%.  Servers are
+    within 2% with any (one solve of L = 128 alone 7% slower with 256)."""
     return {(32, 1): 64, (64, 0): 64, (64, 1): 64, (128, 0): 64, (128, 1): 64, (256, 1): 128, (512, 1): 64, (512, 0): 128,
             (1024, 1): 128}.get((m, pad), 256)
 

@@ -355,8 +355,11 @@ void iter_pcg_fn(int prec, const PlanTabs& pt, const SlotDesc* slots, int nslots
 }
 
 // The two turns in place of four row passes per iteration, where their grid is
-// resident at once (FP32: 120 VGPRs, four workgroups per CU at M = 4096).
-// Measured with the plan's other choices alike.
+// resident at once (FP32: 120 VGPRs, four workgroups per CU at M = 4096): whole
+// solves, passes -> turns, padded L = 2048 mixed 3200 -> 3072 us, L = 1024 1520
+// -> 1495.  At M = 8192 it is not (2,048 workgroups, of which the device holds
+// 512).  In FP64 at M = 2048, where it would be, it is not built: 2520 us as
+// passes, 2366 with the turns (periodic 2330 and 2140).
 template <typename W>
 constexpr bool kTurnPcgBuilt = !kResBuilt<W> && sizeof(W) == 4 && M >= 2048 && M <= 4096;
 

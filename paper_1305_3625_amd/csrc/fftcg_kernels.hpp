@@ -337,8 +337,11 @@ __device__ __forceinline__ void st2(T* base, unsigned idx, cx<T> c) {
 // W, which is written and read by three passes in a row, stays (mixed solve of
 // L = 4096: 79.9 ms kept, 68.8 passing; column pass 133 -> 110 us, row passes
 // 133 and 89 -> 113 and 76).  Not q's store: the update reads it next (68.8
-// against 69.3 ms).  Below, everything fits (L = 2048: 117 MB FP32, 235 MB
-// FP64), and passing costs: FP32 13.8 -> 14.4 ms, FP64 16.0 -> 18.7.
+// against 69.3 ms).  The periodic grid of L = 4096 (half of W, a quarter of
+// the columns' work) gains as well: whole solves FP32 18.8 -> 17.5 ms, FP64
+// 36.3 -> 27.9, preconditioned 7.1 -> 6.6 and 11.8 -> 9.4.  Below, everything
+// fits (L = 2048: 117 MB FP32, 235 MB FP64), and passing costs: FP32 13.8 ->
+// 14.4 ms, FP64 16.0 -> 18.7.
 template <int L>
 constexpr bool kStream = L >= 4096;
 template <typename T, int L>

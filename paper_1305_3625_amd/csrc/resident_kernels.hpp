@@ -4,9 +4,9 @@
 // of it latency: the launch, the chain of loads (slot descriptor, state, then
 // data), reading the vectors that the previous pass has just written.  Here
 // every workgroup owns RPW rows and CW columns for the whole launch and keeps
-// its parts of r, p, z, the x accumulator and d and its columns' spectrum (on
-// the smaller grids all twiddles too) in registers; only the half spectrum W
-// crosses workgroups, and workgroups meet three times per iteration:
+// its parts of r, p, z, the x accumulator and d and its columns' spectrum in
+// registers; only the half spectrum W crosses workgroups, and workgroups meet
+// three times per iteration:
 //   rows forward -> W | columns of W in place | rows inverse of W, the sums
 //   p.q, r.r, r.q and q.q over the grid -> alpha, r, beta, p.
 // With the preconditioner, z = P^-1 r is three more such phases; an FP64 check
@@ -18,10 +18,11 @@
 // the state.
 //
 // What bounds it: the meetings.  On one XCD a meeting takes 0.7 us and the
-// sums 1.4 us; an iteration takes 6.6 us at padded M = 256 in FP32 (16 us as
-// passes) and 5.9 us at periodic M = 64 in FP64.  Over all XCDs, at padded
-// M = 1024, a meeting takes 2.1 to 3 us and the sums 2.8 us of 14.4 us (FP32)
-// or 18.7 us (FP64; 27 us as passes).
+// sums 1.4 us; an iteration takes 6.3 us at padded M = 256 in FP32 (16 us as
+// passes) and 6.0 us at periodic M = 64 in FP64.  Over all XCDs, at padded
+// M = 1024, a meeting takes 2.1 to 3 us and the sums 2.8 us of 14.1 us (FP32)
+// or 18.5 us (FP64; 27 us as passes).  (Iterations alone, without checks:
+// device times of solves that stop a few iterations apart.)
 //
 // W moves between workgroups inside the launch.  Its accesses go past the
 // CUs' L1 caches, and past the L2 caches where they must reach other XCDs
