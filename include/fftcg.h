@@ -189,10 +189,10 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          passes of solves of its own kind it may start on the grids where
  *          they run on undisturbed (M <= 512, and FP32 without a
  *          preconditioner at M = 1024).  A solve that finds no room runs the
- *          passes, with the same result; with AUTO at M <= 64 the fused
- *          engine.  A grid-wide barrier is used where its grid fits the
- *          device beside the grids of the barriers in flight, else this
- *          solve runs the separate update.
+ *          passes, with bitwise the same result; with AUTO at M <= 64 the
+ *          fused engine.  A grid-wide barrier is used where its grid fits
+ *          the device beside the grids of the barriers in flight, else this
+ *          solve runs the separate update (the same up to rounding, below).
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.
