@@ -494,11 +494,12 @@ static bool overlap(const void* a, const void* b, size_t n) {
 }
 
 // whether products of another stream than s are in flight on the device (one
-// of s itself comes before the solve)
-static bool applies_in_flight(int device, hipStream_t s) {
+// of s itself comes before the solve); large: large ones
+static bool applies_in_flight(int device, hipStream_t s, bool large) {
     std::lock_guard<std::mutex> lk(g_plans_mu);
     for (fftcg_plan_t p : listed_plans()) {
         if (p->device != device || !p->apply_pending.load() || p->apply_stream.load() == s) continue;
+        if (large && DeviceUse::kind(p->M) != DeviceUse::LARGE) continue;
         const hipError_t e = hipEventQuery(p->apply_ev);
         if (e != hipSuccess) (void)hipGetLastError();
         if (e == hipErrorNotReady) return true;
@@ -541,7 +542,7 @@ extern "C" int fftcg_profile_apply(fftcg_plan_t plan, int precision, const doubl
     hipStream_t s = (hipStream_t)stream;
     std::lock_guard<std::mutex> lk(plan->mu);
     DeviceUse use(plan->device);
-    (void)use.passes(DeviceUse::LARGE, 0);
+    (void)use.passes(DeviceUse::kind(plan->M), 0);
     hipEvent_t ev[4];
     for (int i = 0; i < 4; ++i)
         if (hipEventCreate(&ev[i]) != hipSuccess) return FFTCG_EDEVICE;
@@ -587,7 +588,7 @@ extern "C" int fftcg_profile_iteration(fftcg_plan_t plan, int precision, const d
     const bool turn = grid && plan_turn(plan, precision);
     if (turn && reps < 2) return FFTCG_EINVAL;
     DeviceUse use(plan->device);
-    (void)use.passes(DeviceUse::LARGE, grid ? plan_barrier_fits(plan, precision) : 0);
+    (void)use.passes(DeviceUse::kind(plan->M), grid ? plan_barrier_fits(plan, precision) : 0);
     // the launches in the order a solve's chunk makes them: with the turn
     // pass row_fwd, col, (turn, col) x (reps - 1), row_inv; else per
     // iteration row_fwd, col, row_inv and (without the folded update) update
@@ -915,13 +916,10 @@ static int solve_multipass_once(fftcg_plan_t plan, Workspace* w, int precision, 
                                 const double* x0, double tol, int maxit, double* x, fftcg_info* info,
                                 hipStream_t s, const uint8_t* mask, bool grid);
 
-// Light solves whose passes a resident solve of this plan may start beside
-// (DeviceUse): any number up to M = 512, where the workgroups of every pass
-// fit beside resident ones (112 registers beside at most 394 of 512).  At M =
-// 1024 a workgroup of the FP64 column pass takes 220 registers of a SIMD, and
-// the resident kernel 272 (FP32), 300 (FP32 preconditioned) or 382 and more
-// (FP64): only the first leaves room, for two such solves (with three more
-// solves beside it four threads solve 1,275 per second, 1,410 as passes).
+// Small passes (of solves and servers) that a resident solve of this plan may
+// start beside (DeviceUse): any number up to M = 512, two of a plain FP32
+// solve at M = 1024 (with three more solves beside it four threads solve 1,275
+// per second, 1,410 as passes), none in FP64 or preconditioned there.
 static int resident_beside(fftcg_plan_t plan, int precision) {
     if (plan->M <= 512) return 1 << 30;
     return plan->precond == FFTCG_PRECOND_NONE && precision == FFTCG_MIXED ? 2 : 0;
@@ -939,7 +937,8 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
     DeviceUse use(plan->device);
     const int beside = resident_beside(plan, precision);
     if (plan_resident(plan, precision)) {
-        const bool room = !applies_in_flight(plan->device, s) && use.resident(plan->ops->resident_xcds(precision), beside);
+        const bool room = !applies_in_flight(plan->device, s, beside > 0) &&
+                          use.resident(plan->ops->resident_xcds(precision), beside);
         if (room) {
             w = plan_acquire(plan);
             if (!w) return FFTCG_ENOMEM;
@@ -973,10 +972,7 @@ static int solve_multipass(fftcg_plan_t plan, int precision, const double* d, co
     // the folded update (any mode but 0), or the preconditioned turns (1, 2),
     // where their grids find room
     const int fits = plan_barrier_fits(plan, precision);
-    const DeviceUse::Kind kind = !plan_resident(plan, precision) ? DeviceUse::LARGE
-                                 : beside > 0                     ? DeviceUse::LIGHT
-                                                                  : DeviceUse::HEAVY;
-    bool grid = use.passes(kind, fits);
+    bool grid = use.passes(DeviceUse::kind(plan->M), fits);
     int rc = FFTCG_OK;
     // a warm start in place is kept in q, which the grid-synchronised path
     // never writes, so that a solve abandoned at a barrier can be repeated

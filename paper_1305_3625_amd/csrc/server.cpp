@@ -579,9 +579,10 @@ void serve_reservations(fftcg_server_s* srv) {
 
 void scheduler(fftcg_server_s* srv) {
     (void)hipSetDevice(srv->opts.device);
-    // single solves of the process keep clear of a server at work
+    // single solves of the process keep clear of a server at work, by its
+    // largest class (-1: none at work)
     DeviceUse use(srv->opts.device);
-    bool used = false;
+    int used = -1;
     while (!srv->stop.load()) {
         serve_reservations(srv);
         std::vector<Class*> cls;
@@ -590,21 +591,22 @@ void scheduler(fftcg_server_s* srv) {
             for (auto& kv : srv->classes) cls.push_back(kv.second.get());
         }
         bool busy = false;
+        int kind = -1;
         for (Class* c : cls) {
             // an exception (a failed host allocation) must not end the
             // thread: the class is simply visited again on the next pass
+            bool at_work = true;
             try {
-                busy |= progress(srv, c);
+                at_work = progress(srv, c);
             } catch (...) {
-                busy = true;
             }
+            busy |= at_work;
+            if (at_work) kind = std::max<int>(kind, DeviceUse::kind(c->plan->M));
         }
-        if (busy != used) {
-            if (busy)
-                (void)use.passes(DeviceUse::LARGE, 0);
-            else
-                use.end();
-            used = busy;
+        if (kind != used) {
+            use.end();
+            if (kind >= 0) (void)use.passes((DeviceUse::Kind)kind, 0);
+            used = kind;
         }
         if (!busy) {
             std::unique_lock<std::mutex> lk(srv->mu);

@@ -6,9 +6,8 @@ its launch.
 
 A resident kernel keeps its CUs for a whole solve, and every launch of
 another solve's passes whose workgroups do not fit beside it waits for its
-end: resident solves start only where no passes are in flight but those of
-light solves (up to M = 512, and plain FP32 ones of M = 1024) that found no
-room themselves."""
+end: no resident solve starts beside passes above M = 1024, and at M = 1024
+those in FP64 or with the preconditioner start alone."""
 
 import ctypes
 import os
@@ -184,15 +183,13 @@ def _hold(fake, p, kind=None, **kw):
     return InFlight(fake, lambda: p.solve(**kw), kind)
 
 
-@pytest.mark.parametrize("big,precond", [((2048, 1), 0), ((2048, 1), 1), ((1024, 0), 0)])
-def test_no_resident_solve_beside_passes(fake, big, precond):
+@pytest.mark.parametrize("big,precond", [((2048, 1), 0), ((2048, 1), 1), ((1024, 1), 0), ((4096, 0), 1)])
+def test_no_resident_solve_beside_large_passes(fake, big, precond):
     p, small, mid, tiny = fake.plan(*big, precond), fake.plan(128, 1), fake.plan(512, 1), fake.plan(64, 0)
-    if big[0] == 1024:  # a grid that has the resident kernel, with the passes asked for
-        assert fake.lib.fftcg_plan_set_grid_sync(p.h, 3) == 0
     with _hold(fake, p):
         for q in (small, mid):
             # a grid that fills the device leaves no room for their barriers either
-            assert q.solve() == ["separate" if big[0] == 2048 else "turn"]
+            assert q.solve() == ["turn" if big[0] == 1024 else "separate"]
         assert tiny.solve() == ["fused"]
     for q in (small, mid, tiny):
         assert q.solve() == ["resident"]
@@ -223,30 +220,23 @@ def test_resident_solves_beside_each_other(fake):
     q.close()
 
 
-def test_resident_beside_light_passes(fake):
-    """M = 512: any number of solves of its kind; M = 1024: plain FP32 beside
-    two of them, FP64 and the preconditioned alone."""
-    p, q, h = fake.plan(256, 1), fake.plan(512, 1), fake.plan(512, 1, 1)
-    for plan, n in ((p, 5), (q, 2)):
-        first = _hold(fake, plan, RESIDENT).__enter__()
-        held = [_hold(fake, plan, CHUNK).__enter__() for _ in range(n)]
-        first.__exit__()
-        with _hold(fake, plan, RESIDENT):  # entered: the resident kernel again
-            pass
-        before = plan.routes()["resident"]
+@pytest.mark.parametrize("precision,precond", [(FP64, 0), (MIXED, 0), (FP64, 1)])
+def test_resident_beside_small_passes(fake, precision, precond):
+    """Up to M = 512 beside any number of solves with M <= 1024 that run the
+    passes; the plain FP32 solve of M = 1024 beside two, FP64 and the
+    preconditioned alone."""
+    bg, p, q, h = fake.plan(512, 1, precond), fake.plan(256, 1), fake.plan(512, 1), fake.plan(512, 1, 1)
+    assert fake.lib.fftcg_plan_set_grid_sync(bg.h, 3) == 0  # its solves run the passes
+    held = []
+    for n in range(1, 6):
+        held.append(_hold(fake, bg, precision=precision).__enter__())
+        assert p.solve() == ["resident"] and p.solve(FP64) == ["resident"]
+        assert q.solve() == ["resident" if n <= 2 else "turn"]
         assert q.solve(FP64) == ["turn"] and h.solve() == ["separate"]
-        assert p.solve() == ["resident"] and plan.routes()["resident"] == before + (plan is p)
-        if plan is q:
-            with _hold(fake, q, RESIDENT):
-                held.append(_hold(fake, q, CHUNK).__enter__())
-            assert q.solve() == ["turn"]  # beside three
-        for x in held:
-            x.__exit__()
-    with _hold(fake, h, RESIDENT):
-        with _hold(fake, q, CHUNK, precision=FP64):
-            assert p.solve() == ["turn"]
+    for x in held:
+        x.__exit__()
     assert q.solve(FP64) == ["resident"] and h.solve() == ["resident"]
-    for x in (p, q, h):
+    for x in (bg, p, q, h):
         x.close()
 
 
@@ -289,7 +279,17 @@ def test_products_in_flight(fake):
     assert q.solve(stream=P(32)) == ["resident"]
     p.close()
     assert q.solve(stream=P(32)) == ["resident"]
-    q.close()
+    # products of M <= 1024: as small passes
+    p, r = fake.plan(512, 1), fake.plan(512, 1)
+    fake.lib.fake_hold_events(1)
+    try:
+        assert fake.lib.fftcg_apply(p.h, FP64, *ptr, P(16)) == 0
+        assert q.solve(stream=P(32)) == ["resident"] and r.solve(stream=P(32)) == ["resident"]
+        assert r.solve(FP64, stream=P(32)) == ["turn"] and r.solve(FP64, stream=P(16)) == ["resident"]
+    finally:
+        fake.lib.fake_hold_events(0)
+    for x in (p, q, r):
+        x.close()
 
 
 def test_resident_words_cleared_or_not_used(fake):
