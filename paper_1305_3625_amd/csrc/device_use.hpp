@@ -98,7 +98,7 @@ public:
 private:
     static constexpr int kDevices = 64;
     struct Device {
-        unsigned xcds;  // XCDs that resident solves hold, a bit each
+        unsigned xcds;  // XCDs that resident solves hold, a bit each, by their hardware number
         int small;      // solves that run the passes, and servers at work,
         int large;      // by kind
         double share;   // of the device, by grids with a barrier

@@ -21,7 +21,8 @@ struct ResidentRun {
     SlotDesc slot;              // the descriptor itself
     unsigned long long* words;  // kMeetWords 64-bit words the workgroups meet through
     unsigned long long token;   // first of kResidentTokens tokens that no launch on the words has used (they grow)
-    int xcd;                    // the XCD to run on, where resident_xcds is 1
+    int xcd;                    // the XCD to run on (its hardware number), where resident_xcds is 1
+    int gen;                    // mark of this launch: the state it leaves carries it (SolveState::gen)
     int K;                      // iterations at most, <= kResidentIters
     int first;                  // 1: the solve begins; 0: it goes on
     int zero;                   // with first: from x = 0 (slot.x is not read)

@@ -255,7 +255,7 @@ template <typename W>
 void resident_t(bool pcg, const PlanTabs& pt, const ResidentRun& rr, const SolveState& st, hipStream_t s) {
     if constexpr (kResBuilt<W>) {
         using R = RGeo<W, M, PAD>;
-        const ResArgs a{rr.slot, rr.words, rr.token, rr.xcd, rr.K, rr.first, rr.zero};
+        const ResArgs a{rr.slot, rr.words, rr.token, rr.xcd, rr.gen, rr.K, rr.first, rr.zero};
         const dim3 grid(R::NB * (R::ONEX ? 8 : 1)), block(R::NT);
         if (pcg)
             hipLaunchKernelGGL((k_solve_resident<W, M, PAD, R::NT, true>), grid, block, 0, s, tab_of<W>(pt),

@@ -890,22 +890,25 @@ static int solve_resident(fftcg_plan_t plan, Workspace* w, int precision, const 
     if (x0 && x0 != x && hipMemcpyAsync(x, x0, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess) return FFTCG_EDEVICE;
     if (x0 && x0 == x && hipMemcpyAsync(w->q, x, n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return FFTCG_EDEVICE;
-    ResidentRun run{*w->h_slot, w->meet, 0, xcd, kResidentIters, 1, x0 ? 0 : 1};
+    ResidentRun run{*w->h_slot, w->meet, 0, xcd, 0, kResidentIters, 1, x0 ? 0 : 1};
     SolveState st;
     do {
         run.token = w->grid_token + 1;
         w->grid_token += kResidentTokens;
+        run.gen = ++w->resident_gen;
         plan->ops->resident(precision, plan->precond != FFTCG_PRECOND_NONE, plan->tabs, run, init, s);
         if (hipGetLastError() != hipSuccess || hipEventRecord(w->ev1, s) != hipSuccess ||
             hipMemcpyAsync(w->h_state, w->st, sizeof(SolveState), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return FFTCG_EDEVICE;
         st = *w->h_state;
+        // (a state that this launch has not left: it gave up, or no workgroup
+        // ran on the XCD asked for)
+        if (st.gen != run.gen || st.status == ST_EGRID) return ST_EGRID;
         run.first = run.zero = 0;
     } while (!st.done);
     if (st.bzero && (hipMemsetAsync(x, 0, n * 8, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess))
         return FFTCG_EDEVICE;
-    if (st.status == ST_EGRID) return ST_EGRID;
     float ms = 0.f;
     (void)hipEventElapsedTime(&ms, w->ev0, w->ev1);
     fill_info(info, st, ms);

@@ -56,6 +56,7 @@ struct Workspace {
     // launches of the grid-synchronised update on this workspace's partial
     // sums (each launch's barrier token is the next value)
     unsigned long long grid_token = 0;
+    int resident_gen = 0;  // resident launches so far
     unsigned long long* meet = nullptr;  // kMeetWords words of the resident kernel (made by its first solve)
     int init(int L, int M, int stride);
     void release();

@@ -121,6 +121,13 @@ __device__ __forceinline__ void gst_all(cx<T>* base, unsigned idx, cx<T> c) {
 }
 __device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// The XCD that the workgroup runs on.
+__device__ __forceinline__ unsigned xcc_id() {
+    unsigned x;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
+    return x;
+}
+
 // ---- meetings of all workgroups -------------------------------------------------
 // The workgroups of one XCD form a group (workgroups go to the XCDs round
 // robin; hello() checks it).  Members tell their group's leader through the
@@ -199,18 +206,26 @@ struct Meet {
         return *s_ok != 0;
     }
     // The first meeting of a launch, safe wherever the workgroups run: every
-    // member must share its leader's XCD.
+    // member must share its leader's XCD, and no two may be the same member
+    // (on one XCD the members are those that run there: two that both were
+    // there in every eight would be; the later one leaves, and the one that is
+    // missing for it ends the launch).
     __device__ __forceinline__ bool hello(unsigned long long token, int* s_ok) const {
-        unsigned xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        const unsigned long long mine = token * 256 + xcc % 255;
+        const unsigned long long mine = token * 256 + xcc_id() % 255;
         drain();
         __syncthreads();
         if (threadIdx.x < 64) {
             const int lane = threadIdx.x;
-            if (lane == 0) word_put<true>(base + HELLO + g * GS + i, mine);
             bool ok = true;
-            if (i == 0) {
+            if (lane == 0) {
+                if constexpr (NG == 1)
+                    ok = __hip_atomic_exchange(gbl(base + HELLO + i), mine, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) / 256 != token;
+                else
+                    word_put<true>(base + HELLO + g * GS + i, mine);
+            }
+            ok = __all(ok);
+            if (ok && i == 0) {
                 ok = wave_wait([&] { return lane >= GM || word_get(base + HELLO + g * GS + lane) / 256 == token; });
                 const bool same = __all(lane >= GM || word_get(base + HELLO + g * GS + lane) == mine);
                 if (ok && lane == 0) word_put<true>(base + HREL + g, token * 256 + (same ? 0 : 255));
@@ -581,6 +596,7 @@ struct ResArgs {
     unsigned long long* words;  // kMeetWords
     unsigned long long token;   // the first of the launch's meetings' tokens
     int xcd;                    // the XCD to run on (one-XCD grids)
+    int gen;                    // the launch's mark, which the state it leaves carries
     int K;                      // iterations of this launch at most
     int first;                  // the solve begins: state from the argument, no vectors yet
     int zero;                   // ... from x = 0
@@ -637,13 +653,18 @@ __global__ void __launch_bounds__(NT) k_solve_resident(Tab<T> tab, Tab<double> t
     __shared__ double s_tot[8];
     __shared__ int s_ok, s_go;
     __shared__ SolveState st;
-    // one-XCD grids: eight times the workgroups are launched, and those of
-    // the XCD asked for stay
-    if (R::ONEX && (int)(blockIdx.x & 7) != ra.xcd) return;
+    // one-XCD grids: eight times the workgroups are launched, and those that
+    // run on the XCD asked for stay: one of every eight, as workgroups go to the
+    // XCDs in turn (from which one on depends on the stream's queue, so the
+    // XCD is not known from the index)
+    if (R::ONEX && (int)xcc_id() != ra.xcd) return;
     const int blk = R::ONEX ? blockIdx.x >> 3 : blockIdx.x;
     const SlotDesc& sd = ra.sd;
     const int tid = threadIdx.x;
-    if (tid == 0) st = ra.first ? init : *sd.st;
+    if (tid == 0) {
+        st = ra.first ? init : *sd.st;
+        st.gen = ra.gen;
+    }
     __syncthreads();
     if (st.done) return;
     const bool rows = tid < RT;  // this thread holds a part of a row

@@ -33,7 +33,9 @@ namespace {
 enum Kind { kApply, kResident, kChunk, kSeparate, kFused };
 typedef void (*Hook)(int kind, int M, int precision);
 std::atomic<Hook> g_hook{nullptr};
-std::atomic<int> g_give_up{0};         // bit 0: the resident kernel, bit 1: the barriers
+// bit 0: the resident kernel, bit 1: the barriers; bit 2: no workgroup of the
+// resident kernel runs (it leaves the state as it was)
+std::atomic<int> g_give_up{0};
 std::atomic<size_t> g_fail_memset{0};  // bytes of the memset that fails (once)
 std::atomic<int> g_hold_events{0};
 std::atomic<int> g_words_clear{-1};  // whether the last resident launch's words held no token
@@ -162,11 +164,13 @@ struct Fake {
         chunk(prec, s);
     }
     static void resident(int prec, bool, const PlanTabs&, const ResidentRun& r, const SolveState& st, hipStream_t) {
-        if (r.first) *r.slot.st = st;
+        if (r.first && !(g_give_up.load() & 4)) *r.slot.st = st;
         int clear = 1;
         for (int i = 0; i < kMeetWords; ++i) clear &= r.words[i] < r.token;
         g_words_clear.store(clear);
         hook(kResident, M, prec);
+        if (g_give_up.load() & 4) return;
+        r.slot.st->gen = r.gen;
         finish(r.slot, L, g_give_up.load() & 1 ? ST_EGRID : FFTCG_OK);
     }
     static int resident_xcds(int) { return M <= 256 ? 1 : 8; }

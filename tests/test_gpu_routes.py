@@ -163,3 +163,43 @@ def test_refused_solve_runs_turn_pass(L, padded, precision):
     assert after["separate"] == before["separate"]
     plan.close()
     other.close()
+
+
+@pytest.mark.parametrize("L,padded,precision,precond", [(128, 1, binding.FP64, 1), (256, 0, binding.FP64, 1),
+                                                        (128, 1, binding.FP64, 0), (128, 1, binding.MIXED, 1),
+                                                        (64, 0, binding.FP64, 0)])
+def test_eight_resident_solves_on_eight_xcds(L, padded, precision, precond):
+    """Eight threads solve at once, each on a stream of its own: every solve
+    finds an XCD that no other holds, whatever XCD the stream's queue begins
+    with (where two shared one, workgroups of both kept each other out, and the
+    meetings gave up)."""
+    import threading
+    import torch
+    inst = (padded_instance if padded else periodic_instance)(L, [36, L, padded], eps=1e-3)
+    plan = binding.Plan(L, padded, inst["ghat"])
+    plan.set_precond(precond)
+    banner("route-eight", L, padded, precision, precond)
+    want, winfo, got = _route(plan, inst, precision)
+    assert got == "resident"
+    D, B = [dev(inst["d"]) for _ in range(8)], [dev(inst["b"]) for _ in range(8)]
+    X = [torch.zeros((L, L), dtype=torch.float64, device="cuda") for _ in range(8)]
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    torch.cuda.synchronize()
+    before = plan.solve_routes()
+
+    def work(k):
+        for _ in range(15):
+            plan.solve(D[k], B[k], X[k], tol=1e-8, precision=precision, stream=streams[k])
+
+    th = [threading.Thread(target=work, args=(k,)) for k in range(8)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    torch.cuda.synchronize()
+    after = plan.solve_routes()
+    print(after)
+    assert plan.grid_sync(precision) != binding.GRID_FELL_BACK
+    assert after["resident"] - before["resident"] == 8 * 15
+    assert all(np.array_equal(host(x), want) for x in X)
+    plan.close()

@@ -317,3 +317,17 @@ def test_device_bytes_counts_the_product_buffer(fake, L, padded):
     fused = 2 * M * 12 + quarter * 12 if M <= 256 else 0
     assert n.value == tables + fused + (M // 2) * (L * 16 + 128)
     p.close()
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+def test_resident_launch_that_left_no_state(fake, in_place):
+    """The state belongs to the launch whose mark it carries: one that an
+    earlier solve left (done, solved) is not taken for this one's."""
+    p = fake.plan(128, 1)
+    assert p.solve() == ["resident"]
+    fake.lib.fake_give_up(4)
+    try:
+        assert p.solve(in_place=in_place) == ["separate"]
+    finally:
+        fake.lib.fake_give_up(0)
+    p.close()
