@@ -184,15 +184,15 @@ int fftcg_plan_set_error_target(fftcg_plan_t plan, int precision, double tau);
  *          workgroups of one XCD (M <= 256) or of the whole device meet three
  *          times per product.  Such a solve holds its XCD (or the device)
  *          until it ends, so it starts only where an XCD (the whole device)
- *          is free of others of this process, and no other solve's passes,
- *          server at work or product of another stream is in flight; beside
- *          passes of solves of its own kind it may start on the grids where
- *          they run on undisturbed (M <= 512, and FP32 without a
- *          preconditioner at M = 1024).  A solve that finds no room runs the
- *          passes, with bitwise the same result; with AUTO at M <= 64 the
- *          fused engine.  A grid-wide barrier is used where its grid fits
- *          the device beside the grids of the barriers in flight, else this
- *          solve runs the separate update (the same up to rounding, below).
+ *          is free of others of this process, and where no passes are in
+ *          flight (of another solve, a server at work or a product of
+ *          another stream) that it would hold up: none above M = 1024, and
+ *          at M = 1024 in FP64 or preconditioned none at all.  A solve that
+ *          finds no room runs the passes, with bitwise the same result; with
+ *          AUTO at M <= 64 the fused engine.  A grid-wide barrier is used
+ *          where its grid fits the device beside the grids of the barriers
+ *          in flight, else this solve runs the separate update (the same up
+ *          to rounding, below).
  *   mode 0: the separate update kernel (as server classes always use).
  *   mode 2: as mode 1 with the barrier's wait limit at zero, so that
  *          workgroups give up at once; for tests of the fallback below.
