@@ -523,10 +523,15 @@ extern "C" int fftcg_apply(fftcg_plan_t plan, int precision, const double* d, co
     HIPCHK(hipStreamWaitEvent(s, plan->apply_ev, 0));
     plan->ops->apply(precision, plan->tabs, d, x, y, plan->apply_W, s);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipEventRecord(plan->apply_ev, s));
-    // (a captured product is not in flight, and its event cannot be queried)
+    // (a captured product is not in flight, and its event must not be queried:
+    // that can end the capture)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (!eager) {
+        std::lock_guard<std::mutex> plans(g_plans_mu);  // no query of an earlier product is under way
+        plan->apply_pending.store(false);
+    }
+    HIPCHK(hipEventRecord(plan->apply_ev, s));
     plan->apply_stream.store(s);
     plan->apply_pending.store(eager);
     return FFTCG_OK;

@@ -27,10 +27,11 @@ using namespace fftcg;
 
 struct FakeEvent {
     std::atomic<int> pending{0};
+    std::atomic<int> captured{0};  // last recorded in a capture
 };
 
 namespace {
-enum Kind { kApply, kResident, kChunk, kSeparate, kFused };
+enum Kind { kApply, kResident, kChunk, kSeparate, kFused, kCapturedRecord };
 typedef void (*Hook)(int kind, int M, int precision);
 std::atomic<Hook> g_hook{nullptr};
 // bit 0: the resident kernel, bit 1: the barriers; bit 2: no workgroup of the
@@ -38,6 +39,8 @@ std::atomic<Hook> g_hook{nullptr};
 std::atomic<int> g_give_up{0};
 std::atomic<size_t> g_fail_memset{0};  // bytes of the memset that fails (once)
 std::atomic<int> g_hold_events{0};
+std::atomic<int> g_capture{0};           // whether streams are being captured
+std::atomic<int> g_captured_queries{0};  // queries of events last recorded in a capture
 std::atomic<int> g_words_clear{-1};  // whether the last resident launch's words held no token
 
 void hook(Kind k, int M, int prec) {
@@ -98,10 +101,13 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
 }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+    e->captured.store(g_capture.load());
     e->pending.store(g_hold_events.load());
+    if (g_capture.load()) hook(kCapturedRecord, 0, 0);
     return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t e) {
+    if (e->captured.load()) g_captured_queries += 1;
     return e->pending.load() && g_hold_events.load() ? hipErrorNotReady : hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
@@ -115,7 +121,7 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
-    *c = hipStreamCaptureStatusNone;
+    *c = g_capture.load() ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
 hipError_t hipGetDeviceCount(int* n) {
@@ -267,5 +273,7 @@ extern "C" void fake_set_hook(Hook h) { g_hook.store(h); }
 extern "C" void fake_give_up(int bits) { g_give_up.store(bits); }
 extern "C" void fake_fail_memset(size_t n) { g_fail_memset.store(n); }
 extern "C" void fake_hold_events(int h) { g_hold_events.store(h); }
+extern "C" void fake_capture(int c) { g_capture.store(c); }
+extern "C" int fake_captured_queries(void) { return g_captured_queries.load(); }
 extern "C" int fake_words_clear(void) { return g_words_clear.load(); }
 extern "C" size_t fake_meet_bytes(void) { return (size_t)kMeetWords * 8; }

@@ -83,7 +83,7 @@ hipError_t hipMemset(void* dst, int v, size_t n);
 hipError_t hipEventCreate(hipEvent_t* e);
 hipError_t hipEventSynchronize(hipEvent_t e);
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b);
-typedef enum { hipStreamCaptureStatusNone = 0 } hipStreamCaptureStatus;
+typedef enum { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 } hipStreamCaptureStatus;
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c);
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 hipError_t hipSetDevice(int d);

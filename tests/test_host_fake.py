@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BUILD = os.path.join(ROOT, "_build", "fake")
 P, I, D, S = ctypes.c_void_p, ctypes.c_int, ctypes.c_double, ctypes.c_size_t
 FP64, MIXED = 0, 1
-APPLY, RESIDENT, CHUNK, SEPARATE, FUSED = range(5)
+APPLY, RESIDENT, CHUNK, SEPARATE, FUSED, CAPTURED_RECORD = range(6)
 ROUTES = ("fused", "resident", "turn", "folded", "separate")
 HOOK = ctypes.CFUNCTYPE(None, I, I, I)
 
@@ -290,6 +290,32 @@ def test_products_in_flight(fake):
         fake.lib.fake_hold_events(0)
     for x in (p, q, r):
         x.close()
+
+
+def test_captured_products_are_not_queried(fake):
+    """The event of a product that is being captured must not be queried (the
+    query can end the capture): not after it, and not while it is recorded
+    over that of an earlier product still in flight."""
+    p, q = fake.plan(2048, 1), fake.plan(128, 1)
+    a = [np.zeros(2048 * 2048) for _ in range(3)]
+    ptr = [v.ctypes.data_as(P) for v in a]
+    fake.lib.fake_hold_events(1)
+    try:
+        assert fake.lib.fftcg_apply(p.h, FP64, *ptr, P(16)) == 0
+        assert q.solve(stream=P(32)) == ["turn"]
+        n = fake.lib.fake_captured_queries()
+        fake.lib.fake_capture(1)
+        with InFlight(fake, lambda: fake.lib.fftcg_apply(p.h, FP64, *ptr, P(16)), CAPTURED_RECORD) as c:
+            fake.lib.fake_capture(0)
+            q.solve(stream=P(32))
+        assert c.out == 0
+        q.solve(stream=P(32))
+        assert fake.lib.fake_captured_queries() == n
+    finally:
+        fake.lib.fake_capture(0)
+        fake.lib.fake_hold_events(0)
+    p.close()
+    q.close()
 
 
 def test_resident_words_cleared_or_not_used(fake):
