@@ -18,10 +18,10 @@
 // the state.
 //
 // What bounds it: the meetings.  On one XCD a meeting takes 0.7 us and the
-// sums 1.4 us; an iteration takes 6.3 us at padded M = 256 in FP32 (16 us as
-// passes) and 6.0 us at periodic M = 64 in FP64.  Over all XCDs, at padded
-// M = 1024, a meeting takes 2.1 to 3 us and the sums 2.8 us of 14.1 us (FP32)
-// or 18.5 us (FP64; 27 us as passes).  (Iterations alone, without checks:
+// sums 1.4 us; an iteration takes 6.2 us at padded M = 256 in FP32 (16 us as
+// passes) and 5.9 us at periodic M = 64 in FP64.  Over all XCDs, at padded
+// M = 1024, a meeting takes 2.1 to 3 us and the sums 2.8 us of 14.2 us (FP32)
+// or 18.7 us (FP64; 27 us as passes).  (Iterations alone, without checks:
 // device times of solves that stop a few iterations apart.)
 //
 // W moves between workgroups inside the launch.  Its accesses go past the
